@@ -167,11 +167,12 @@ int lbm_create(const lbm_grid* grid, const uint8_t* solid_mask, double tau,
   off = align256(off + size_t(g.ny) * sizeof(double));
   h->off_motion = off;
   off = align256(off + sizeof(BodyMotion));
-  // Force partials of two steps, with room for masks that need up to twice the slots
-  // of this one (plus 4096 doubles): a body moving through the grid keeps the layout.
+  // Force partials of two launches of kFuse steps, with room for masks that need up to
+  // twice the slots of this one (plus 4096 doubles): a body moving through the grid keeps
+  // the layout.
   h->part_cap = 2 * h->part_doubles() + 4096;
   h->off_part = off;
-  off = align256(off + 2 * h->part_cap * sizeof(double));
+  off = align256(off + 2 * kFuse * h->part_cap * sizeof(double));
   h->njblocks = h->plan.has_box ? h->plan.box_bx * h->plan.box_rows : 0;
   h->jcap = h->njblocks;
   h->off_jpart = off;
@@ -235,7 +236,9 @@ DevTables ws_tables(const lbm_t* h) {
   t.uin = reinterpret_cast<const double*>(h->ws + h->off_uin);
   t.motion = h->motion_dev();
   t.part[0] = h->part(0);
-  t.part[1] = h->part(1);
+  t.part[1] = h->part(kFuse);
+  t.part_stride = int64_t(h->part_cap);
+  t.fuse = true;
   t.jpart = reinterpret_cast<double*>(h->ws + h->off_jpart);
   return t;
 }
@@ -329,33 +332,70 @@ BoxArgs box_args(const lbm_t* h, const void* src, const DevTables& t) {
 
 namespace {
 
+// Work map of fused launches for n steps between two alternating buffers, or one without blocks
+// where single steps are the faster or the only form.
+FuseMap fuse_for(const lbm_t* h, const DevTables& t, int32_t n) {
+  const FuseMap none{};
+  if (n < kFuse || !t.fuse || h->buf_bytes32() == 0) return none;
+  const FuseMap m = fuse_map(h->plan, int(h->esz));
+  const FuseRect& r = m.r[0];
+  const double nodes = double(h->g.nx) * h->g.ny;
+  const double body =
+      r.kind == kFuseBody ? double(r.x1 - r.x0) * (r.y1 - r.y0) / nodes : 0.0;
+  return fuse_pays(h->g.precision, h->g.collision, nodes, body) ? m : none;
+}
+
 // Enqueue n >= 1 steps; step k reads io(k).first and writes io(k).second.  With a
 // non-null ring, the force row of step k goes to ring row k (rows are self-contained:
 // the J of the following step, or of the pull after the last one, is stored with it).
+// `alternate`: io takes two buffers in turns, so that kFuse (odd) steps may go in one launch.
 template <class IO>
 int enqueue_steps(lbm_t* h, const DevTables& t, hipStream_t stream, int32_t n, double* ring,
-                  int64_t step0, IO&& io) {
+                  int64_t step0, bool alternate, IO&& io) {
   const Plan& p = h->plan;
   const bool forces = ring != nullptr;
   StepArgs a = step_args(h, t);
+  FuseArgs q{};
+  q.map = alternate ? fuse_for(h, t, n) : FuseMap{};
+  q.part_stride = t.part_stride;
   const void* last = nullptr;
-  for (int32_t k = 0; k < n; ++k) {
+  // Single steps first, then the fused launches: a launch reduces the rows of the one before
+  // it (steps [k - in_last, k), partials in part[1 - turn]).
+  const int32_t singles = q.map.nblocks > 0 ? n % kFuse : n;
+  int turn = 0, in_last = 0;
+  for (int32_t k = 0; k < n; k += in_last, turn ^= 1) {
     const auto sd = io(k);
     a.src = sd.first;
-    a.dst = sd.second;
-    a.step_key = sr_step_key(step0 + k);
-    last = sd.second;
-    a.part_out = forces ? t.part[k & 1] : nullptr;
-    a.red_in = nullptr;
-    a.red_row = nullptr;
-    a.red_prev_jnext = nullptr;
-    if (forces && k >= 1) {
-      a.red_in = t.part[(k - 1) & 1];
-      a.red_row = ring + int64_t(k - 1) * kRow;
-      a.red_prev_jnext = k >= 2 ? ring + int64_t(k - 2) * kRow + kJnext : nullptr;
+    hipError_t e;
+    if (k < singles) {
+      a.dst = sd.second;
+      a.step_key = sr_step_key(step0 + k);
+      a.part_out = forces ? t.part[turn] : nullptr;
+      a.red_in = nullptr;
+      a.red_row = nullptr;
+      a.red_prev_jnext = nullptr;
+      if (forces && k >= 1) {
+        a.red_in = t.part[1 - turn];
+        a.red_row = ring + int64_t(k - 1) * kRow;
+        a.red_prev_jnext = k >= 2 ? ring + int64_t(k - 2) * kRow + kJnext : nullptr;
+      }
+      e = launch_step(h->g.precision, forces, a, stream);
+      in_last = 1;
+    } else {
+      a.dst = io(k + kFuse - 1).second;
+      for (int j = 0; j < kFuse; ++j) q.step_key[j] = sr_step_key(step0 + k + j);
+      q.part_out = forces ? t.part[turn] : nullptr;
+      q.nred = forces ? in_last : 0;
+      if (q.nred) {
+        q.red_in = t.part[1 - turn];
+        q.red_row = ring + int64_t(k - in_last) * kRow;
+        q.red_has_prev = k - in_last >= 1;
+      }
+      e = launch_fused(h->g.precision, forces, a, q, stream);
+      in_last = kFuse;
     }
-    hipError_t e = launch_step(h->g.precision, forces, a, stream);
     if (e != hipSuccess) return h->hip_fail(e, "launch step");
+    last = a.dst;
   }
   if (forces) {
     if (p.has_box) {
@@ -364,11 +404,13 @@ int enqueue_steps(lbm_t* h, const DevTables& t, hipStream_t stream, int32_t n, d
       if (e != hipSuccess) return h->hip_fail(e, "launch box momentum");
     }
     FinalArgs f{};
-    f.red_in = t.part[(n - 1) & 1];
+    f.nrows = in_last;
+    f.red_in = t.part[1 - turn];
+    f.part_stride = t.part_stride;
     f.nslots = p.nslots;
     f.njslots = p.njslots;
-    f.row = ring + int64_t(n - 1) * kRow;
-    f.prev_jnext = n >= 2 ? ring + int64_t(n - 2) * kRow + kJnext : nullptr;
+    f.row = ring + int64_t(n - in_last) * kRow;
+    f.prev_jnext = n > in_last ? ring + int64_t(n - in_last - 1) * kRow + kJnext : nullptr;
     f.jpart = p.has_box ? t.jpart : nullptr;
     f.njblocks = h->njblocks;
     hipError_t e = launch_finalize(f, stream);
@@ -380,7 +422,8 @@ int enqueue_steps(lbm_t* h, const DevTables& t, hipStream_t stream, int32_t n, d
 // n steps on the handle's own ping-pong state buffers.
 int enqueue_own_steps(lbm_t* h, int32_t n, double* ring) {
   const int c0 = h->cur;
-  const int rc = enqueue_steps(h, ws_tables(h), h->stream, n, ring, h->steps_done, [&](int32_t k) {
+  const int rc = enqueue_steps(h, ws_tables(h), h->stream, n, ring, h->steps_done, true,
+                               [&](int32_t k) {
     const int s = (c0 + k) & 1;
     return std::pair<const void*, void*>(h->buf(s), h->buf(1 - s));
   });
@@ -397,7 +440,7 @@ namespace lbm {
 
 int enqueue_pingpong(lbm_t* h, const DevTables& t, void* b0, void* b1, hipStream_t stream,
                      int32_t n, double* ring) {
-  return enqueue_steps(h, t, stream, n, ring, 0, [&](int32_t k) {
+  return enqueue_steps(h, t, stream, n, ring, 0, true, [&](int32_t k) {
     return (k & 1) ? std::pair<const void*, void*>(b1, b0) : std::pair<const void*, void*>(b0, b1);
   });
 }
@@ -1030,7 +1073,7 @@ int lbm_adjoint_backward(lbm_t* h, double dJ, double* grad_uin, double* grad_tau
     if (len <= 1) return LBM_OK;
     // Recomputed step k of segment c is step c * every + k of the forward run.
     return enqueue_steps(h, ws_tables(h), s, len - 1, nullptr, h->adj_base + int64_t(c) * every,
-                         [&](int32_t k) {
+                         false, [&](int32_t k) {
       return std::pair<const void*, void*>(seg(c, k), seg(c, k + 1));
     });
   };

@@ -183,7 +183,7 @@ struct lbm_batch_t {
       }
       for (int j = 0; j < 2; ++j) e.buf[j] = h->buf(h->cur ^ j ^ bpar);
       e.part[0] = h->part(0);
-      e.part[1] = h->part(1);
+      e.part[1] = h->part(kFuse);
       e.ring = ring() + int64_t(i) * kRingRow;
       e.step_off = h->steps_done - steps_done;
       if (h->plan.has_box) {

@@ -93,6 +93,7 @@ struct lbm_t {
   size_t part_doubles() const {
     return size_t(plan.nslots) * lbm::kPart + size_t(plan.njslots) * lbm::kBoxPart;
   }
+  // Partials of step k (of 2 kFuse kept).
   double* part(int k) const {
     return reinterpret_cast<double*>(ws + off_part) + size_t(k) * part_cap;
   }
@@ -108,7 +109,10 @@ struct DevTables {
   const int32_t* strip_slot;   // per-strip force slots
   const double* uin;           // [ny] inlet profile
   const BodyMotion* motion;    // body motion (device), or null at rest
-  double* part[2];             // force partials of alternate steps
+  double* part[2];             // force partials of alternate launches (kFuse steps each
+                               // when fuse, one otherwise)
+  int64_t part_stride;         // doubles between the partials of a launch's steps
+  bool fuse;                   // there is room for the partials of fused launches
   double* jpart;               // box-sweep partials
 };
 DevTables ws_tables(const lbm_t* h);

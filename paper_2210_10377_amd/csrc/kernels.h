@@ -5,6 +5,8 @@
 
 #include <cstdint>
 
+#include "plan.h"
+
 namespace lbm {
 
 // Force partial of one strip, and the per-step sums: FAx FAy FBx FBy Jx Jy Phix Phiy
@@ -91,11 +93,28 @@ struct BoxArgs {
   double* jpart;              // [blocks][2]
 };
 
+// Arguments of a fused launch besides the step's own (src is the state kFuse steps before
+// dst; part_out and the reduction are given here).
+struct FuseArgs {
+  FuseMap map;
+  double* part_out;       // force partials of the first step, or null
+  int64_t part_stride;    // doubles between the partials of successive steps
+  uint32_t step_key[kFuse];
+  // Force rows of the launch before this one: partials and ring rows of nred steps.
+  int32_t nred;
+  const double* red_in;
+  double* red_row;        // ring row of its first step
+  int32_t red_has_prev;   // the row before that one takes its Jnext
+};
+
+// The steps of the last launch.
 struct FinalArgs {
-  const double* red_in;   // partials of the last step (StepArgs layout)
+  int32_t nrows;          // their number
+  const double* red_in;   // partials of the first (StepArgs layout)
+  int64_t part_stride;    // doubles between the partials of successive steps
   int32_t nslots, njslots;
-  double* row;            // ring row of the last step
-  double* prev_jnext;     // Jnext slot of the row before, or null
+  double* row;            // ring row of the first
+  double* prev_jnext;     // Jnext slot of the row before it, or null
   const double* jpart;    // [njblocks][2], or null when there is no box
   int32_t njblocks;
 };
@@ -158,6 +177,9 @@ struct CpArgs {
 };
 
 hipError_t launch_step(int precision, bool forces, const StepArgs& a, hipStream_t s);
+// kFuse steps in one launch (state buffers below 4 GiB).
+hipError_t launch_fused(int precision, bool forces, const StepArgs& a, const FuseArgs& q,
+                        hipStream_t s);
 // C_p = (rho/3 - p_inf) / q at every listed node, rho the sum of the node's stored
 // populations in binary64, p_inf = rho/3 of the reference node (or p_ref).
 hipError_t launch_boundary_cp(int precision, const CpArgs& a, hipStream_t s);

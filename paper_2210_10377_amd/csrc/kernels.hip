@@ -29,6 +29,7 @@
 #include <algorithm>
 
 #include "device.h"
+#include "force_terms.h"
 #include "kernels.h"
 #include "plan.h"
 
@@ -37,10 +38,6 @@ namespace lbm {
 namespace {
 
 using namespace dev;
-
-__device__ __forceinline__ bool in_box(const StepArgs& a, int x, int y) {
-  return x >= a.bx0 && x < a.bx1 && y >= a.by0 && y < a.by1;
-}
 
 __device__ __forceinline__ int lane_id() { return int(threadIdx.x) & 63; }
 
@@ -81,8 +78,8 @@ __device__ __forceinline__ void interior_finish(const StepArgs& a, int x0, int y
     if constexpr (JP) {
       if (i > 0) {
         const double fi = to_f64<P>(q, i);
-        jp[0] += kCx[i] * fi;
-        jp[1] += kCy[i] * fi;
+        add_signed(kCx[i], fi, jp[0]);
+        add_signed(kCy[i], fi, jp[1]);
       }
     }
   }
@@ -111,49 +108,6 @@ __device__ __forceinline__ void edge_strip(const StepArgs& a, int x0, int y) {
   const uint32_t word = S::kSR ? sr_node_word(a.step_key, a.nx, x, y) : 0u;
 #pragma unroll
   for (int i = 0; i < kQ; ++i) dst.st(i, o, pack_sr<P>(g[i], i, word));
-}
-
-// Control-volume terms of fluid node (x, y) (second Eq. rtt7) added to acc: the
-// momentum of its populations before collision (f) and as stored after it (s) when it
-// lies in the control volume, and the stored populations crossing the box surface:
-// entering V (+) from a node outside, leaving V (-) from a node inside.
-template <int P>
-__device__ __forceinline__ void box_terms(const StepArgs& a, int x, int y,
-                                          const typename Storage<P>::C (&f)[kQ],
-                                          const typename Storage<P>::T (&s)[kQ],
-                                          double (&acc)[kPart]) {
-  using S = Storage<P>;
-  if (in_box(a, x, y)) {
-    double jx = 0.0, jy = 0.0, px = 0.0, py = 0.0;
-#pragma unroll
-    for (int i = 1; i < kQ; ++i) {
-      const double fi = pre_f64<P>(f[i], i);
-      jx += kCx[i] * fi;
-      jy += kCy[i] * fi;
-      const double sv = to_f64<P>(s[i], i);
-      px += kCx[i] * sv;
-      py += kCy[i] * sv;
-    }
-    acc[4] += jx;
-    acc[5] += jy;
-    acc[kJpost] += px;
-    acc[kJpost + 1] += py;
-#pragma unroll
-    for (int i = 1; i < kQ; ++i)
-      if (!in_box(a, x + kCx[i], y + kCy[i])) {
-        const double sv = to_f64<P>(s[i], i);
-        acc[6] -= kCx[i] * sv;
-        acc[7] -= kCy[i] * sv;
-      }
-  } else {
-#pragma unroll
-    for (int i = 1; i < kQ; ++i)
-      if (in_box(a, x + kCx[i], y + kCy[i])) {
-        const double sv = to_f64<P>(s[i], i);
-        acc[6] += kCx[i] * sv;
-        acc[7] += kCy[i] * sv;
-      }
-  }
 }
 
 // Interior strip touching the control-volume surface: plain pulls (the loaded v),
@@ -212,71 +166,11 @@ __device__ __forceinline__ void general_strip(const StepArgs& a, int x0, int y, 
       dst.st(i, o, s[i]);
     }
     if (forces) {
-      // Momentum exchange on the links of this node (Sec. III; Eq. rtt4): the
-      // population leaving along c_i towards the body is f_i before collision (A) or
-      // f~_i after it (B); the body returns f~_i (as stored) along -c_i, less the
-      // moving-wall term of that return when the body moves.
-#pragma unroll
-      for (int i = 1; i < kQ; ++i) {
-        if (pull_code(w, kOpp[i]) != kBody) continue;
-        const double sv = to_f64<P>(s[i], i);
-        const double back =
-            (MOV && a.motion) ? sv + body_wall_term(*a.motion, a.rho_w6, kOpp[i], x, y) : sv;
-        const double fa = pre_f64<P>(f[i], i) + back;
-        acc[0] += kCx[i] * fa;
-        acc[1] += kCy[i] * fa;
-        acc[2] += kCx[i] * (sv + back);
-        acc[3] += kCy[i] * (sv + back);
-      }
+      link_terms<P, MOV>(a, w, x, y, f, s, acc);
       // Control volume (second Eq. rtt7).
       box_terms<P>(a, x, y, f, s, acc);
-      // Stress integration (Sec. III, Eq. stress_int): each axis link of this node is a
-      // unit face of the staircase surface with normal -c_i out of the body; the
-      // traction (-p I + sigma) . n uses p = rho/3 and sigma = -(1 - omega/2) Pi^neq of
-      // the pre-collision populations (Pi^neq = sum c c f - rho u u - rho I/3), in
-      // binary64.  Faces are linear in n, so the node adds the traction of their sum.
-      int nsx = 0, nsy = 0;
-#pragma unroll
-      for (int i = 1; i <= 4; ++i)
-        if (pull_code(w, kOpp[i]) == kBody) {
-          nsx -= kCx[i];
-          nsy -= kCy[i];
-        }
-      if (nsx != 0 || nsy != 0) {
-        double fd[kQ];
-#pragma unroll
-        for (int i = 0; i < kQ; ++i)
-          fd[i] = pre_f64<P>(f[i], i);
-        const double rho = ((fd[0] + fd[1]) + (fd[2] + fd[3])) + ((fd[4] + fd[5]) + (fd[6] + fd[7])) + fd[8];
-        const double ux = ((fd[1] + fd[5] + fd[8]) - (fd[3] + fd[6] + fd[7])) / rho;
-        const double uy = ((fd[2] + fd[5] + fd[6]) - (fd[4] + fd[7] + fd[8])) / rho;
-        const double diag = (fd[5] + fd[6]) + (fd[7] + fd[8]);
-        const double p = rho * (1.0 / 3.0);
-        const double visc = -(1.0 - 0.5 * a.omega);
-        const double sxx = visc * (((fd[1] + fd[3]) + diag) - rho * ux * ux - p);
-        const double syy = visc * (((fd[2] + fd[4]) + diag) - rho * uy * uy - p);
-        const double sxy = visc * (((fd[5] + fd[7]) - (fd[6] + fd[8])) - rho * ux * uy);
-        acc[8] += (sxx - p) * nsx + sxy * nsy;
-        acc[9] += sxy * nsx + (syy - p) * nsy;
-      }
+      stress_terms<P>(a, w, f, acc);
     }
-  }
-}
-
-// Force row of the previous step from its partial slots (fixed order).
-__device__ __forceinline__ void reduce_row(const double* red_in, int nslots, int njslots,
-                                           double* row, double* prev_jnext) {
-  // General strips, then the box momenta of the box-interior strips (J before and after
-  // collision, added to the two J sums).
-  double t = reduce_partials<kPart>(red_in, nslots);
-  const double tj = reduce_partials<kBoxPart>(red_in + int64_t(nslots) * kPart, njslots);
-  const int tid = int(threadIdx.x);
-  const bool pre = tid == 4 || tid == 5, post = tid == kJpost || tid == kJpost + 1;
-  const double tjs = __shfl(tj, pre ? tid - 4 : (post ? tid - kJpost + 2 : 0), 64);
-  if (pre || post) t += tjs;
-  if (threadIdx.x < kPart) {
-    row[threadIdx.x] = t;
-    if (prev_jnext && (threadIdx.x == 4 || threadIdx.x == 5)) prev_jnext[threadIdx.x - 4] = t;
   }
 }
 
@@ -315,8 +209,8 @@ __device__ __forceinline__ void step_tile(const StepArgs& a, int tile,
 #pragma unroll
       for (int i = 1; i < kQ; ++i) {
         const double fi = to_f64<P>(v[i], i);
-        acc[0] += kCx[i] * fi;
-        acc[1] += kCy[i] * fi;
+        add_signed(kCx[i], fi, acc[0]);
+        add_signed(kCy[i], fi, acc[1]);
       }
       interior_finish<P, BUF, COLL, true>(a, x0, y0, v, acc + 2);
       wave_sum_store<kBoxPart>(acc, a.part_out + int64_t(a.nslots) * kPart +
@@ -475,8 +369,13 @@ __global__ __launch_bounds__(kThreads) void batch_box_kernel(BatchLaunch b, int3
   box_block<P, true>(x, b.box_local[blockIdx.x]);
 }
 
-__device__ __forceinline__ void finalize_body(const FinalArgs& a) {
-  reduce_row(a.red_in, a.nslots, a.njslots, a.row, a.prev_jnext);
+// Block r of a finalization: row r of the last launch's a.nrows rows, the last of them with
+// the J of the pull after it.
+__device__ __forceinline__ void finalize_body(const FinalArgs& a, int r) {
+  double* row = a.row + int64_t(r) * kRingRow;
+  reduce_row(a.red_in + r * a.part_stride, a.nslots, a.njslots, row,
+             r > 0 ? row - kRingRow + kJnext : a.prev_jnext);
+  if (r + 1 < a.nrows) return;
   if (a.jpart) {
     __syncthreads();
     __shared__ double red[kThreads][2];
@@ -491,14 +390,16 @@ __device__ __forceinline__ void finalize_body(const FinalArgs& a) {
     if (threadIdx.x < 2) {
       double s = 0.0;
       for (int k = 0; k < kThreads; ++k) s += red[k][threadIdx.x];
-      a.row[kJnext + threadIdx.x] = s;
+      row[kJnext + threadIdx.x] = s;
     }
   } else if (threadIdx.x < 2) {
-    a.row[kJnext + threadIdx.x] = __builtin_nan("");
+    row[kJnext + threadIdx.x] = __builtin_nan("");
   }
 }
 
-__global__ __launch_bounds__(kThreads) void finalize_kernel(FinalArgs a) { finalize_body(a); }
+__global__ __launch_bounds__(kThreads) void finalize_kernel(FinalArgs a) {
+  finalize_body(a, int(blockIdx.x));
+}
 
 // Finalize of every instance of a batch (one block each): force row `row` from the
 // partials part[part_parity] and, without a box, NaN for its Jnext.
@@ -507,6 +408,7 @@ __global__ __launch_bounds__(kThreads) void batch_finalize_kernel(BatchLaunch b,
                                                                   int32_t has_prev) {
   const BatchInst& I = b.inst[blockIdx.x];
   FinalArgs f{};
+  f.nrows = 1;
   f.red_in = I.part[part_parity];
   f.nslots = I.a.nslots;
   f.njslots = I.a.njslots;
@@ -515,7 +417,7 @@ __global__ __launch_bounds__(kThreads) void batch_finalize_kernel(BatchLaunch b,
   f.prev_jnext = has_prev ? I.ring + (int64_t(row) - 1) * rs + kJnext : nullptr;
   f.jpart = I.njblocks > 0 ? I.box.jpart : nullptr;
   f.njblocks = I.njblocks;
-  finalize_body(f);
+  finalize_body(f, 0);
 }
 
 template <int P>
@@ -787,7 +689,7 @@ hipError_t launch_batch_tail(int precision, const BatchLaunch& b, int32_t parity
 }
 
 hipError_t launch_finalize(const FinalArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(kThreads), 0, s, a);
+  hipLaunchKernelGGL(finalize_kernel, dim3(a.nrows), dim3(kThreads), 0, s, a);
   return hipGetLastError();
 }
 

@@ -96,7 +96,12 @@ int lbm_step_static(lbm_t* h, void* buf0, void* buf1, size_t buf_bytes, int32_t 
   off = align256(off + sizeof(BodyMotion));
   const size_t off_part = off;
   const size_t part = align256(h->part_doubles() * sizeof(double));
-  off += 2 * part;
+  // The partials of two launches: of kFuse steps each where the array holds them.
+  const size_t off_rest = align256(size_t(h->njblocks) * 2 * sizeof(double)) +
+                          (want ? align256(size_t(n) * kRingRow * sizeof(double)) : 0);
+  const bool fuse = off + 2 * kFuse * part + off_rest <= kScratchBytes;
+  const size_t launch_part = (fuse ? kFuse : 1) * part;
+  off += 2 * launch_part;
   const size_t off_jpart = off;
   off = align256(off + size_t(h->njblocks) * 2 * sizeof(double));
   const size_t off_ring = off;
@@ -128,7 +133,9 @@ int lbm_step_static(lbm_t* h, void* buf0, void* buf1, size_t buf_bytes, int32_t 
   t.uin = reinterpret_cast<const double*>(s + off_uin);
   t.motion = h->motion.moving ? reinterpret_cast<const BodyMotion*>(s + off_mot) : nullptr;
   t.part[0] = reinterpret_cast<double*>(s + off_part);
-  t.part[1] = reinterpret_cast<double*>(s + off_part + part);
+  t.part[1] = reinterpret_cast<double*>(s + off_part + launch_part);
+  t.part_stride = int64_t(part / sizeof(double));
+  t.fuse = fuse;
   t.jpart = reinterpret_cast<double*>(s + off_jpart);
   double* ring = want ? reinterpret_cast<double*>(s + off_ring) : nullptr;
   const int rc = enqueue_pingpong(h, t, buf0, buf1, st, n, ring);

@@ -343,6 +343,128 @@ int replan(const lbm_grid& g, const uint8_t* mask, const std::vector<int32_t>& c
   return LBM_OK;
 }
 
+bool fuse_pays(int precision, int collision, double nodes, double body) {
+  // A fused launch lasts as long as its longest unit at least (25 us: three steps of rows of a
+  // body with all forces), which a single step of a small grid undercuts; and it moves a third
+  // of the bytes, so it gains most where those count most.  Measured, single against fused, in
+  // us a step with all forces (without): binary32 724 x 362 7.8 : 8.3 (5.3 : 5.3), 900 x 450
+  // 9.5 : 8.7 (7.2 : 5.8), 2048 x 1024 27 : 17, 8192 x 4096 397 : 177; binary64 512 x 256
+  // 6.0 : 8.5 (4.7 : 4.7), 724 x 362 10.5 : 8.7 (8.9 : 5.8), 4096 x 2048 199 : 88.  The
+  // stochastically rounded and the binary16 storage spend more arithmetic per byte:
+  // 2048 x 1024 27 : 31 and 16 : 22, 3001 x 1499 54 : 50 and 30 : 37, 5792 x 2896 197 : 153
+  // and 101 : 98.
+  // The stabilized collisions stay with single steps: regularized, binary32, 1024 x 512 without
+  // forces 8.1 : 9.5, a moving airfoil with forces 12.4 : 13.3.  A node of the body rectangle
+  // costs several times what a plain one costs.
+  if (collision != LBM_COLL_BGK) return false;
+  switch (precision) {
+    case LBM_FP64: return nodes >= 2.5e5 && body <= 0.4;
+    case LBM_FP32:
+    case LBM_FP32DEV: return nodes >= 4e5 && body <= 0.2;
+    case LBM_FP32SR: return nodes >= 4e6 && body <= 0.06;
+    default: return nodes >= 1.5e7 && body <= 0.04;
+  }
+}
+
+FuseMap fuse_map(const Plan& p, int elem_bytes) {
+  constexpr int kM = kFuseM;
+  // Rows of a unit: in the plain rectangles few enough to give every SIMD three waves, many
+  // enough to keep the margins (two rows of two steps) small; in the body rectangle as many as
+  // a launch has time for (a row of three steps with forces takes 5 - 8 us, a launch of
+  // 8192 x 4096 in binary32 500 us, of 1024 x 512 27 us).
+  const int64_t bytes = int64_t(p.nx) * p.ny * kQ * elem_bytes;
+  const int64_t lanes = bytes / (kQ * 8) / kFuseLanes;  // units of one row
+  const int rows = int(std::clamp<int64_t>(lanes / 3072, 6, 12));
+  const int body_rows = int(std::clamp<int64_t>(2 + bytes / 37000000, 2, 32));
+  const int edge_rows = std::clamp(body_rows / 2, 2, 8);
+  // The body rectangle (inclusive here): the general nodes with kM nodes of margin, so that
+  // the other windows meet edge codes only, and the nodes with control-volume terms.
+  int x0 = p.nx, x1 = -1, y0 = p.ny, y1 = -1;
+  if (p.gx0 <= p.gx1) {
+    x0 = p.gx0 - kM;
+    x1 = p.gx1 + kM;
+    y0 = p.gy0 - kM;
+    y1 = p.gy1 + kM;
+    // A margin across a periodic edge takes the whole axis.
+    if (p.bc_x == LBM_BCX_PERIODIC && (x0 < 0 || x1 >= p.nx)) {
+      x0 = 0;
+      x1 = p.nx - 1;
+    }
+    if (p.bc_y == LBM_BCY_PERIODIC && (y0 < 0 || y1 >= p.ny)) {
+      y0 = 0;
+      y1 = p.ny - 1;
+    }
+  }
+  if (p.has_box) {
+    x0 = std::min(x0, p.box[0] - 1);
+    x1 = std::max(x1, p.box[1]);
+    y0 = std::min(y0, p.box[2] - 1);
+    y1 = std::max(y1, p.box[3]);
+  }
+  FuseMap m{};
+  auto add = [&](int kind, int ax0, int ax1, int ay0, int ay1) {
+    if (ax0 >= ax1 || ay0 >= ay1) return;
+    FuseRect& r = m.r[m.nrects++];
+    r.x0 = ax0;
+    r.x1 = ax1;
+    r.y0 = ay0;
+    r.y1 = ay1;
+    r.kind = int16_t(kind);
+    r.first = m.nblocks;
+    const int per = kind == kFuseBody ? kStripW
+                                      : (kind == kFuseEdge ? kFuseEdgeW : kFuseLanes * 8 / elem_bytes);
+    r.rows = int16_t(kind == kFuseBody ? body_rows : (kind == kFuseEdge ? edge_rows : rows));
+    r.nw = (ax1 - ax0 + per - 1) / per;
+    const int64_t units = int64_t(r.nw) * ((ay1 - ay0 + r.rows - 1) / r.rows);
+    const int in_block = kind == kFuseBody ? kStrips / 2 : kStrips;
+    m.nblocks += int32_t((units + in_block - 1) / in_block);
+  };
+  // The rectangles around the body: the rows before and after it, the columns beside it.
+  struct Box {
+    int x0, x1, y0, y1;
+  };
+  Box around[4];
+  int n = 0;
+  if (x0 <= x1) {
+    x0 = std::max(x0, 0) / kStripW * kStripW;
+    x1 = std::min((x1 / kStripW + 1) * kStripW, p.nx);
+    y0 = std::max(y0, 0);
+    y1 = std::min(y1 + 1, p.ny);
+    add(kFuseBody, x0, x1, y0, y1);
+    around[n++] = {0, p.nx, 0, y0};
+    around[n++] = {0, x0, y0, y1};
+    around[n++] = {x1, p.nx, y0, y1};
+    around[n++] = {0, p.nx, y1, p.ny};
+  } else {
+    around[n++] = {0, p.nx, 0, p.ny};
+  }
+  // The nodes whose windows (margins included) stream plainly: kM + 1 nodes from the edges,
+  // along x in whole 64-byte sectors (a window's first lanes are half a sector left of its
+  // first column).
+  const int sector = 64 / elem_bytes;
+  const Box in = {sector, (p.nx - kM - 1) / sector * sector, kM + 1, p.ny - kM - 1};
+  // Edge units take longest, so they start first.
+  for (int pass = 0; pass < 2; ++pass)
+    for (int k = 0; k < n; ++k) {
+      const Box& b = around[k];
+      if (b.x0 >= b.x1 || b.y0 >= b.y1) continue;
+      const Box c = {std::max(b.x0, in.x0), std::min(b.x1, in.x1), std::max(b.y0, in.y0),
+                     std::min(b.y1, in.y1)};
+      const bool none = c.x0 >= c.x1 || c.y0 >= c.y1;
+      if (pass == 1) {
+        if (!none) add(kFusePlain, c.x0, c.x1, c.y0, c.y1);
+      } else if (none) {
+        add(kFuseEdge, b.x0, b.x1, b.y0, b.y1);
+      } else {
+        add(kFuseEdge, b.x0, b.x1, b.y0, c.y0);
+        add(kFuseEdge, b.x0, b.x1, c.y1, b.y1);
+        add(kFuseEdge, b.x0, c.x0, c.y0, c.y1);
+        add(kFuseEdge, c.x1, b.x1, c.y0, c.y1);
+      }
+    }
+  return m;
+}
+
 void tile_slots(const Plan& p, int rows, int& ntx, int& nty, std::vector<int32_t>& out) {
   const int tile_w = kTileW / rows;
   ntx = (p.nx + tile_w - 1) / tile_w;

@@ -142,6 +142,31 @@ constexpr int strip_class(int nx, int ny, int gx0, int gx1, int gy0, int gy1, in
   return strip_is_interior(nx, ny, x0, y0) ? kStripBoxRing : kStripGeneral;
 }
 
+// Work map of the fused kernel, which advances a lattice by kFuse steps in one launch: the
+// grid cut into rectangles of one kind of work each, and these into units, one a wave.
+//   kFuseBody: every node with a force term, and the nodes with body codes (with kFuseM nodes of
+//     margin); columns in whole strips, two waves a strip and two strips a block;
+//   kFuseEdge: nodes whose windows reach the edges of the grid;
+//   kFusePlain: the rest, whose windows stream plainly, margins included: windows of
+//     kFuseLanes lanes of 8 bytes each, whole 64-byte sectors of every row.
+constexpr int kFuse = 3;
+constexpr int kFuseM = kFuse - 1;
+constexpr int kFuseLanes = 56;
+constexpr int kFuseEdgeW = 64 - 2 * kFuseM;
+constexpr int kHalf = kStripW / 2;
+enum FuseKind { kFuseBody = 0, kFuseEdge = 1, kFusePlain = 2 };
+struct FuseRect {
+  int32_t x0, x1, y0, y1;  // half-open
+  int16_t kind, rows;      // FuseKind; rows of a unit
+  int32_t nw;              // windows (body: strips) along x
+  int32_t first;           // its first block
+};
+constexpr int kFuseRects = 24;
+struct FuseMap {
+  int32_t nrects, nblocks;
+  FuseRect r[kFuseRects];
+};
+
 struct Plan {
   int nx = 0, ny = 0, bc_x = 0, bc_y = 0;
   bool has_box = false;
@@ -175,6 +200,13 @@ int build_plan(const lbm_grid& g, const uint8_t* mask, Plan& p, std::string& err
 // strips, with the tile counts along x and y: the same slots as p.strip_slot in another
 // tile order.
 void tile_slots(const Plan& p, int rows, int& ntx, int& nty, std::vector<int32_t>& out);
+
+// The fused kernel's work map of p for elements of elem_bytes.
+FuseMap fuse_map(const Plan& p, int elem_bytes);
+
+// Whether fused launches are faster than single steps for `nodes` nodes, the share `body` of
+// them in the body rectangle.
+bool fuse_pays(int precision, int collision, double nodes, double body);
 
 // Node words a mask change rewrites (index, old word, new word), in index order.
 struct PlanDelta {

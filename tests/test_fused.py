@@ -1,0 +1,188 @@
+"""Three steps per launch (the fused kernel): its cut of the grid on the CPU, and on the GPU
+bitwise equality with single steps.
+
+lbm_step takes the fused kernel on grids large enough to gain from it, for runs of three steps or
+more; calls of one or two steps always take the single-step kernel, so a run in such calls is
+the reference.  States are bitwise alike whatever the calls, and so are the momentum-exchange and
+stress forces; the control-volume forces of a call's last step read a separately ordered sum
+of the box momentum, so they agree to binary64 rounding of that sum."""
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+import workloads
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2210_10377_amd", "csrc")
+
+DRIVER = r"""
+#include <cstdio>
+#include <random>
+#include <vector>
+#include "plan.h"
+using namespace lbm;
+#define CHECK(c) do { if (!(c)) { std::printf("line %d: %s (%dx%d bc %d%d esz %d)\n", __LINE__, #c, g.nx, g.ny, g.bc_x, g.bc_y, esz); return 1; } } while (0)
+int main() {
+  std::mt19937 rng(7);
+  auto pick = [&](int lo, int hi) { return lo + int(rng() % unsigned(hi - lo + 1)); };
+  for (int it = 0; it < 600; ++it) {
+    lbm_grid g{};
+    const int big[] = {3, 4, 17, 63, 64, 65, 127, 128, 129, 200, 333, 700};
+    g.nx = it % 3 ? big[pick(0, 11)] : pick(3, 500);
+    g.ny = it % 5 ? pick(3, 90) : big[pick(0, 8)];
+    g.bc_x = pick(0, 1);
+    g.bc_y = pick(0, 1);
+    g.precision = LBM_FP32;
+    g.tile = pick(0, 2);
+    for (int k = 0; k < 4; ++k) g.box[k] = -1;
+    std::vector<uint8_t> mask(size_t(g.nx) * g.ny, 0);
+    const int kind = pick(0, 3);
+    if (kind >= 1) {
+      const int n = kind == 3 ? g.nx * g.ny / 10 : 1 + pick(0, 3);
+      for (int k = 0; k < n; ++k) mask[size_t(pick(0, g.ny - 1)) * g.nx + pick(0, g.nx - 1)] = 1;
+    }
+    if (kind == 2 && g.nx > 12 && g.ny > 12) {
+      std::fill(mask.begin(), mask.end(), 0);
+      const int x = pick(3, g.nx - 5), y = pick(3, g.ny - 5);
+      mask[size_t(y) * g.nx + x] = 1;
+      g.box[0] = x - 2; g.box[1] = x + 3; g.box[2] = y - 2; g.box[3] = y + 3;
+    }
+    Plan p;
+    std::string err;
+    int esz = 8;
+    if (build_plan(g, mask.data(), p, err) != LBM_OK) continue;
+    for (int e = 0; e < 3; ++e) {
+      esz = e == 0 ? 8 : (e == 1 ? 4 : 2);
+      const FuseMap m = fuse_map(p, esz);
+      CHECK(m.nrects <= kFuseRects && m.nrects >= 1);
+      std::vector<int> owner(mask.size(), 0), kindof(mask.size(), -1);
+      int blocks = 0;
+      for (int k = 0; k < m.nrects; ++k) {
+        const FuseRect& r = m.r[k];
+        CHECK(r.x0 >= 0 && r.x0 < r.x1 && r.x1 <= g.nx && r.y0 >= 0 && r.y0 < r.y1 && r.y1 <= g.ny);
+        CHECK(r.first == blocks && r.rows >= 1);
+        const int per = r.kind == kFuseBody ? kStripW : (r.kind == kFuseEdge ? kFuseEdgeW : kFuseLanes * 8 / esz);
+        CHECK(r.nw == (r.x1 - r.x0 + per - 1) / per);
+        const int units = r.nw * ((r.y1 - r.y0 + r.rows - 1) / r.rows);
+        const int in = r.kind == kFuseBody ? kStrips / 2 : kStrips;
+        blocks += (units + in - 1) / in;
+        if (r.kind == kFuseBody) CHECK(k == 0 && r.x0 % kStripW == 0 && (r.x1 % kStripW == 0 || r.x1 == g.nx));
+        if (r.kind == kFusePlain) CHECK(r.x0 * esz % 64 == 0);
+        for (int y = r.y0; y < r.y1; ++y)
+          for (int x = r.x0; x < r.x1; ++x) {
+            ++owner[size_t(y) * g.nx + x];
+            kindof[size_t(y) * g.nx + x] = r.kind;
+          }
+      }
+      CHECK(blocks == m.nblocks);
+      const int nsx = (g.nx + kStripW - 1) / kStripW;
+      for (int y = 0; y < g.ny; ++y)
+        for (int x = 0; x < g.nx; ++x) {
+          const size_t at = size_t(y) * g.nx + x;
+          CHECK(owner[at] == 1);                                // every node once
+          if (p.row_slot[size_t(y) * nsx + x / kStripW] >= 0 && kindof[at] != kFuseBody) {
+            // A strip with a slot lies in the body rectangle as a whole.
+            CHECK(false);
+          }
+          // Within the margin of a node outside the body rectangle every code is the edge's;
+          // around a plain node all stream.
+          if (kindof[at] == kFuseBody) continue;
+          const int mar = kFuseM;
+          for (int dy = -mar; dy <= mar; ++dy)
+            for (int dx = -mar; dx <= mar; ++dx) {
+              int ax = x + dx, ay = y + dy;
+              if (g.bc_x == LBM_BCX_PERIODIC) ax = ((ax % g.nx) + g.nx) % g.nx;
+              if (g.bc_y == LBM_BCY_PERIODIC) ay = ((ay % g.ny) + g.ny) % g.ny;
+              const bool out = ax < 0 || ax >= g.nx || ay < 0 || ay >= g.ny;
+              if (kindof[at] == kFusePlain) CHECK(!out && p.node[size_t(ay) * g.nx + ax] == 0u);
+              if (!out) CHECK(p.node[size_t(ay) * g.nx + ax] == edge_word(g.nx, g.ny, g.bc_x, g.bc_y, ax, ay));
+            }
+        }
+    }
+  }
+  std::printf("ok\n");
+  return 0;
+}
+"""
+
+
+def test_work_map_owns_every_node_once_and_keeps_its_margins(tmp_path):
+    """Random grids, masks, boundary codes and storages: every node in one rectangle, every
+    strip with forces in the body rectangle, edge codes only within the margins of the other
+    nodes, plain streaming only around the plain ones."""
+    src = tmp_path / "driver.cpp"
+    src.write_text(DRIVER)
+    exe = tmp_path / "driver"
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-fsanitize=address,undefined",
+                           "-I", CSRC, "-I", os.path.join(ROOT, "include"), str(src),
+                           os.path.join(CSRC, "plan.cpp"), "-o", str(exe)])
+    out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=300)
+    assert out.returncode == 0 and out.stdout.strip() == "ok", out.stdout + out.stderr
+
+
+def _case(name):
+    z = lambda nx, ny: np.zeros((ny, nx), np.uint8)  # noqa: E731
+    if name == "airfoil":            # 725 x 701, the box inside the grid
+        w = workloads.naca_channel(725, 701, 181, 4.0, 500.0, 1)
+        return w.mask, w.box
+    if name == "two_bodies":         # at the outlet, at a wall and across the wrap; no box
+        m = z(803, 640)
+        m[300:320, 802] = 1
+        m[0:3, 90:100] = 1
+        m[400:405, 0:2] = 1
+        return m, None
+    if name == "thin_rows":          # three rows that are all edges
+        return z(170003, 3), None
+    if name == "narrow":             # narrower than a wave
+        m = z(37, 14000)
+        m[5000:5010, 12:20] = 1
+        return m, workloads.default_box(m, 4)
+    if name in ("cylinder_4m", "cylinder_15m"):  # large enough for the other storages
+        nx, ny = (2803, 1499) if name == "cylinder_4m" else (6007, 2501)
+        m = workloads.cylinder_mask(nx, ny, 900.0, 749.5, 60.5)
+        return m, workloads.default_box(m, 20)
+    raise KeyError(name)
+
+
+CASES = [("airfoil", p, bx, by, c, s) for p in ("fp64", "fp32", "fp32dev")
+         for bx, by, c, s in ((0, 0, "bgk", 0.0), (1, 1, "bgk", 1e-3))]
+CASES += [("two_bodies", p, bx, by, "bgk", 0.0) for p in ("fp64", "fp32")
+          for bx, by in ((0, 0), (1, 0), (0, 1), (1, 1))]
+CASES += [("thin_rows", "fp32", bx, by, "bgk", 0.0) for bx, by in ((0, 0), (1, 1))]
+CASES += [("narrow", p, 0, 0, "bgk", 0.0) for p in ("fp64", "fp32dev")]
+CASES += [("cylinder_4m", "fp32sr", 0, 1, "bgk", 0.0), ("cylinder_15m", "fp16dev", 0, 1, "bgk", 0.0)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name,precision,bc_x,bc_y,collision,spin", CASES)
+def test_fused_launches_bitwise_equal_single_steps(name, precision, bc_x, bc_y, collision, spin):
+    from paper_2210_10377_amd import Sim
+    mask, box = _case(name)
+    ny, nx = mask.shape
+    rng = np.random.default_rng(5)
+    uin = 0.05 * (1 + 0.1 * rng.uniform(-1, 1, ny))
+    lines = 1 + 0.02 * rng.uniform(-1, 1, (9, ny, 1)) * rng.uniform(-1, 1, (9, 1, nx))
+    S = workloads.NEAR_REST_BASE[:, None, None] * lines
+    n = 7  # a single step and two fused launches
+    runs = []
+    for calls in ([n], [2, 2, 2, 1]):
+        print(f"fused {name} {precision} bc {bc_x}{bc_y} {collision} calls {calls}", flush=True)
+        sim = Sim(mask, 0.7, uin, precision=precision, bc_x=bc_x, bc_y=bc_y, box=box,
+                  max_record=n, collision=collision)
+        sim.set_populations(S)
+        if spin:
+            sim.set_body_motion(ux=0.01, omega=spin / 100, xc=nx / 3, yc=ny / 2)
+        for k in calls:
+            sim.step(k)
+        runs.append((sim.populations(), sim.forces()))
+        del sim
+    (P0, F0), (P1, F1) = runs
+    assert np.array_equal(P0, P1)
+    assert np.array_equal(F0[:, [0, 1, 3]], F1[:, [0, 1, 3]])
+    if box is not None:
+        # The box momentum J sums up to N values of at most 0.45 a population: its rounding is
+        # below N 2^-53 0.45 in any order, and a row holds two of them.
+        N = (box[1] - box[0]) * (box[3] - box[2]) * 9
+        assert np.abs(F0 - F1).max() <= 4 * N * 0.45 * 2.0 ** -53
