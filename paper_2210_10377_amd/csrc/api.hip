@@ -337,7 +337,7 @@ namespace {
 FuseMap fuse_for(const lbm_t* h, const DevTables& t, int32_t n) {
   const FuseMap none{};
   if (n < kFuse || !t.fuse || h->buf_bytes32() == 0) return none;
-  const FuseMap m = fuse_map(h->plan, int(h->esz));
+  const FuseMap m = fuse_map(h->plan, int(h->esz), int64_t(h->g.nx) * h->g.ny);
   const FuseRect& r = m.r[0];
   const double nodes = double(h->g.nx) * h->g.ny;
   const double body =
@@ -357,7 +357,7 @@ int enqueue_steps(lbm_t* h, const DevTables& t, hipStream_t stream, int32_t n, d
   StepArgs a = step_args(h, t);
   FuseArgs q{};
   q.map = alternate ? fuse_for(h, t, n) : FuseMap{};
-  q.part_stride = t.part_stride;
+  q.step.part_stride = t.part_stride;
   const void* last = nullptr;
   // Single steps first, then the fused launches: a launch reduces the rows of the one before
   // it (steps [k - in_last, k), partials in part[1 - turn]).
@@ -383,8 +383,8 @@ int enqueue_steps(lbm_t* h, const DevTables& t, hipStream_t stream, int32_t n, d
       in_last = 1;
     } else {
       a.dst = io(k + kFuse - 1).second;
-      for (int j = 0; j < kFuse; ++j) q.step_key[j] = sr_step_key(step0 + k + j);
-      q.part_out = forces ? t.part[turn] : nullptr;
+      for (int j = 0; j < kFuse; ++j) q.step.step_key[j] = sr_step_key(step0 + k + j);
+      q.step.part_out = forces ? t.part[turn] : nullptr;
       q.nred = forces ? in_last : 0;
       if (q.nred) {
         q.red_in = t.part[1 - turn];
@@ -407,6 +407,7 @@ int enqueue_steps(lbm_t* h, const DevTables& t, hipStream_t stream, int32_t n, d
     f.nrows = in_last;
     f.red_in = t.part[1 - turn];
     f.part_stride = t.part_stride;
+    f.row_stride = kRow;
     f.nslots = p.nslots;
     f.njslots = p.njslots;
     f.row = ring + int64_t(n - in_last) * kRow;

@@ -47,9 +47,17 @@ struct lbm_batch_t {
   int64_t total_tiles = 0, total_box = 0, total_fluid = 0, total_nodes = 0;
   int64_t max_tiles = 0;  // tile-list capacity: the most tiles of the three tile shapes
   std::vector<int32_t> tile_inst, tile_local, box_inst, box_local;
+  // Fused launches: the members' work maps, the blocks of all of them (the longest kinds
+  // first), and the plan generations they were built from.  Blocks are reserved at create
+  // (item_cap) so that a new mask of a member fits; without room single steps are taken.
+  std::vector<FuseMap> fmap;
+  std::vector<int32_t> item_inst, item_local;
+  std::vector<uint64_t> fuse_gen;
+  int64_t item_cap = 0;
+  bool fuse = false;
   std::vector<int> nj0;  // box-sweep blocks of each member at create (the lists' sizes)
   std::vector<BatchInst> desc;  // the instance table as last uploaded
-  size_t off_desc = 0, off_ti = 0, off_tl = 0, off_bi = 0, off_bl = 0, off_ctl = 0,
+  size_t off_desc = 0, off_fmap = 0, off_fi = 0, off_fl = 0, off_ti = 0, off_tl = 0, off_bi = 0, off_bl = 0, off_ctl = 0,
          off_ring = 0, off_alt = 0, total = 0;
   // Strip-slot tables of the members that run in the batch in a tile shape other than
   // their own (schedule tile_shape): element offset in the region at off_alt (or -1),
@@ -165,6 +173,51 @@ struct lbm_batch_t {
     }
   }
 
+  // Work maps and block list of fused launches from the members' present plans; `fuse`: they
+  // are the faster form.
+  void build_fuse() {
+    fmap.clear();
+    item_inst.clear();
+    item_local.clear();
+    fuse_gen.clear();
+    double body = 0.0;
+    for (const lbm_t* h : m) {
+      fuse_gen.push_back(h->plan_gen);
+      fmap.push_back(fuse_map(h->plan, int(h->esz), total_nodes));
+      const FuseRect& r = fmap.back().r[0];
+      if (r.kind == kFuseBody) body += double(r.x1 - r.x0) * (r.y1 - r.y0);
+    }
+    for (int kind = kFuseBody; kind <= kFusePlain; ++kind)
+      for (size_t i = 0; i < m.size(); ++i) {
+        const FuseMap& f = fmap[i];
+        for (int k = 0; k < f.nrects; ++k) {
+          if (f.r[k].kind != kind) continue;
+          const int end = k + 1 < f.nrects ? f.r[k + 1].first : f.nblocks;
+          for (int b = f.r[k].first; b < end; ++b) {
+            item_inst.push_back(int32_t(i));
+            item_local.push_back(b);
+          }
+        }
+      }
+    fuse = fuse_pays(precision, m[0]->g.collision, double(total_nodes),
+                     body / double(total_nodes)) &&
+           (item_cap == 0 || int64_t(item_inst.size()) <= item_cap);
+  }
+  bool fuse_current() const {
+    for (size_t i = 0; i < m.size(); ++i)
+      if (fuse_gen[i] != m[i]->plan_gen) return false;
+    return true;
+  }
+  int upload_fuse() {
+    if (!fuse) return LBM_OK;
+    int rc = upload(fmap.data(), off_fmap, fmap.size() * sizeof(FuseMap), "upload work maps");
+    if (rc == LBM_OK) rc = upload(item_inst.data(), off_fi, item_inst.size() * 4, "upload work list");
+    if (rc == LBM_OK) rc = upload(item_local.data(), off_fl, item_local.size() * 4, "upload work list");
+    if (rc != LBM_OK) return rc;
+    const hipError_t e = hipStreamSynchronize(stream);
+    return e == hipSuccess ? LBM_OK : hip_fail(e, "upload synchronize");
+  }
+
   // Instance table for the members' present state, with buf[bpar] the current buffer.
   std::vector<BatchInst> make_desc() const {
     std::vector<BatchInst> d(m.size());
@@ -184,6 +237,7 @@ struct lbm_batch_t {
       for (int j = 0; j < 2; ++j) e.buf[j] = h->buf(h->cur ^ j ^ bpar);
       e.part[0] = h->part(0);
       e.part[1] = h->part(kFuse);
+      e.part_stride = int64_t(h->part_cap);
       e.ring = ring() + int64_t(i) * kRingRow;
       e.step_off = h->steps_done - steps_done;
       if (h->plan.has_box) {
@@ -274,6 +328,11 @@ struct lbm_batch_t {
       const int rc = upload(alt_host.data(), off_alt, alt_host.size() * 4, "upload strip slots");
       if (rc != LBM_OK) return rc;
     }
+    if (!fuse_current()) {
+      build_fuse();
+      const int rc = upload_fuse();
+      if (rc != LBM_OK) return rc;
+    }
     std::vector<BatchInst> d = make_desc();
     if (d.size() == desc.size() &&
         std::memcmp(d.data(), desc.data(), d.size() * sizeof(BatchInst)) == 0)
@@ -328,9 +387,12 @@ struct lbm_batch_t {
       const hipError_t e = launch_batch_queue_reset(L.queue, stream);
       if (e != hipSuccess) return hip_fail(e, "reset tile queue");
     }
+    // Single steps by the schedule (all of them, or what is left over kFuse), then the fused
+    // launches, which have an order of their own.
+    const int32_t singles = fuse && n >= kFuse ? n % kFuse : n;
     int32_t done = 0;
-    while (done < n) {
-      const int len = G > 0 ? std::min<int32_t>(G, n - done) : n - done;
+    while (done < singles) {
+      const int len = G > 0 ? std::min<int32_t>(G, singles - done) : singles - done;
       hipError_t e;
       if (forces || precision == LBM_FP32SR) {
         e = launch_batch_ctl(reinterpret_cast<int32_t*>(ws + off_ctl), int32_t(row0 + done), done,
@@ -352,9 +414,37 @@ struct lbm_batch_t {
       bpar = (bpar + len) & 1;
       done += len;
     }
+    // Steps of the last launch and the partials it wrote (a single step k wrote part[k & 1]).
+    int in_last = 1, turn = (n - 1) & 1;
+    if (done < n) {
+      BatchFuse f{};
+      f.inst = L.inst;
+      f.map = reinterpret_cast<const FuseMap*>(ws + off_fmap);
+      f.item_inst = reinterpret_cast<const int32_t*>(ws + off_fi);
+      f.item_local = reinterpret_cast<const int32_t*>(ws + off_fl);
+      f.n_inst = L.n_inst;
+      f.nitems = int32_t(item_inst.size());
+      f.moving = L.moving;
+      in_last = done > 0 ? 1 : 0;
+      turn = (done - 1) & 1;
+      for (; done < n; done += kFuse) {
+        f.parity = bpar;
+        f.turn = turn ^ 1;
+        f.step0 = steps_done + done;
+        f.nred = forces ? in_last : 0;
+        f.nred_blocks = (f.nred * f.n_inst + 7) / 8 * 8;
+        f.red_row = int32_t(row0 + done - in_last);
+        f.red_has_prev = done - in_last >= 1;
+        const hipError_t e = launch_batch_fused(precision, forces, f, stream);
+        if (e != hipSuccess) return hip_fail(e, "launch batch steps");
+        turn ^= 1;
+        in_last = kFuse;
+        bpar ^= 1;
+      }
+    }
     if (forces) {
-      const hipError_t e = launch_batch_tail(precision, L, bpar, int32_t(row0 + n - 1),
-                                             (n - 1) & 1, n >= 2, stream);
+      const hipError_t e = launch_batch_tail(precision, L, bpar, int32_t(row0 + n - in_last), in_last,
+                                             turn, n > in_last, stream);
       if (e != hipSuccess) return hip_fail(e, "launch batch tail");
     }
     for (lbm_t* h : m) {
@@ -428,9 +518,17 @@ int lbm_batch_create(lbm_t* const* members, int32_t n, int32_t max_record, lbm_b
   }
   b->build_alt();
   b->build_lists();
+  b->build_fuse();
+  b->item_cap = b->fuse ? 2 * int64_t(b->item_inst.size()) + 256 : 1;
   size_t off = 0;
   b->off_desc = off;
   off = align256(off + size_t(n) * sizeof(BatchInst));
+  b->off_fmap = off;
+  off = align256(off + size_t(n) * sizeof(FuseMap));
+  b->off_fi = off;
+  off = align256(off + size_t(b->item_cap) * 4);
+  b->off_fl = off;
+  off = align256(off + size_t(b->item_cap) * 4);
   b->off_ti = off;
   off = align256(off + size_t(b->max_tiles) * 4);
   b->off_tl = off;
@@ -477,7 +575,9 @@ int lbm_batch_bind(lbm_batch_t* b, void* device_workspace, size_t bytes, void* h
   b->desc.clear();
   b->nrec = 0;
   b->rec_scheme.clear();
+  b->build_fuse();
   int rc = b->upload_lists();
+  if (rc == LBM_OK) rc = b->upload_fuse();
   if (rc == LBM_OK) rc = b->refresh();
   if (rc != LBM_OK) return rc;
   b->bound = true;

@@ -196,7 +196,7 @@ struct LaneRows {
 // holds 8 bytes of columns, X being the first of lane 4; lanes 4 .. 59 own theirs.  The loads
 // of a row are issued one row ahead.
 template <int P, int COLL>
-__device__ __forceinline__ void march_plain(const StepArgs& a, const FuseArgs& q, int X, int xe,
+__device__ __forceinline__ void march_plain(const StepArgs& a, const FuseStep& q, int X, int xe,
                                             int ya, int h) {
   using S = Storage<P>;
   using T = typename S::T;
@@ -348,9 +348,12 @@ __device__ __forceinline__ void strip_sum_store(const double* mine, const double
 // BODY: half a strip of the body rectangle (codes and force slots from the plan).  Every
 // wave of a BODY block runs the same number of rows and meets at the same barriers.  What a
 // row needs besides its populations is read two rows ahead, its populations one row ahead.
+// Lane columns are xv, `owned` those that the window stores; its columns with margins are
+// [X - kM, X + own + kM) where own > 0 (a window of both sides of the grid has own = 0: it has
+// no row that streams plainly).
 template <int P, bool FORCES, int COLL, bool MOV, bool BODY>
-__device__ __forceinline__ void march_coded(const StepArgs& a, const FuseArgs& q, int X, int own,
-                                            int ya, int yb, int rows, int split,
+__device__ __forceinline__ void march_coded(const StepArgs& a, const FuseStep& q, int X, int own,
+                                            int xv, bool owned, int ya, int yb, int rows,
                                             const Pair (&pairs)[kStrips / 2], int pair, int half,
                                             Exchange& ex) {
   using S = Storage<P>;
@@ -359,8 +362,7 @@ __device__ __forceinline__ void march_coded(const StepArgs& a, const FuseArgs& q
   constexpr bool kForces = FORCES && BODY;
   const int lane = int(threadIdx.x) & 63;
   const bool periodic_x = a.bc_x == LBM_BCX_PERIODIC, periodic_y = a.bc_y == LBM_BCY_PERIODIC;
-  const int xv = lane < split ? X + lane : X + lane - 64;
-  // Column of the lane: wrapped, or clamped past a bounded edge (such a lane is never read).
+  // Column of the lane (xv): wrapped, or clamped past a bounded edge (such a lane is never read).
   int x = periodic_x ? xv % a.nx : min(max(xv, 0), a.nx - 1);
   if (x < 0) x += a.nx;
   const bool at_inlet = !periodic_x && X - kM <= 0;
@@ -371,11 +373,12 @@ __device__ __forceinline__ void march_coded(const StepArgs& a, const FuseArgs& q
   auto wrapped = [&](int yy) { return yy < 0 ? yy + a.ny : (yy >= a.ny ? yy - a.ny : yy); };
   // Rows that this window needs (its own and the margin's).
   auto needed = [&](int yy) {
-    return yy >= ya - kM && yy < yb + kM && (periodic_y || (yy >= 0 && yy < a.ny));
+    return yy >= ya - kM && yy < yb + kM && (periodic_y || (yy >= 0 && yy < a.ny)) &&
+           !(BODY && own <= 0);
   };
   // Does every pull of row y that this window needs stream plainly?
   auto plain_row = [&](int y) {
-    return y > 0 && y + 1 < a.ny && X - kM > 0 && X + own + kM < a.nx &&
+    return own > 0 && y > 0 && y + 1 < a.ny && X - kM > 0 && X + own + kM < a.nx &&
            !(BODY && y >= a.gy0 && y <= a.gy1 && X - kM <= a.gx1 && X + own + kM - 1 >= a.gx0);
   };
   struct Row {
@@ -434,7 +437,7 @@ __device__ __forceinline__ void march_coded(const StepArgs& a, const FuseArgs& q
         for (int i = 0; i < kQ; ++i) f[i] = unpack<P>(v[i], i);
       }
       collide_pack<P, COLL>(a, f, q.step_key[j], x, y, s);
-      mine = lane < own && yy >= ya && yy < yb && !(r.w & kSolidBit);
+      mine = owned && yy >= ya && yy < yb && !(r.w & kSolidBit);
       if (j == kM && mine) {
         const int32_t o = y * a.pitch + x;
 #pragma unroll
@@ -546,6 +549,54 @@ __device__ __forceinline__ void march_coded(const StepArgs& a, const FuseArgs& q
 // and 35 measured alike to 2 %).
 constexpr int kFuseGroup = 4;
 
+// Block b of a lattice's work map.
+template <int P, bool FORCES, int COLL, bool MOV>
+__device__ __forceinline__ void fused_block(const StepArgs& a, const FuseMap& m, const FuseStep& q,
+                                            int b, Exchange& ex) {
+  const int lane = int(threadIdx.x) & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+  int k = m.nrects - 1;
+  while (k > 0 && b < m.r[k].first) --k;
+  const FuseRect r = m.r[k];
+  Pair pairs[kStrips / 2] = {};
+  if (r.kind == kFuseBody) {
+    const int pair = wave >> 1, half = wave & 1;
+#pragma unroll
+    for (int p = 0; p < kStrips / 2; ++p) {
+      const int unit = (b - r.first) * (kStrips / 2) + p, chunk = unit / r.nw;
+      const int ya = min(r.y0 + chunk * r.rows, r.y1);
+      pairs[p] = {r.x0 / kStripW * kStripW + (unit - chunk * r.nw) * kStripW, ya,
+                  min(ya + r.rows, r.y1)};
+    }
+    const Pair me = pair == 0 ? pairs[0] : pairs[1];
+    const int X = me.x0 + half * kHalf;
+    const int own = X >= r.x0 ? min(max(r.x1 - X, 0), kHalf) : 0;
+    march_coded<P, FORCES, COLL, MOV, true>(a, q, X, own,
+                                            X + lane - (lane < 64 - kHalf / 2 ? 0 : 64), lane < own,
+                                            me.ya, me.yb, r.rows, pairs, pair, half, ex);
+    return;
+  }
+  const int unit = (b - r.first) * kStrips + wave, chunk = unit / r.nw;
+  const int ya = r.y0 + chunk * r.rows, yb = min(ya + r.rows, r.y1);
+  if (ya >= yb) return;
+  const int w = unit - chunk * r.nw;
+  if (r.kind == kFusePlain) {
+    march_plain<P, COLL>(a, q, r.x0 + w * (kFuseLanes * Kept<P>::kN), r.x1, ya, yb - ya);
+  } else {
+    // One call serves both kinds (it is long).
+    const bool sides = r.kind == kFuseSides;
+    const int X = sides ? 0 : r.x0 + w * kFuseEdgeW;
+    const int own = sides ? 0 : min(kFuseEdgeW, r.x1 - X);
+    const int edge = X + lane - (lane < 64 - kM ? 0 : 64);
+    const int side = lane < kSideRight || lane >= 64 - kM ? edge : r.x1 - kM + lane - kSideRight;
+    const bool side_owned =
+        lane < r.x0 || (lane >= kSideRight + kM && lane < 64 - kM && side < a.nx);
+    march_coded<P, false, COLL, false, false>(a, q, X, own, sides ? side : edge,
+                                              sides ? side_owned : lane < own, ya, yb, yb - ya,
+                                              pairs, 0, 0, ex);
+  }
+}
+
 // Registers for three waves a SIMD with 4-byte storage (the stochastic rounding takes 191
 // otherwise: 4096 x 4096 160 against 147 us a step), two with the others.
 template <int P, bool FORCES, int COLL, bool MOV>
@@ -558,44 +609,46 @@ void fused_kernel(StepArgs a, FuseArgs q) {
     // The first eight blocks (one per XCD) reduce the force rows of the launch before this one.
     if (b < 8) {
       if (b < q.nred)
-        reduce_row(q.red_in + b * q.part_stride, a.nslots, a.njslots, q.red_row + b * kRingRow,
+        reduce_row(q.red_in + b * q.step.part_stride, a.nslots, a.njslots, q.red_row + b * kRingRow,
                    b > 0 || q.red_has_prev ? q.red_row + (b - 1) * kRingRow + kJnext : nullptr);
       return;
     }
     b -= 8;
   }
-  const FuseMap& m = q.map;
-  b = block_tile<kFuseGroup>(b, m.nblocks);
-  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
-  int k = m.nrects - 1;
-  while (k > 0 && b < m.r[k].first) --k;
-  const FuseRect r = m.r[k];
-  Pair pairs[kStrips / 2] = {};
-  if (r.kind == kFuseBody) {
-    const int pair = wave >> 1, half = wave & 1;
-#pragma unroll
-    for (int p = 0; p < kStrips / 2; ++p) {
-      const int unit = (b - r.first) * (kStrips / 2) + p, chunk = unit / r.nw;
-      const int ya = min(r.y0 + chunk * r.rows, r.y1);
-      pairs[p] = {r.x0 + (unit - chunk * r.nw) * kStripW, ya, min(ya + r.rows, r.y1)};
-    }
-    const Pair me = pair == 0 ? pairs[0] : pairs[1];
-    const int X = me.x0 + half * kHalf;
-    march_coded<P, FORCES, COLL, MOV, true>(a, q, X, min(max(a.nx - X, 0), kHalf), me.ya, me.yb,
-                                            r.rows, 64 - kHalf / 2, pairs, pair, half, ex);
+  fused_block<P, FORCES, COLL, MOV>(a, q.map, q.step, block_tile<kFuseGroup>(b, q.map.nblocks), ex);
+}
+
+// kFuse steps of every instance of a batch: the first blocks reduce the force rows of the
+// launch before this one, the others take the instances' blocks in the order of the item list.
+template <int P, bool FORCES, bool MOV>
+__global__ __launch_bounds__(kThreads)
+    __attribute__((amdgpu_waves_per_eu(sizeof(typename Storage<P>::T) == 4 ? 3 : 2)))
+void batch_fused_kernel(BatchFuse b) {
+  __shared__ Exchange ex;
+  int t = int(blockIdx.x);
+  if (t < b.nred_blocks) {
+    const int i = t / b.nred, r = t - i * b.nred;
+    if (i >= b.n_inst) return;
+    const BatchInst& I = b.inst[i];
+    const int64_t rs = int64_t(b.n_inst) * kRingRow;  // rows are step-major
+    double* row = I.ring + (b.red_row + r) * rs;
+    reduce_row(I.part[b.turn ^ 1] + r * I.part_stride, I.a.nslots, I.a.njslots, row,
+               r > 0 || b.red_has_prev ? row - rs + kJnext : nullptr);
     return;
   }
-  const int unit = (b - r.first) * kStrips + wave, chunk = unit / r.nw;
-  const int ya = r.y0 + chunk * r.rows, yb = min(ya + r.rows, r.y1);
-  if (ya >= yb) return;
-  const int w = unit - chunk * r.nw;
-  if (r.kind == kFusePlain) {
-    march_plain<P, COLL>(a, q, r.x0 + w * (kFuseLanes * Kept<P>::kN), r.x1, ya, yb - ya);
-  } else {
-    const int X = r.x0 + w * kFuseEdgeW;
-    march_coded<P, false, COLL, false, false>(a, q, X, min(kFuseEdgeW, r.x1 - X), ya, yb, yb - ya,
-                                            64 - kM, pairs, 0, 0, ex);
-  }
+  t -= b.nred_blocks;
+  const int i = b.item_inst[t];
+  const BatchInst& I = b.inst[i];
+  StepArgs a = I.a;
+  a.src = I.buf[b.parity];
+  a.dst = I.buf[1 - b.parity];
+  FuseStep q;
+  q.part_out = I.part[b.turn];
+  q.part_stride = I.part_stride;
+#pragma unroll
+  for (int j = 0; j < kFuse; ++j)
+    q.step_key[j] = Storage<P>::kSR ? sr_step_key(b.step0 + I.step_off + j) : 0u;
+  fused_block<P, FORCES, LBM_COLL_BGK, MOV>(a, b.map[i], q, b.item_local[t], ex);
 }
 
 template <int P, bool MOV>
@@ -614,7 +667,35 @@ hipError_t fused_go(bool forces, const StepArgs& a, const FuseArgs& q, hipStream
   return a.motion ? fused_go2<P, true>(forces, a, q, s) : fused_go2<P, false>(forces, a, q, s);
 }
 
+template <int P>
+hipError_t batch_fused_go(bool forces, const BatchFuse& b, hipStream_t s) {
+  const dim3 grid(unsigned(b.nred_blocks + b.nitems));
+  if (forces) {
+    if (b.moving)
+      hipLaunchKernelGGL((batch_fused_kernel<P, true, true>), grid, dim3(kThreads), 0, s, b);
+    else
+      hipLaunchKernelGGL((batch_fused_kernel<P, true, false>), grid, dim3(kThreads), 0, s, b);
+  } else {
+    if (b.moving)
+      hipLaunchKernelGGL((batch_fused_kernel<P, false, true>), grid, dim3(kThreads), 0, s, b);
+    else
+      hipLaunchKernelGGL((batch_fused_kernel<P, false, false>), grid, dim3(kThreads), 0, s, b);
+  }
+  return hipGetLastError();
+}
+
 }  // namespace
+
+hipError_t launch_batch_fused(int precision, bool forces, const BatchFuse& b, hipStream_t s) {
+  switch (precision) {
+    case LBM_FP64: return batch_fused_go<LBM_FP64>(forces, b, s);
+    case LBM_FP32: return batch_fused_go<LBM_FP32>(forces, b, s);
+    case LBM_FP32DEV: return batch_fused_go<LBM_FP32DEV>(forces, b, s);
+    case LBM_FP32SR: return batch_fused_go<LBM_FP32SR>(forces, b, s);
+    case LBM_FP16DEV: return batch_fused_go<LBM_FP16DEV>(forces, b, s);
+    default: return hipErrorInvalidValue;
+  }
+}
 
 hipError_t launch_fused(int precision, bool forces, const StepArgs& a, const FuseArgs& q,
                         hipStream_t s) {

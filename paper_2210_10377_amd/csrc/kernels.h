@@ -93,13 +93,18 @@ struct BoxArgs {
   double* jpart;              // [blocks][2]
 };
 
+// What the steps of a fused launch write and draw from, besides the state.
+struct FuseStep {
+  double* part_out;       // force partials of the first step, or null
+  int64_t part_stride;    // doubles between the partials of successive steps
+  uint32_t step_key[kFuse];
+};
+
 // Arguments of a fused launch besides the step's own (src is the state kFuse steps before
 // dst; part_out and the reduction are given here).
 struct FuseArgs {
   FuseMap map;
-  double* part_out;       // force partials of the first step, or null
-  int64_t part_stride;    // doubles between the partials of successive steps
-  uint32_t step_key[kFuse];
+  FuseStep step;
   // Force rows of the launch before this one: partials and ring rows of nred steps.
   int32_t nred;
   const double* red_in;
@@ -114,6 +119,7 @@ struct FinalArgs {
   int64_t part_stride;    // doubles between the partials of successive steps
   int32_t nslots, njslots;
   double* row;            // ring row of the first
+  int64_t row_stride;     // doubles between successive rows
   double* prev_jnext;     // Jnext slot of the row before it, or null
   const double* jpart;    // [njblocks][2], or null when there is no box
   int32_t njblocks;
@@ -123,7 +129,8 @@ struct FinalArgs {
 struct BatchInst {
   StepArgs a;               // geometry, tables and physics (src/dst/partials unused)
   void* buf[2];             // the two state buffers
-  double* part[2];          // force partial buffers of alternate steps
+  double* part[2];          // force partial buffers of alternate launches
+  int64_t part_stride;      // doubles between the partials of a fused launch's steps
   double* ring;             // this instance's force row of step 0 ([rows][n_inst][kRingRow])
   BoxArgs box;              // control-volume sweep (src chosen per launch)
   int32_t njblocks;         // blocks of that sweep (0 without a box)
@@ -148,6 +155,20 @@ struct BatchLaunch {
   int32_t grid_blocks;       // tile blocks per launch (0: one block per tile)
   int32_t collision;         // LBM_COLL_* of every instance
   int32_t moving;            // some instance has a body in motion
+};
+
+// A fused launch of a batch.
+struct BatchFuse {
+  const BatchInst* inst;      // [n_inst], device
+  const FuseMap* map;         // [n_inst], device
+  const int32_t* item_inst;   // [nitems] instance of each block, device
+  const int32_t* item_local;  // [nitems] its block in the instance's map, device
+  int32_t n_inst, nitems;
+  int32_t parity, turn;       // source buffer, partials written
+  int32_t moving;             // some instance has a body in motion
+  int32_t nred, nred_blocks;  // steps of the launch before this one to reduce; blocks for it
+  int32_t red_row, red_has_prev;  // ring row of the first of them; the row before takes its Jnext
+  int64_t step0;              // the batch's step count before the launch
 };
 
 // A mask change of a body moving through the grid, over the current state buffer.
@@ -189,14 +210,16 @@ hipError_t launch_remask(int precision, const RemaskArgs& a, int blocks, double*
                          hipStream_t s);
 hipError_t launch_batch_step(int precision, bool forces, const BatchLaunch& b, int32_t parity,
                              int32_t k, hipStream_t s);
+// kFuse steps of every instance in one launch.
+hipError_t launch_batch_fused(int precision, bool forces, const BatchFuse& b, hipStream_t s);
 hipError_t launch_batch_ctl(int32_t* ctl, int32_t row_base, int32_t nprev, int64_t base,
                             hipStream_t s);
 // Zeroes both tile counters of the queue schedule (before a call's first launch).
 hipError_t launch_batch_queue_reset(int32_t* queue, hipStream_t s);
-// Control-volume sweeps over buffer `parity` and finalization of force row `row` of every
-// instance (the last step of a call; its partials are in part[part_parity]).
+// Control-volume sweeps over buffer `parity` and finalization of the force rows of a call's
+// last launch, nrows from `row`, of every instance (partials in part[part_parity]).
 hipError_t launch_batch_tail(int precision, const BatchLaunch& b, int32_t parity, int32_t row,
-                             int32_t part_parity, bool has_prev, hipStream_t s);
+                             int32_t nrows, int32_t part_parity, bool has_prev, hipStream_t s);
 hipError_t launch_box_momentum(int precision, const BoxArgs& a, int blocks, hipStream_t s);
 hipError_t launch_finalize(const FinalArgs& a, hipStream_t s);
 // Rest state w_i in every element of a population buffer (padding included).

@@ -372,9 +372,9 @@ __global__ __launch_bounds__(kThreads) void batch_box_kernel(BatchLaunch b, int3
 // Block r of a finalization: row r of the last launch's a.nrows rows, the last of them with
 // the J of the pull after it.
 __device__ __forceinline__ void finalize_body(const FinalArgs& a, int r) {
-  double* row = a.row + int64_t(r) * kRingRow;
+  double* row = a.row + r * a.row_stride;
   reduce_row(a.red_in + r * a.part_stride, a.nslots, a.njslots, row,
-             r > 0 ? row - kRingRow + kJnext : a.prev_jnext);
+             r > 0 ? row - a.row_stride + kJnext : a.prev_jnext);
   if (r + 1 < a.nrows) return;
   if (a.jpart) {
     __syncthreads();
@@ -401,23 +401,26 @@ __global__ __launch_bounds__(kThreads) void finalize_kernel(FinalArgs a) {
   finalize_body(a, int(blockIdx.x));
 }
 
-// Finalize of every instance of a batch (one block each): force row `row` from the
-// partials part[part_parity] and, without a box, NaN for its Jnext.
+// Finalize of every instance of a batch (nrows blocks each): the force rows from `row` on, from
+// the partials part[part_parity], and, without a box, NaN for the Jnext of the last.
 __global__ __launch_bounds__(kThreads) void batch_finalize_kernel(BatchLaunch b, int32_t row,
+                                                                  int32_t nrows,
                                                                   int32_t part_parity,
                                                                   int32_t has_prev) {
-  const BatchInst& I = b.inst[blockIdx.x];
+  const BatchInst& I = b.inst[blockIdx.x / nrows];
   FinalArgs f{};
-  f.nrows = 1;
+  f.nrows = nrows;
   f.red_in = I.part[part_parity];
+  f.part_stride = I.part_stride;
   f.nslots = I.a.nslots;
   f.njslots = I.a.njslots;
   const int64_t rs = int64_t(b.n_inst) * kRingRow;  // rows are step-major
   f.row = I.ring + int64_t(row) * rs;
+  f.row_stride = rs;
   f.prev_jnext = has_prev ? I.ring + (int64_t(row) - 1) * rs + kJnext : nullptr;
   f.jpart = I.njblocks > 0 ? I.box.jpart : nullptr;
   f.njblocks = I.njblocks;
-  finalize_body(f, 0);
+  finalize_body(f, int(blockIdx.x) % nrows);
 }
 
 template <int P>
@@ -658,7 +661,7 @@ hipError_t launch_batch_ctl(int32_t* ctl, int32_t row_base, int32_t nprev, int64
 }
 
 hipError_t launch_batch_tail(int precision, const BatchLaunch& b, int32_t parity, int32_t row,
-                             int32_t part_parity, bool has_prev, hipStream_t s) {
+                             int32_t nrows, int32_t part_parity, bool has_prev, hipStream_t s) {
   if (b.total_box_blocks > 0) {
     const dim3 grid(b.total_box_blocks);
     switch (precision) {
@@ -683,8 +686,8 @@ hipError_t launch_batch_tail(int precision, const BatchLaunch& b, int32_t parity
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(batch_finalize_kernel, dim3(b.n_inst), dim3(kThreads), 0, s, b, row,
-                     part_parity, int32_t(has_prev ? 1 : 0));
+  hipLaunchKernelGGL(batch_finalize_kernel, dim3(b.n_inst * nrows), dim3(kThreads), 0, s, b, row,
+                     nrows, part_parity, int32_t(has_prev ? 1 : 0));
   return hipGetLastError();
 }
 

@@ -355,7 +355,10 @@ bool fuse_pays(int precision, int collision, double nodes, double body) {
   // and 101 : 98.
   // The stabilized collisions stay with single steps: regularized, binary32, 1024 x 512 without
   // forces 8.1 : 9.5, a moving airfoil with forces 12.4 : 13.3.  A node of the body rectangle
-  // costs several times what a plain one costs.
+  // costs several times what a plain one costs.  Batches behave alike (body share 0.11, with
+  // forces and without): binary32, 16 lattices of 43 000 nodes 20 : 19 and 16 : 15, 64
+  // 47 : 47 and 42 : 34, 256 175 : 148 and 170 : 106; binary64 31 : 24 and 29 : 18, 84 : 61 and
+  // 84 : 45, 336 : 230 and 349 : 169; stochastically rounded 256 193 : 237.
   if (collision != LBM_COLL_BGK) return false;
   switch (precision) {
     case LBM_FP64: return nodes >= 2.5e5 && body <= 0.4;
@@ -366,13 +369,13 @@ bool fuse_pays(int precision, int collision, double nodes, double body) {
   }
 }
 
-FuseMap fuse_map(const Plan& p, int elem_bytes) {
+FuseMap fuse_map(const Plan& p, int elem_bytes, int64_t nodes) {
   constexpr int kM = kFuseM;
   // Rows of a unit: in the plain rectangles few enough to give every SIMD three waves, many
   // enough to keep the margins (two rows of two steps) small; in the body rectangle as many as
   // a launch has time for (a row of three steps with forces takes 5 - 8 us, a launch of
   // 8192 x 4096 in binary32 500 us, of 1024 x 512 27 us).
-  const int64_t bytes = int64_t(p.nx) * p.ny * kQ * elem_bytes;
+  const int64_t bytes = nodes * kQ * elem_bytes;
   const int64_t lanes = bytes / (kQ * 8) / kFuseLanes;  // units of one row
   const int rows = int(std::clamp<int64_t>(lanes / 3072, 6, 12));
   const int body_rows = int(std::clamp<int64_t>(2 + bytes / 37000000, 2, 32));
@@ -413,8 +416,10 @@ FuseMap fuse_map(const Plan& p, int elem_bytes) {
     r.first = m.nblocks;
     const int per = kind == kFuseBody ? kStripW
                                       : (kind == kFuseEdge ? kFuseEdgeW : kFuseLanes * 8 / elem_bytes);
-    r.rows = int16_t(kind == kFuseBody ? body_rows : (kind == kFuseEdge ? edge_rows : rows));
-    r.nw = (ax1 - ax0 + per - 1) / per;
+    r.rows = int16_t(kind == kFuseBody ? body_rows : (kind == kFusePlain ? rows : edge_rows));
+    r.nw = kind == kFuseSides  ? 1
+           : kind == kFuseBody ? (ax1 - ax0 / kStripW * kStripW + per - 1) / per
+                               : (ax1 - ax0 + per - 1) / per;
     const int64_t units = int64_t(r.nw) * ((ay1 - ay0 + r.rows - 1) / r.rows);
     const int in_block = kind == kFuseBody ? kStrips / 2 : kStrips;
     m.nblocks += int32_t((units + in_block - 1) / in_block);
@@ -426,8 +431,8 @@ FuseMap fuse_map(const Plan& p, int elem_bytes) {
   Box around[4];
   int n = 0;
   if (x0 <= x1) {
-    x0 = std::max(x0, 0) / kStripW * kStripW;
-    x1 = std::min((x1 / kStripW + 1) * kStripW, p.nx);
+    x0 = std::max(x0, 0) / kHalf * kHalf;
+    x1 = std::min((x1 / kHalf + 1) * kHalf, p.nx);
     y0 = std::max(y0, 0);
     y1 = std::min(y1 + 1, p.ny);
     add(kFuseBody, x0, x1, y0, y1);
@@ -443,16 +448,30 @@ FuseMap fuse_map(const Plan& p, int elem_bytes) {
   // first column).
   const int sector = 64 / elem_bytes;
   const Box in = {sector, (p.nx - kM - 1) / sector * sector, kM + 1, p.ny - kM - 1};
-  // Edge units take longest, so they start first.
-  for (int pass = 0; pass < 2; ++pass)
+  // The columns beside the interior, left and right of it in one window where both sides (with
+  // their margins) fit one.
+  const bool sides = in.x0 + kM <= kSideRight && p.nx - in.x1 + 2 * kM <= 64 - kM - kSideRight &&
+                     in.x0 < in.x1;
+  // Units that take longest start first.
+  for (int pass = 0; pass < 3; ++pass)
     for (int k = 0; k < n; ++k) {
       const Box& b = around[k];
       if (b.x0 >= b.x1 || b.y0 >= b.y1) continue;
       const Box c = {std::max(b.x0, in.x0), std::min(b.x1, in.x1), std::max(b.y0, in.y0),
                      std::min(b.y1, in.y1)};
+      // Beside the body: its left rectangle takes both sides if the right one reaches inside.
+      const bool beside = n == 4 && (k == 1 || k == 2);
+      const bool both = sides && c.y0 < c.y1 &&
+                        (beside ? around[1].x1 >= in.x0 && around[2].x0 <= in.x1
+                                : c.x0 < c.x1);
       const bool none = c.x0 >= c.x1 || c.y0 >= c.y1;
-      if (pass == 1) {
+      if (pass == 2) {
         if (!none) add(kFusePlain, c.x0, c.x1, c.y0, c.y1);
+      } else if (pass == 1) {
+        if (both && k != 2) add(kFuseSides, in.x0, in.x1, c.y0, c.y1);
+      } else if (both) {
+        add(kFuseEdge, b.x0, b.x1, b.y0, c.y0);
+        add(kFuseEdge, b.x0, b.x1, c.y1, b.y1);
       } else if (none) {
         add(kFuseEdge, b.x0, b.x1, b.y0, b.y1);
       } else {

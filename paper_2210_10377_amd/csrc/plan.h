@@ -145,8 +145,10 @@ constexpr int strip_class(int nx, int ny, int gx0, int gx1, int gy0, int gy1, in
 // Work map of the fused kernel, which advances a lattice by kFuse steps in one launch: the
 // grid cut into rectangles of one kind of work each, and these into units, one a wave.
 //   kFuseBody: every node with a force term, and the nodes with body codes (with kFuseM nodes of
-//     margin); columns in whole strips, two waves a strip and two strips a block;
+//     margin); columns in half strips, two waves a strip (one idle where its half lies outside)
+//     and two strips a block;
 //   kFuseEdge: nodes whose windows reach the edges of the grid;
+//   kFuseSides: the columns left of x0 and those from x1 on, both in one window;
 //   kFusePlain: the rest, whose windows stream plainly, margins included: windows of
 //     kFuseLanes lanes of 8 bytes each, whole 64-byte sectors of every row.
 constexpr int kFuse = 3;
@@ -154,7 +156,10 @@ constexpr int kFuseM = kFuse - 1;
 constexpr int kFuseLanes = 56;
 constexpr int kFuseEdgeW = 64 - 2 * kFuseM;
 constexpr int kHalf = kStripW / 2;
-enum FuseKind { kFuseBody = 0, kFuseEdge = 1, kFusePlain = 2 };
+enum FuseKind { kFuseBody = 0, kFuseEdge = 1, kFuseSides = 2, kFusePlain = 3 };
+// Lanes of a kFuseSides window: column l in lane l < kSideRight, the columns from x1 - kFuseM
+// on from lane kSideRight, columns -kFuseM .. -1 in the last lanes.
+constexpr int kSideRight = 24;
 struct FuseRect {
   int32_t x0, x1, y0, y1;  // half-open
   int16_t kind, rows;      // FuseKind; rows of a unit
@@ -201,11 +206,12 @@ int build_plan(const lbm_grid& g, const uint8_t* mask, Plan& p, std::string& err
 // tile order.
 void tile_slots(const Plan& p, int rows, int& ntx, int& nty, std::vector<int32_t>& out);
 
-// The fused kernel's work map of p for elements of elem_bytes.
-FuseMap fuse_map(const Plan& p, int elem_bytes);
+// The fused kernel's work map of p for elements of elem_bytes, in a launch of `nodes` nodes in
+// all (p's own, or those of a batch).
+FuseMap fuse_map(const Plan& p, int elem_bytes, int64_t nodes);
 
 // Whether fused launches are faster than single steps for `nodes` nodes, the share `body` of
-// them in the body rectangle.
+// them in the body rectangles (of one lattice, or of a batch's lattices together).
 bool fuse_pays(int precision, int collision, double nodes, double body);
 
 // Node words a mask change rewrites (index, old word, new word), in index order.

@@ -389,3 +389,41 @@ def test_schedule_validation():
     assert C.load().lbm_batch_set_schedule(b._h, ctypes.byref(s)) == C.LBM_EINVAL
     b.set_schedule(tile_shape="narrow")
     assert b.info().schedule.tile_shape == C.LBM_TILE_NARROW
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision", ["fp64", "fp32dev"])
+def test_fused_batch_bitwise_equals_singles(precision):
+    """A batch large enough for three steps per launch, among its members one in motion and one
+    moved through the grid between the calls: every instance bitwise equal to the member
+    stepped alone (whatever launches each takes), in calls of 1, 8 and 3 steps."""
+    from paper_2210_10377_amd import Batch, Sim
+    ws = workloads.batched_instances(14, seed=11)
+    runs = []
+    for batched in (True, False):
+        sims = [Sim(w.mask, w.tau, w.uin, precision=precision, box=w.box, max_record=12,
+                    u_ref=w.u_ref, l_ref=w.l_ref) for w in ws]
+        assert sum(s.nx * s.ny for s in sims) >= 400_000
+        sims[3].set_body_motion(ux=0.004, omega=1e-4, xc=0.3 * sims[3].nx, yc=0.5 * sims[3].ny)
+        b = Batch(sims, max_record=12) if batched else None
+        out = []
+        for k in (1, 8, 3):
+            print(f"fused batch {precision} batched={batched} k={k}", flush=True)
+            if batched:
+                b.step(k)
+                F = list(b.forces()[0])
+            else:
+                for s in sims:
+                    s.step(k)
+                F = [s.forces() for s in sims]
+            out.append(F)
+            if k == 8:
+                m = np.roll(ws[5].mask, 1, axis=1)
+                box = (ws[5].box[0] + 1, ws[5].box[1] + 1, *ws[5].box[2:])
+                out.append([sims[5].set_mask(m, box)])
+        out.append([s.populations() for s in sims])
+        runs.append(out)
+        del b, sims
+    for a, c in zip(*runs):
+        for x, y in zip(a, c):
+            np.testing.assert_array_equal(x, y)

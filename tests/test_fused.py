@@ -55,7 +55,7 @@ int main() {
     if (build_plan(g, mask.data(), p, err) != LBM_OK) continue;
     for (int e = 0; e < 3; ++e) {
       esz = e == 0 ? 8 : (e == 1 ? 4 : 2);
-      const FuseMap m = fuse_map(p, esz);
+      const FuseMap m = fuse_map(p, esz, int64_t(pick(0, 1) ? 1 : 50000) * g.nx * g.ny);
       CHECK(m.nrects <= kFuseRects && m.nrects >= 1);
       std::vector<int> owner(mask.size(), 0), kindof(mask.size(), -1);
       int blocks = 0;
@@ -64,14 +64,21 @@ int main() {
         CHECK(r.x0 >= 0 && r.x0 < r.x1 && r.x1 <= g.nx && r.y0 >= 0 && r.y0 < r.y1 && r.y1 <= g.ny);
         CHECK(r.first == blocks && r.rows >= 1);
         const int per = r.kind == kFuseBody ? kStripW : (r.kind == kFuseEdge ? kFuseEdgeW : kFuseLanes * 8 / esz);
-        CHECK(r.nw == (r.x1 - r.x0 + per - 1) / per);
+        if (r.kind == kFuseSides) CHECK(r.nw == 1);
+        else CHECK(r.nw == (r.x1 - (r.kind == kFuseBody ? r.x0 / kStripW * kStripW : r.x0) + per - 1) / per);
         const int units = r.nw * ((r.y1 - r.y0 + r.rows - 1) / r.rows);
         const int in = r.kind == kFuseBody ? kStrips / 2 : kStrips;
         blocks += (units + in - 1) / in;
-        if (r.kind == kFuseBody) CHECK(k == 0 && r.x0 % kStripW == 0 && (r.x1 % kStripW == 0 || r.x1 == g.nx));
+        if (r.kind == kFuseBody) CHECK(k == 0 && r.x0 % kHalf == 0 && (r.x1 % kHalf == 0 || r.x1 == g.nx));
         if (r.kind == kFusePlain) CHECK(r.x0 * esz % 64 == 0);
+        if (r.kind == kFuseSides) {
+          // Both sides and their margins in lanes of their own.
+          CHECK(r.x0 + kFuseM <= kSideRight);
+          CHECK(kSideRight + kFuseM + (g.nx - r.x1) + kFuseM <= 64 - kFuseM);
+        }
         for (int y = r.y0; y < r.y1; ++y)
-          for (int x = r.x0; x < r.x1; ++x) {
+          for (int x = r.kind == kFuseSides ? 0 : r.x0; x < (r.kind == kFuseSides ? g.nx : r.x1); ++x) {
+            if (r.kind == kFuseSides && x >= r.x0 && x < r.x1) continue;
             ++owner[size_t(y) * g.nx + x];
             kindof[size_t(y) * g.nx + x] = r.kind;
           }
@@ -82,10 +89,12 @@ int main() {
         for (int x = 0; x < g.nx; ++x) {
           const size_t at = size_t(y) * g.nx + x;
           CHECK(owner[at] == 1);                                // every node once
-          if (p.row_slot[size_t(y) * nsx + x / kStripW] >= 0 && kindof[at] != kFuseBody) {
-            // A strip with a slot lies in the body rectangle as a whole.
-            CHECK(false);
-          }
+          // A node with a force term lies in the body rectangle.
+          bool term = p.has_box && x >= p.box[0] - 1 && x <= p.box[1] && y >= p.box[2] - 1 && y <= p.box[3];
+          for (int i = 1; i < kQ; ++i)
+            term = term || (!(p.node[at] & kSolidBit) && pull_code(p.node[at], i) == kBody);
+          if (term) CHECK(kindof[at] == kFuseBody);
+          if (term) CHECK(p.row_slot[size_t(y) * nsx + x / kStripW] >= 0);
           // Within the margin of a node outside the body rectangle every code is the edge's;
           // around a plain node all stream.
           if (kindof[at] == kFuseBody) continue;
