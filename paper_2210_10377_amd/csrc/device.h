@@ -257,80 +257,53 @@ struct Planes<T, false> {
 // BGK collision (see collide) with every fused operation named and none left to the compiler,
 // so that each kernel that inlines it rounds alike.  Terms even in the velocity serve both
 // directions of an opposite pair; that changes no result, since c.u of the one is exactly minus
-// that of the other.
-//
-// Binary32: f^eq = w z, z = s + rho poly (deviations) or rho (1 + poly), poly = 3 c.u +
-// 4.5 (c.u)^2 - 1.5 u^2.  EXACT off (binary16 storage): bare weights, and the last operation
-// rounds once, to binary16; the compiler joins it with the conversion that follows in the
-// kernels that only store the result, and FP16 names the joint operation for the others.
-template <bool DEV, bool EXACT, bool FP16>
-__device__ __forceinline__ void collide_bgk32(const float (&f)[kQ], float om, float (&g)[kQ]) {
+// that of the other.  f^eq = w z, z = s + rho poly (deviations) or rho (1 + poly), poly = 3 c.u +
+// 4.5 (c.u)^2 - 1.5 u^2.  EXACT (32-bit storage): weights to more than their own precision, see
+// wmul.  With bare weights in binary16 storage the last operation rounds once, to binary16; the
+// compiler joins it with the conversion that follows in the kernels that only store the result,
+// and FP16 names the joint operation for the others.
+template <class C, bool DEV, bool EXACT, bool FP16>
+__device__ __forceinline__ void collide_bgk(const C (&f)[kQ], C om, C (&g)[kQ]) {
 #pragma clang fp contract(off)
-  const float s = ((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7])) + f[8];
-  const float jx = (f[1] + f[5] + f[8]) - (f[3] + f[6] + f[7]);
-  const float jy = (f[2] + f[5] + f[6]) - (f[4] + f[7] + f[8]);
-  const float rho = DEV ? 1.0f + s : s;
-  const float ir = 1.0f / rho;
-  const float ux = jx * ir, uy = jy * ir;
-  const float uu = __builtin_fmaf(ux, ux, uy * uy);
-  auto relax = [&](int i, float poly) {
-    const float z = DEV ? __builtin_fmaf(rho, poly, s) : rho * (1.0f + poly);
-    const float w = weight<float>(i);
-    if constexpr (EXACT) {
-      const float fe = __builtin_fmaf(w, z, weight_lo(i) * z);
-      g[i] = __builtin_fmaf(om, fe - f[i], f[i]);
+  auto fma = [](C a, C b, C c) __attribute__((always_inline)) {
+    if constexpr (sizeof(C) == 8)
+      return __builtin_fma(a, b, c);
+    else
+      return __builtin_fmaf(a, b, c);
+  };
+  const C s = ((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7])) + f[8];
+  const C jx = (f[1] + f[5] + f[8]) - (f[3] + f[6] + f[7]);
+  const C jy = (f[2] + f[5] + f[6]) - (f[4] + f[7] + f[8]);
+  const C rho = DEV ? C(1) + s : s;
+  const C ir = C(1) / rho;
+  const C ux = jx * ir, uy = jy * ir;
+  const C uu = fma(ux, ux, uy * uy);
+  auto relax = [&](int i, C poly) __attribute__((always_inline)) {
+    const C z = DEV ? fma(rho, poly, s) : rho * (C(1) + poly);
+    const C w = weight<C>(i);
+    if constexpr (sizeof(C) == 4 && EXACT) {
+      const C fe = fma(w, z, weight_lo(i) * z);
+      g[i] = fma(om, fe - f[i], f[i]);
     } else {
-      const float d = __builtin_fmaf(w, z, -f[i]);
+      const C d = fma(w, z, -f[i]);
       if constexpr (FP16) {
         _Float16 h;
         asm("v_fma_mixlo_f16 %0, %1, %2, %3" : "=v"(h) : "v"(om), "v"(d), "v"(f[i]));
-        g[i] = float(h);
+        g[i] = C(h);
       } else {
-        g[i] = __builtin_fmaf(om, d, f[i]);
+        g[i] = fma(om, d, f[i]);
       }
     }
   };
-  relax(0, -1.5f * uu);
+  relax(0, C(-1.5) * uu);
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     constexpr int kPair[4] = {1, 2, 5, 6};
     const int i = kPair[k];
-    const float cu = i == 1 ? ux
-                            : (i == 2 ? uy
-                                      : (i == 5 ? __builtin_fmaf(jx, ir, uy)
-                                                : __builtin_fmaf(-jx, ir, uy)));
-    const float sq = (4.5f * cu) * cu;
-    relax(i, __builtin_fmaf(-1.5f, uu, __builtin_fmaf(3.0f, cu, sq)));
-    relax(i + 2, __builtin_fmaf(-1.5f, uu, __builtin_fmaf(-3.0f, cu, sq)));
-  }
-}
-
-// Binary64: f^eq (deviations: f^eq - w) = w [s + rho (4.5 (c.u)^2 - 1.5 u^2) + 3 c.j], the
-// density from sums of opposite directions, the momentum from their differences.
-template <bool DEV>
-__device__ __forceinline__ void collide_bgk64(const double (&f)[kQ], double om, double (&g)[kQ]) {
-#pragma clang fp contract(off)
-  const double p1 = f[1] + f[3], p2 = f[2] + f[4], p5 = f[5] + f[7], p6 = f[6] + f[8];
-  const double m1 = f[1] - f[3], m2 = f[2] - f[4], m5 = f[5] - f[7], m6 = f[6] - f[8];
-  const double s = f[0] + ((p1 + p2) + (p5 + p6));
-  const double jx = m1 + (m5 - m6), jy = m2 + (m5 + m6);
-  const double rho = DEV ? 1.0 + s : s;
-  const double ir = 1.0 / rho;
-  const double ux = jx * ir, uy = jy * ir;
-  const double usq = 1.5 * __builtin_fma(ux, ux, uy * uy);
-  auto relax = [&](int i, double z) {
-    g[i] = __builtin_fma(om, weight<double>(i) * z - f[i], f[i]);
-  };
-  relax(0, __builtin_fma(-rho, usq, s));
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    constexpr int kPair[4] = {1, 2, 5, 6};
-    const int i = kPair[k];
-    const double cu = i == 1 ? ux : (i == 2 ? uy : (i == 5 ? ux + uy : uy - ux));
-    const double cj = i == 1 ? jx : (i == 2 ? jy : (i == 5 ? jx + jy : jy - jx));
-    const double even = __builtin_fma(rho, __builtin_fma(4.5 * cu, cu, -usq), s);
-    relax(i, __builtin_fma(3.0, cj, even));
-    relax(i + 2, __builtin_fma(-3.0, cj, even));
+    const C cu = i == 1 ? ux : (i == 2 ? uy : (i == 5 ? fma(jx, ir, uy) : fma(-jx, ir, uy)));
+    const C sq = (C(4.5) * cu) * cu;
+    relax(i, fma(C(-1.5), uu, fma(C(3), cu, sq)));
+    relax(i + 2, fma(C(-1.5), uu, fma(C(-3), cu, sq)));
   }
 }
 
@@ -352,11 +325,8 @@ __device__ __forceinline__ void collide_bgk64(const double (&f)[kQ], double om, 
 // is formed except the entropic weights f^eq_i.
 template <class C, bool DEV, int COLL, bool EXACT = true, bool FP16 = false>
 __device__ __forceinline__ void collide(const C (&f)[kQ], C omega, C (&g)[kQ]) {
-if constexpr (COLL == LBM_COLL_BGK) {
-    if constexpr (sizeof(C) == 8)
-      collide_bgk64<DEV>(f, omega, g);
-    else
-      collide_bgk32<DEV, EXACT, FP16>(f, omega, g);
+  if constexpr (COLL == LBM_COLL_BGK) {
+    collide_bgk<C, DEV, EXACT, FP16>(f, omega, g);
     return;
   }
   const C s = ((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7])) + f[8];
