@@ -2,7 +2,7 @@
 // the per-step forces (A, B, DRTT terms, SI), the control-volume momentum sweep, and the
 // fixed-order reductions of the force partials into ring rows.
 //
-// One launch per step.  A block of 256 threads covers a tile of 256 nodes along x in one
+// One launch per step (two where the strips with force terms have their own).  A block of 256 threads covers a tile of 256 nodes along x in one
 // (y, z) row; each wave a 64-node strip whose class (strip table) picks its path:
 //   plain / box-J: 27 loads at fixed offsets (no boundary within reach), collision,
 //     27 non-temporal stores; box-J strips add the momentum of their pulled populations;
@@ -10,12 +10,19 @@
 //     a periodic wrap, bounce-back (wall, body, outlet ghost of a solid node), the inlet
 //     moving-wall rule or the outlet ghost copy; strips with force terms accumulate A, B,
 //     J, Phi and SI in FP64 and reduce them over the wave into their slot.
+// Large grids are bound by HBM (1280 x 128 x 64 in binary32: 5.8 TB/s), small ones by the
+// latency of a strip with force terms: 64 x 32 x 32 took 30 us a step, 22 of them in that
+// strip's launch, while it branched on every direction of the pull and of the link terms and
+// summed over lanes through LDS; without branches (selects by bit masks, walls and wrapped
+// rows scalar), with lane sums by register swaps and rotations, and in the step's own launch
+// it takes 11.
 // The first block of a launch reduces the previous step's slots, in a fixed order, into
 // that step's ring row.  Blocks are mapped to tiles so that runs of kXcdRun (8)
 // neighbouring tiles along x go to one XCD (their +-1-shifted pulls share cache lines in
 // that L2).
 #include <hip/hip_runtime.h>
 
+#include "device.h"
 #include "kernels.h"
 #include "kernels3.h"
 #include "lbm.h"
@@ -214,39 +221,25 @@ __device__ __forceinline__ void collide27(C (&f)[kQ], C omega) {
 
 __device__ __forceinline__ int wrapc(int s, int n) { return s < 0 ? s + n : (s >= n ? s - n : s); }
 
+__device__ __forceinline__ bool in_range(const Geom3& g, int axis, int at) {
+  return g.whole[axis] || (at >= g.box[2 * axis] && at < g.box[2 * axis + 1]);
+}
 __device__ __forceinline__ bool in_box(const Geom3& g, int x, int y, int z) {
-  return (g.whole[0] || (x >= g.box[0] && x < g.box[1])) &&
-         (g.whole[1] || (y >= g.box[2] && y < g.box[3])) &&
-         (g.whole[2] || (z >= g.box[4] && z < g.box[5]));
+  return in_range(g, 0, x) && in_range(g, 1, y) && in_range(g, 2, z);
 }
 
-// Source of the pull of direction i at fluid node (x, y, z) with node word w: the
-// element offset of the source node ((z ny + y) rstride + x), and whether direction
-// opp(i) of the node itself is read (bounce-back: wall, body, outlet ghost of a solid node; the inlet's
-// moving-wall rule).  *inl: the inlet term applies; *body: a force-bearing body link in
-// direction opp(i).
-__device__ __forceinline__ int32_t pull_offset(const Geom3& g, int x, int y, int z, uint32_t w,
-                                               int i, int32_t self, bool* bb, bool* inl,
-                                               bool* body) {
-  int sx = x - kCx[i], sy = y - kCy[i], sz = z - kCz[i];
-  if (g.bc_x == LBM_BCX_PERIODIC) sx = wrapc(sx, g.nx);
-  if (g.bc_y == LBM_BCY_PERIODIC) sy = wrapc(sy, g.ny);
-  if (g.bc_z == LBM_BCY_PERIODIC) sz = wrapc(sz, g.nz);
-  *inl = false;
-  *body = false;
-  *bb = true;
-  if (sy < 0 || sy >= g.ny || sz < 0 || sz >= g.nz) return self;  // wall
-  if ((w >> i) & 1u) {
-    *body = sx >= 0 && sx < g.nx;
-    return self;
-  }
-  if (sx < 0) {
-    *inl = true;
-    return self;
-  }
-  *bb = false;
-  const int cx = sx >= g.nx ? g.nx - 1 : sx;  // the outlet ghost copies plane nx-1
-  return (sz * g.ny + sy) * g.rstride + cx;
+// Bits of the directions whose component in c is v.
+constexpr uint32_t dirs(const int (&c)[kQ], int v) {
+  uint32_t m = 0;
+  for (int i = 1; i < kQ; ++i)
+    if (c[i] == v) m |= 1u << i;
+  return m;
+}
+constexpr uint32_t kAllDirs = ((1u << kQ) - 1u) & ~1u;
+// The same set of directions, each replaced by its opposite.
+__device__ __forceinline__ uint32_t opposite(uint32_t m) {
+  constexpr uint32_t kOdd = 0x2aaaaaau & kAllDirs;
+  return ((m & kOdd) << 1) | ((m >> 1) & kOdd);
 }
 
 // Moving-wall term of the population pulled in direction i across a body link at node
@@ -263,47 +256,70 @@ __device__ __forceinline__ double body_wall_term3(const Geom3& g, int i, int x, 
 
 // Pull of all 27 populations of a fluid node through the boundary rules; *links: bit d
 // set for a body link in direction d.  MOV: the body links carry the moving-wall term.
+// The row (y, z) is the wave's, so walls and wrapped rows are scalar; what differs by lane
+// are the directions (bit masks) that read direction opp(i) of the node itself: bounce-back
+// (wall, body, outlet ghost of a solid node) and the inlet's moving-wall rule.
 template <int P, bool MOV>
 __device__ __forceinline__ void pull27(const Geom3& g, const typename St3<P>::T* __restrict__ src,
-                                       int x, int y, int z, uint32_t w, int32_t self,
+                                       int x, int y, int z, uint32_t w,
                                        typename St3<P>::C (&f)[kQ], uint32_t* links) {
   using C = typename St3<P>::C;
-  uint32_t inlm = 0, lk = 0;
-  f[0] = unpack3<P>(src[self], 0);
+  using T = typename St3<P>::T;
+  const bool px = g.bc_x == LBM_BCX_PERIODIC, py = g.bc_y == LBM_BCY_PERIODIC,
+             pz = g.bc_z == LBM_BCY_PERIODIC;
+  const uint32_t wall = (!py && y == 0 ? dirs(kCy, 1) : 0u) |
+                        (!py && y == g.ny - 1 ? dirs(kCy, -1) : 0u) |
+                        (!pz && z == 0 ? dirs(kCz, 1) : 0u) |
+                        (!pz && z == g.nz - 1 ? dirs(kCz, -1) : 0u);
+  const uint32_t left = !px && x == 0 ? dirs(kCx, 1) : 0u;
+  const uint32_t right = !px && x == g.nx - 1 ? dirs(kCx, -1) : 0u;
+  const uint32_t solid = w & kAllDirs & ~wall;
+  const uint32_t back = wall | solid | left;
+  const uint32_t inl = left & ~(wall | solid);
+  const uint32_t body = solid & ~(left | right);
+  // Columns and rows of the sources (the outlet ghost copies plane nx - 1; a row past a wall
+  // is not read).
+  const int xs[3] = {x + 1 < g.nx ? x + 1 : (px ? 0 : x), x, x > 0 ? x - 1 : (px ? g.nx - 1 : 0)};
+  const int ys[3] = {y + 1 < g.ny ? y + 1 : (py ? 0 : y), y, y > 0 ? y - 1 : (py ? g.ny - 1 : 0)};
+  const int zs[3] = {z + 1 < g.nz ? z + 1 : (pz ? 0 : z), z, z > 0 ? z - 1 : (pz ? g.nz - 1 : 0)};
+  const T* own = src + int64_t(z * g.ny + y) * g.rstride;
+  T v[kQ];
+  v[0] = own[x];
 #pragma unroll
   for (int i = 1; i < kQ; ++i) {
-    bool bb, inl, body;
-    const int32_t off = pull_offset(g, x, y, z, w, i, self, &bb, &inl, &body);
-    f[i] = unpack3<P>(src[int64_t(bb ? opp(i) : i) * g.dstride + off], i);  // w_opp(i) = w_i
-    if (inl) inlm |= 1u << i;
-    if (body) lk |= 1u << opp(i);
+    // Either source by a bit mask over the address (a choice of pointers compiles to a branch).
+    const T* from = src + int64_t(i) * g.dstride +
+                    int64_t(zs[kCz[i] + 1] * g.ny + ys[kCy[i] + 1]) * g.rstride;
+    const int64_t turn = own + int64_t(opp(i)) * g.dstride - from;
+    const int32_t m = int32_t(back << (31 - i)) >> 31;
+    const int xc = xs[kCx[i] + 1];
+    v[i] = from[(turn & int64_t(m)) + (xc + ((x - xc) & m))];
   }
-  if (MOV && lk) {
+#pragma unroll
+  for (int i = 0; i < kQ; ++i) f[i] = unpack3<P>(v[i], i);  // w_opp(i) = w_i
+  if (MOV && body) {
 #pragma unroll
     for (int i = 1; i < kQ; ++i)
-      if ((lk >> opp(i)) & 1u) f[i] += C(body_wall_term3(g, i, x, y, z));
+      if ((body >> i) & 1u) f[i] += C(body_wall_term3(g, i, x, y, z));
   }
-  if (inlm) {
+  if (inl) {
     const double u = g.rho_w6 * g.uin[z * g.ny + y];
 #pragma unroll
     for (int i = 1; i < kQ; ++i)
-      if (kCx[i] && ((inlm >> i) & 1u)) f[i] += C(u * (w27<double>(i) * kCx[i]));
+      if (kCx[i] && ((inl >> i) & 1u)) f[i] += C(u * (w27<double>(i) * kCx[i]));
   }
-  *links = lk;
+  *links = opposite(body);
 }
 
-// Sum N doubles over the wave (butterfly, fixed order); lanes 0..N-1 store them.
-template <int N>
-__device__ __forceinline__ void wave_store(double (&v)[N], double* out) {
-#pragma unroll
-  for (int k = 0; k < N; ++k)
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v[k] += __shfl_xor(v[k], off, 64);
-  const int lane = threadIdx.x & 63;
-  double mine = v[0];
-#pragma unroll
-  for (int k = 1; k < N; ++k) mine = lane == k ? v[k] : mine;
-  if (lane < N) out[lane] = mine;
+// Sums of four values over the wave (in the order of a butterfly over the lane distances 32,
+// 16, .., 1), component sum4_at() of them in each lane.
+__device__ __forceinline__ double sum4(double a, double b, double c, double d) {
+  using namespace lbm::dev;
+  return row_sum(fold16(fold32(a, b), fold32(c, d)));
+}
+__device__ __forceinline__ int sum4_at() {
+  const int row = (int(threadIdx.x) >> 4) & 3;
+  return (row & 1) << 1 | row >> 1;
 }
 
 // Sum N doubles over the block in a fixed order; thread k < N gets total k in out[k].
@@ -423,7 +439,7 @@ __device__ __forceinline__ void general_strip(const Step3Args& a, uint32_t e, in
   uint32_t lk = 0;
   bool inV = false;
   if (fluid) {
-    pull27<P, MOV>(g, src, x, y, z, w, int32_t(self), f, &lk);
+    pull27<P, MOV>(g, src, x, y, z, w, f, &lk);
     if (fterms) {
       inV = g.has_box && in_box(g, x, y, z);
       if (inV)
@@ -436,13 +452,12 @@ __device__ __forceinline__ void general_strip(const Step3Args& a, uint32_t e, in
         }
       if (lk) {
 #pragma unroll
-        for (int d = 1; d < kQ; ++d)
-          if ((lk >> d) & 1u) {
-            const double v = pre64<P>(f[d], d);
-            pre[0] += kCx[d] * v;
-            pre[1] += kCy[d] * v;
-            pre[2] += kCz[d] * v;
-          }
+        for (int d = 1; d < kQ; ++d) {
+          const double v = (lk >> d) & 1u ? pre64<P>(f[d], d) : 0.0;
+          if (kCx[d]) pre[0] += kCx[d] * v;
+          if (kCy[d]) pre[1] += kCy[d] * v;
+          if (kCz[d]) pre[2] += kCz[d] * v;
+        }
         // SI over the axis links of this node: (sigma - p I) . sum n, n = -c_d.
         if (lk & 0x7eu) {
           double rho = 0.0, jx = 0.0, jy = 0.0, jz = 0.0;
@@ -486,15 +501,12 @@ __device__ __forceinline__ void general_strip(const Step3Args& a, uint32_t e, in
       }
     }
   }
-  // Lane k of the wave keeps total k of the pre-collision terms.
-  double mine_pre = 0.0;
+  // Total 4 k + sum4_at() of the pre-collision terms.
+  double before[3] = {};
   if (fterms) {
-#pragma unroll
-    for (int k = 0; k < 9; ++k)
-#pragma unroll
-      for (int o = 32; o >= 1; o >>= 1) pre[k] += __shfl_xor(pre[k], o, 64);
-#pragma unroll
-    for (int k = 0; k < 9; ++k) mine_pre = lane == k ? pre[k] : mine_pre;
+    before[0] = sum4(pre[0], pre[1], pre[2], pre[3]);
+    before[1] = sum4(pre[4], pre[5], pre[6], pre[7]);
+    before[2] = sum4(pre[8], 0.0, 0.0, 0.0);
   }
   if (fluid) {
     collide27<C, S::kDev, COLL>(f, omega);
@@ -510,17 +522,24 @@ __device__ __forceinline__ void general_strip(const Step3Args& a, uint32_t e, in
         // The population returned along link d at t+1 is f~_d plus, for a moving body,
         // the moving-wall term of the pull of opp(d) (half-way point x + c_d / 2).
 #pragma unroll
-        for (int d = 1; d < kQ; ++d)
-          if ((lk >> d) & 1u) {
-            const double v = pre64<P>(f[d], d);
-            const double back = MOV ? v + body_wall_term3(g, opp(d), x, y, z) : v;
+        for (int d = 1; d < kQ; ++d) {
+          const bool on = (lk >> d) & 1u;
+          const double v = on ? pre64<P>(f[d], d) : 0.0;
+          double back = v;
+          if (MOV) back = on ? v + body_wall_term3(g, opp(d), x, y, z) : 0.0;
+          if (kCx[d]) {
             post[0] += kCx[d] * back;
-            post[1] += kCy[d] * back;
-            post[2] += kCz[d] * back;
             post[3] += kCx[d] * (v + back);
+          }
+          if (kCy[d]) {
+            post[1] += kCy[d] * back;
             post[4] += kCy[d] * (v + back);
+          }
+          if (kCz[d]) {
+            post[2] += kCz[d] * back;
             post[5] += kCz[d] * (v + back);
           }
+        }
       }
       if (g.has_box) {
         // Surface flux: populations leaving V (node inside) or entering it (outside).
@@ -529,51 +548,69 @@ __device__ __forceinline__ void general_strip(const Step3Args& a, uint32_t e, in
         if (!g.whole[1]) near = near && y >= g.box[2] - 1 && y <= g.box[3];
         if (!g.whole[2]) near = near && z >= g.box[4] - 1 && z <= g.box[5];
         if (near) {
+          // Whether the neighbours' columns and rows lie in V.
+          bool ix[3], iy[3], iz[3];
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            const int tx = x + c - 1, ty = y + c - 1, tz = z + c - 1;
+            ix[c] = in_range(g, 0, g.bc_x == LBM_BCX_PERIODIC ? wrapc(tx, g.nx) : tx);
+            iy[c] = in_range(g, 1, g.bc_y == LBM_BCY_PERIODIC ? wrapc(ty, g.ny) : ty);
+            iz[c] = in_range(g, 2, g.bc_z == LBM_BCY_PERIODIC ? wrapc(tz, g.nz) : tz);
+          }
+          const double out = inV ? -1.0 : 1.0;
 #pragma unroll
           for (int d = 1; d < kQ; ++d) {
-            int tx2 = x + kCx[d], ty2 = y + kCy[d], tz2 = z + kCz[d];
-            if (g.bc_x == LBM_BCX_PERIODIC) tx2 = wrapc(tx2, g.nx);
-            if (g.bc_y == LBM_BCY_PERIODIC) ty2 = wrapc(ty2, g.ny);
-            if (g.bc_z == LBM_BCY_PERIODIC) tz2 = wrapc(tz2, g.nz);
-            if (in_box(g, tx2, ty2, tz2) != inV) {
-              const double v = (pre64<P>(f[d], d)) *
-                               (inV ? -1.0 : 1.0);
-              post[6] += kCx[d] * v;
-              post[7] += kCy[d] * v;
-              post[8] += kCz[d] * v;
-            }
+            const bool in = ix[kCx[d] + 1] && (iy[kCy[d] + 1] && iz[kCz[d] + 1]);
+            const double v = in != inV ? pre64<P>(f[d], d) * out : 0.0;
+            if (kCx[d]) post[6] += kCx[d] * v;
+            if (kCy[d]) post[7] += kCy[d] * v;
+            if (kCz[d]) post[8] += kCz[d] * v;
           }
         }
       }
     }
   }
   if (fterms) {
-#pragma unroll
-    for (int k = 0; k < 9; ++k)
-#pragma unroll
-      for (int o = 32; o >= 1; o >>= 1) post[k] += __shfl_xor(post[k], o, 64);
-    double mine_post = 0.0;
-#pragma unroll
-    for (int k = 0; k < 9; ++k) mine_post = lane == k ? post[k] : mine_post;
-    // Slot layout FA(3) FB(3) J(3) Phi(3) SI(3): lanes 0-2 A = pre + post, 3-5 B,
-    // 6-8 J, 9-11 Phi, 12-14 SI.
-    const double apre = __shfl(mine_pre, lane % 3, 64);       // A lost (lanes 0-2)
-    const double jv = __shfl(mine_pre, 3 + lane % 3, 64);     // J
-    const double si = __shfl(mine_pre, 6 + lane % 3, 64);     // SI
-    const double apost = __shfl(mine_post, lane % 3, 64);     // A returned
-    const double bv = __shfl(mine_post, 3 + lane % 3, 64);    // B
-    const double ph = __shfl(mine_post, 6 + lane % 3, 64);    // Phi
-    double v = 0.0;
-    if (lane < 3) v = apre + apost;
-    else if (lane < 6) v = bv;
-    else if (lane < 9) v = jv;
-    else if (lane < 12) v = ph;
-    else v = si;
-    if (lane < kPart) a.part_out[int64_t(strip_slot(e)) * kPart + lane] = v;
+    const double after[3] = {sum4(post[0], post[1], post[2], post[3]),
+                             sum4(post[4], post[5], post[6], post[7]),
+                             sum4(post[8], 0.0, 0.0, 0.0)};
+    // Slot layout FA(3) FB(3) J(3) Phi(3) SI(3).  Columns 0-2 of each row of 16 lanes take the
+    // terms before the collision (with A = lost + returned), columns 3-5 those after it.
+    const int col = lane & 15, c = sum4_at();
+    const bool first = col < 3;
+    const int part = first ? col : col - 3, k = 4 * part + c;
+    double v = first ? (part == 0 ? before[0] : (part == 1 ? before[1] : before[2]))
+                     : (part == 0 ? after[0] : (part == 1 ? after[1] : after[2]));
+    if (col == 0 && c < 3) v = before[0] + after[0];
+    const int at = first ? (k < 3 ? k : (k < 6 ? k + 3 : k + 6)) : (k < 6 ? k : k + 3);
+    if (col < 6 && k < 9 && (first || k >= 3))
+      a.part_out[int64_t(strip_slot(e)) * kPart + at] = v;
   }
 }
 
-template <int P, bool FORCES, int COLL, bool MOV>
+// Strip of a force slot (one wave per slot, in slot order): the general path with A, B, J, Phi
+// and SI.
+template <int P, int COLL, bool MOV>
+__device__ __forceinline__ void force_strip(const Step3Args& a, int64_t slot, int lane) {
+  if (slot >= a.nslots) return;
+  const uint32_t si = a.fstrips[slot];
+  const int64_t tile = si / kStrips, row = tile / a.ntx;
+  const int x = int(tile % a.ntx) * kTileW + int(si % kStrips) * kStripW + lane;
+  general_strip<P, true, COLL, MOV>(a, a.strip[si], row, x, int(row % a.g.ny), int(row / a.g.ny),
+                                    lane);
+}
+
+template <int P, int COLL, bool MOV>
+__global__ __launch_bounds__(kThreads) void force3_kernel(Step3Args a) {
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+  force_strip<P, COLL, MOV>(a, int64_t(blockIdx.x) * kStrips + wave, threadIdx.x & 63);
+}
+
+// Where the strips with force terms run: nowhere apart (no forces), in a launch of their own,
+// or in the step's, which gives it their registers (140 against 46 - 80).
+enum Forces3 { kNoForces, kApart, kJoined };
+
+template <int P, int FORCES, int COLL, bool MOV>
 __global__ __launch_bounds__(kThreads) void step3_kernel(Step3Args a) {
   using S = St3<P>;
   using T = typename S::T;
@@ -587,9 +624,17 @@ __global__ __launch_bounds__(kThreads) void step3_kernel(Step3Args a) {
     if (b < 8) return;
     b -= 8;
   }
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6), lane = threadIdx.x & 63;
+  if (FORCES == kJoined) {
+    // Then the strips with force terms, which take longest.
+    if (b < a.force_blocks) {
+      force_strip<P, COLL, MOV>(a, b * kStrips + wave, lane);
+      return;
+    }
+    b -= a.force_blocks;
+  }
   const int64_t tile = tile_of(b);
   if (tile >= a.ntiles) return;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const uint32_t e = a.strip[tile * kStrips + wave];
   if (e == kStripEmpty) return;
   const Geom3& g = a.g;
@@ -635,7 +680,10 @@ __global__ __launch_bounds__(kThreads) void step3_kernel(Step3Args a) {
           if (kCz[i]) j[2] += kCz[i] * v;
         }
       }
-      wave_store<3>(j, a.part_out + int64_t(a.nslots) * kPart + int64_t(strip_slot(e)) * 3);
+      const double v = sum4(j[0], j[1], j[2], 0.0);
+      const int k = sum4_at();
+      if ((lane & 15) == 0 && k < 3)
+        a.part_out[int64_t(a.nslots) * kPart + int64_t(strip_slot(e)) * 3 + k] = v;
     }
     collide27<C, S::kDev, COLL>(f, omega);
     const uint32_t word = S::kSR ? sr_word3(a.step_key, row * g.nx + x) : 0u;
@@ -643,27 +691,10 @@ __global__ __launch_bounds__(kThreads) void step3_kernel(Step3Args a) {
     for (int i = 0; i < kQ; ++i) st_nt(dst + int64_t(i) * g.dstride + self, pack3_sr<P>(f[i], i, word));
     return;
   }
-  // Strips with force terms run in force3_kernel when forces are evaluated; they hold
-  // every body link, so the edge strips left here need no moving-wall term then.
+  // With forces, the strips with force terms have blocks of their own; they hold every body
+  // link, so the edge strips left here need no moving-wall term then.
   if (FORCES && cls == kForce) return;
   general_strip<P, false, COLL, FORCES ? false : MOV>(a, e, row, x, y, z, lane);
-}
-
-// The strips with force terms (one wave per slot, in slot order): the general path
-// with A, B, J, Phi and SI.
-template <int P, int COLL, bool MOV>
-__global__ __launch_bounds__(kThreads) void force3_kernel(Step3Args a) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t slot = int64_t(blockIdx.x) * kStrips + wave;
-  if (slot >= a.nslots) return;
-  const uint32_t si = a.fstrips[slot];
-  const uint32_t e = a.strip[si];
-  const int64_t tile = si / kStrips;
-  const int tx = int(tile % a.ntx);
-  const int64_t row = tile / a.ntx;
-  const int y = int(row % a.g.ny), z = int(row / a.g.ny);
-  const int x = tx * kTileW + int(si % kStrips) * kStripW + lane;
-  general_strip<P, true, COLL, MOV>(a, e, row, x, y, z, lane);
 }
 
 // J of the pull of the state src over V, per block of 256 nodes along x in a box row.
@@ -687,8 +718,7 @@ __global__ __launch_bounds__(kThreads) void box3_kernel(Box3Args a) {
     if (!(w & kSolid)) {
       C f[kQ];
       uint32_t lk;
-      pull27<P, MOV>(g, static_cast<const T*>(a.src), x, y, z, w, int32_t(row * g.rstride + x), f,
-                     &lk);
+      pull27<P, MOV>(g, static_cast<const T*>(a.src), x, y, z, w, f, &lk);
 #pragma unroll
       for (int i = 1; i < kQ; ++i) {
         const double v = pre64<P>(f[i], i);
@@ -800,20 +830,40 @@ __global__ __launch_bounds__(kThreads) void fill_rest3_kernel(void* buf, int64_t
   }
 }
 
+// Whether the strips with force terms join the step's launch.  That saves a launch and hides
+// them behind the other strips, but leaves those three waves a SIMD instead of six or seven,
+// too few to keep HBM busy with binary16 loads or behind the stochastic rounding.  Measured on
+// grids with a sphere, joined against apart, in us a step: binary32 64 x 32 x 32 11.0 : 18.3,
+// 200 x 100 x 100 93 : 98, 1280 x 128 x 64 389 : 405; binary64 12 : 20, 157 : 167, 790 : 812;
+// stochastically rounded 128 x 65 x 64 35.8 : 36.4, 200 x 100 x 100 108 : 101; binary16
+// 96 x 48 x 48 17.2 : 22.1, 128 x 65 x 64 28.6 : 27.2, 1280 x 128 x 64 270 : 205.
+bool join3(int precision, int64_t nodes) {
+  switch (precision) {
+    case LBM_FP32SR: return nodes <= 1000000;
+    case LBM_FP16DEV: return nodes <= 400000;
+    default: return true;
+  }
+}
+
 template <int P, int COLL, bool MOV>
-hipError_t step_pcm(bool forces, const Step3Args& a, hipStream_t s) {
+hipError_t step_pcm(bool forces, Step3Args a, hipStream_t s) {
   const int64_t tiles = (a.ntiles + 8 * kXcdRun - 1) / (8 * kXcdRun) * (8 * kXcdRun);
-  const dim3 grid(unsigned(tiles + (a.red_in ? 8 : 0)));
-  if (forces) {
-    hipLaunchKernelGGL((step3_kernel<P, true, COLL, MOV>), grid, dim3(kThreads), 0, s, a);
+  // Whole rounds over the XCDs, so that the tile blocks keep their alignment.
+  const int force_blocks = (a.nslots + kStrips * 8 - 1) / (kStrips * 8) * 8;
+  const bool joined = forces && join3(P, int64_t(a.g.nx) * a.g.ny * a.g.nz);
+  a.force_blocks = joined ? force_blocks : 0;
+  const dim3 grid(unsigned(tiles + a.force_blocks + (a.red_in ? 8 : 0)));
+  if (joined) {
+    hipLaunchKernelGGL((step3_kernel<P, kJoined, COLL, MOV>), grid, dim3(kThreads), 0, s, a);
+  } else if (forces) {
+    hipLaunchKernelGGL((step3_kernel<P, kApart, COLL, MOV>), grid, dim3(kThreads), 0, s, a);
     if (a.nslots > 0) {
-      hipError_t e = hipGetLastError();
+      const hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
-      const unsigned fblocks = unsigned((a.nslots + kStrips - 1) / kStrips);
-      hipLaunchKernelGGL((force3_kernel<P, COLL, MOV>), dim3(fblocks), dim3(kThreads), 0, s, a);
+      hipLaunchKernelGGL((force3_kernel<P, COLL, MOV>), dim3(force_blocks), dim3(kThreads), 0, s, a);
     }
   } else {
-    hipLaunchKernelGGL((step3_kernel<P, false, COLL, MOV>), grid, dim3(kThreads), 0, s, a);
+    hipLaunchKernelGGL((step3_kernel<P, kNoForces, COLL, MOV>), grid, dim3(kThreads), 0, s, a);
   }
   return hipGetLastError();
 }

@@ -324,3 +324,35 @@ def test_checkpoint_reset_and_parameter_changes_3d():
     d.step(20)
     assert np.array_equal(b.populations(), d.populations())
     assert np.array_equal(b.forces(), d.forces())
+
+
+@pytest.mark.parametrize("precision,shape", [("fp32sr", (200, 71, 70)), ("fp32sr", (201, 72, 70)),
+                                             ("fp16dev", (130, 55, 55)), ("fp16dev", (130, 56, 56)),
+                                             ("fp32", (130, 56, 56)), ("fp64", (201, 72, 70))])
+def test_force_strips_joined_and_apart(precision, shape):
+    """Grids on both sides of the sizes where the strips with force terms leave the step's
+    launch (1e6 nodes stochastically rounded, 4e5 in binary16), and others that never do:
+    two steps of a random state with forces against the oracle, populations bitwise those of
+    steps without forces.  Tolerances as for the large airfoil above; binary16 5e-2 (its
+    rounding of 5e-4 of a deviation, over the box of about 1e4 nodes against a force of random
+    terms over about 1e3 links)."""
+    nx, ny, nz = shape
+    mask = d3.sphere_mask(nx, ny, nz, 0.3 * nx, ny / 2, nz / 2, 6.3)
+    c = (int(0.3 * nx), ny // 2, nz // 2)
+    box = tuple(v for m in c for v in (m - 10, m + 11))
+    S0 = d3.near_rest_state3(nx, ny, nz, seed=7, amp=0.02,
+                             dtype=np.float64 if precision == "fp64" else np.float32)
+    sims = [_sim3(mask, 0.56, 0.04, precision=precision, box=box, max_record=4) for _ in range(2)]
+    for g, schemes in zip(sims, (None, ())):
+        g.set_populations(S0)
+        g.step(2, **({} if schemes is None else {"schemes": schemes}))
+    Fg = sims[0].forces()
+    np.testing.assert_array_equal(sims[0].populations(), sims[1].populations())
+    o = D.OracleSim3(mask, tau=0.56, uin=np.full((nz, ny), 0.04), box=box)
+    o.set_state(S0)
+    o.step(2)
+    e = _force_err(Fg, o.forces())
+    print(precision, shape, "force errors", e)
+    tol = {"fp64": np.full(4, TOL64), "fp16dev": np.full(4, 5e-2)}.get(
+        precision, np.array([2e-4, 2e-4, 1e-2, 1e-3]))
+    assert np.all(e <= tol), e
