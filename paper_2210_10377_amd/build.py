@@ -15,7 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblbm.so")
-SOURCES = ["api.hip", "batch.hip", "kernels.hip", "fused.hip", "adjoint.hip", "plan.cpp", "api3.hip",
+SOURCES = ["api.hip", "batch.hip", "kernels.hip", "fused.hip", "tiles.hip", "adjoint.hip", "plan.cpp", "api3.hip",
            "kernels3.hip", "plan3.cpp", "noalloc.hip"]
 ARCH = os.environ.get("LBM_OFFLOAD_ARCH", "gfx950")
 ROCM_LIB = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "lib")

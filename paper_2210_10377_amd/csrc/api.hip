@@ -334,9 +334,11 @@ namespace {
 
 // Work map of fused launches for n steps between two alternating buffers, or one without blocks
 // where single steps are the faster or the only form.
-FuseMap fuse_for(const lbm_t* h, const DevTables& t, int32_t n) {
+FuseMap fuse_for(const lbm_t* h, const DevTables& t, int32_t n, bool forces) {
   const FuseMap none{};
   if (n < kFuse || !t.fuse || h->buf_bytes32() == 0) return none;
+  const int rows = tile_rows(h->g.precision, h->g.collision, forces, h->g.nx, h->g.ny);
+  if (rows > 0) return tile_map(h->plan, rows);
   const FuseMap m = fuse_map(h->plan, int(h->esz), int64_t(h->g.nx) * h->g.ny);
   const FuseRect& r = m.r[0];
   const double nodes = double(h->g.nx) * h->g.ny;
@@ -356,7 +358,7 @@ int enqueue_steps(lbm_t* h, const DevTables& t, hipStream_t stream, int32_t n, d
   const bool forces = ring != nullptr;
   StepArgs a = step_args(h, t);
   FuseArgs q{};
-  q.map = alternate ? fuse_for(h, t, n) : FuseMap{};
+  q.map = alternate ? fuse_for(h, t, n, forces) : FuseMap{};
   q.step.part_stride = t.part_stride;
   const void* last = nullptr;
   // Single steps first, then the fused launches: a launch reduces the rows of the one before
@@ -391,7 +393,8 @@ int enqueue_steps(lbm_t* h, const DevTables& t, hipStream_t stream, int32_t n, d
         q.red_row = ring + int64_t(k - in_last) * kRow;
         q.red_has_prev = k - in_last >= 1;
       }
-      e = launch_fused(h->g.precision, forces, a, q, stream);
+      e = q.map.tile_rows ? launch_tiles(h->g.precision, forces, a, q, stream)
+                          : launch_fused(h->g.precision, forces, a, q, stream);
       in_last = kFuse;
     }
     if (e != hipSuccess) return h->hip_fail(e, "launch step");

@@ -1,11 +1,42 @@
-// Device building blocks of the per-step forces, shared by the step kernels: the force
-// terms of one node under each estimator, and the fixed-order reduction of a step's partials.
+// Device building blocks shared by the step kernels: collision and rounding of a node, the
+// force terms of one node under each estimator, and the fixed-order reduction of a step's
+// partials.
 #pragma once
 
 #include "device.h"
 
 namespace lbm {
 namespace dev {
+
+// Collision of arithmetic values f; s: the values to store.
+template <int P, int COLL>
+__device__ __forceinline__ void collide_pack(const StepArgs& a,
+                                             const typename Storage<P>::C (&f)[kQ], uint32_t key,
+                                             int x, int y, typename Storage<P>::T (&s)[kQ]) {
+  using S = Storage<P>;
+  using C = typename S::C;
+  C g[kQ];
+  collide<C, S::kDev, COLL, S::kExactW, sizeof(typename S::T) == 2>(f, C(a.omega), g);
+  const uint32_t word = S::kSR ? sr_node_word(key, a.nx, x, y) : 0u;
+#pragma unroll
+  for (int i = 0; i < kQ; ++i) s[i] = pack_sr<P>(g[i], i, word);
+}
+
+// Force slot of the strip of row y that starts at column x0 (negative: none).
+__device__ __forceinline__ int slot_of(const StepArgs& a, int x0, int y) {
+  const int at = a.tile_rows == 1
+                     ? y * (a.ntx * kStrips) + x0 / kStripW
+                     : ((y >> 2) * a.ntx + x0 / kStripW) * kStrips + (y & 3);
+  return a.strip_slot[at];
+}
+
+// Barrier of the block that orders LDS accesses only: loads and stores of global memory that
+// are under way are not waited for (no wave reads what another one of the launch stores).
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
 
 // acc += c v for a lattice velocity component c.
 __device__ __forceinline__ void add_signed(int c, double v, double& acc) {

@@ -109,20 +109,6 @@ __device__ __forceinline__ void pull_coded(const Rows<T>& R, const T (&next)[kQ]
   }
 }
 
-// Collision of arithmetic values f; s: the values to store.
-template <int P, int COLL>
-__device__ __forceinline__ void collide_pack(const StepArgs& a,
-                                             const typename Storage<P>::C (&f)[kQ], uint32_t key,
-                                             int x, int y, typename Storage<P>::T (&s)[kQ]) {
-  using S = Storage<P>;
-  using C = typename S::C;
-  C g[kQ];
-  collide<C, S::kDev, COLL, S::kExactW, sizeof(typename S::T) == 2>(f, C(a.omega), g);
-  const uint32_t word = S::kSR ? sr_node_word(key, a.nx, x, y) : 0u;
-#pragma unroll
-  for (int i = 0; i < kQ; ++i) s[i] = pack_sr<P>(g[i], i, word);
-}
-
 // What a lane of a plain window keeps of a stored population: the value itself, or for
 // binary16 its binary32 equal, which the next step needs.
 template <int P>
@@ -308,21 +294,6 @@ __device__ __forceinline__ void march_plain(const StepArgs& a, const FuseStep& q
 struct Pair {
   int x0, ya, yb;  // strip's first column, rows [ya, yb) (empty for an idle pair)
 };
-
-__device__ __forceinline__ int slot_of(const StepArgs& a, int x0, int y) {
-  const int at = a.tile_rows == 1
-                     ? y * (a.ntx * kStrips) + x0 / kStripW
-                     : ((y >> 2) * a.ntx + x0 / kStripW) * kStrips + (y & 3);
-  return a.strip_slot[at];
-}
-
-// Barrier of the block that orders LDS accesses only: loads and stores of global memory that
-// are under way are not waited for (no wave reads what another one of the launch stores).
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
 
 // Force exchange of the two halves of a strip (turn, pair, sending half, component, lane): each
 // half sends the other one half of its components.

@@ -201,6 +201,9 @@ hipError_t launch_step(int precision, bool forces, const StepArgs& a, hipStream_
 // kFuse steps in one launch (state buffers below 4 GiB).
 hipError_t launch_fused(int precision, bool forces, const StepArgs& a, const FuseArgs& q,
                         hipStream_t s);
+// The same with a work map of tiles.
+hipError_t launch_tiles(int precision, bool forces, const StepArgs& a, const FuseArgs& q,
+                        hipStream_t s);
 // C_p = (rho/3 - p_inf) / q at every listed node, rho the sum of the node's stored
 // populations in binary64, p_inf = rho/3 of the reference node (or p_ref).
 hipError_t launch_boundary_cp(int precision, const CpArgs& a, hipStream_t s);

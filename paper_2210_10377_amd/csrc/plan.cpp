@@ -369,6 +369,38 @@ bool fuse_pays(int precision, int collision, double nodes, double body) {
   }
 }
 
+int tile_rows(int precision, int collision, bool forces, int nx, int ny) {
+  // Small lattices are bound by latency: a launch of one step takes 3.4 us, with forces 5.2 as
+  // each strip of the body sums 12 components, however few nodes there are.  Three steps of a
+  // tile take 6 and 10.  Beyond one block a CU the margins (12 rows of work for 8) cost more than
+  // the launches.  Measured in us a step with all forces (without), single steps : tiles of 4
+  // rows : of 8 : windows: binary64 200 x 80 5.2 : 3.4 : 4.0 : 9.3 (3.6 : 2.8 : 3.4 : 5.1), 512 x 256
+  // 6.3 : 4.9 : 4.1 : 8.7 (5.1 : 3.8 : 3.0 : 5.6), 724 x 362 9.7 : 8.8 : 7.5 : 9.6 (9.2 : 8.5 : 7.2 :
+  // 5.8), 1024 x 512 15.7 : 14.5 : 11.4 : 12.4 (15 : 12.6 : 9.5 : 9.6); binary32 512 x 256 5.7 : 4.5 :
+  // 3.9 : 9.0 (3.9 : 2.8 : 2.7 : 5.2), 724 x 362 6.7 : 7.4 : 6.0 : 8.8 (5.4 : 5.0 : 5.3 : 5.7),
+  // 1024 x 512 10.2 : 12.6 : 9.4 : 9.1 (8.1 : 7.9 : 6.8 : 6.3); stochastically rounded, binary16 and
+  // entropic 512 x 256 6.0 : 4.6, 5.6 : 4.1 and 5.7 : 4.4, 724 x 362 6.8 : 7.8, 5.9 : 5.8 and 6.5 : 7.0
+  // (single : 8 rows).  The regularized collision is left to single steps: its compiled form
+  // rounds differently here.
+  if (collision == LBM_COLL_REGULARIZED) return 0;
+  const double nodes = double(nx) * ny;
+  double most = 2e5;
+  if (collision == LBM_COLL_BGK) {
+    if (precision == LBM_FP64) most = forces ? 5.5e5 : 2e5;
+    if (precision == LBM_FP32 || precision == LBM_FP32DEV) most = forces ? 3.5e5 : 2.7e5;
+  }
+  if (nodes > most) return 0;
+  const int strips = (nx + kStripW - 1) / kStripW;
+  return strips * ((ny + 3) / 4) <= 256 ? 4 : 8;
+}
+
+FuseMap tile_map(const Plan& p, int rows) {
+  FuseMap m{};
+  m.tile_rows = rows;
+  m.nblocks = (p.nx + kStripW - 1) / kStripW * ((p.ny + rows - 1) / rows);
+  return m;
+}
+
 FuseMap fuse_map(const Plan& p, int elem_bytes, int64_t nodes) {
   constexpr int kM = kFuseM;
   // Rows of a unit: in the plain rectangles few enough to give every SIMD three waves, many

@@ -169,6 +169,7 @@ struct FuseRect {
 constexpr int kFuseRects = 24;
 struct FuseMap {
   int32_t nrects, nblocks;
+  int32_t tile_rows;  // rows of a block where each takes one strip's columns, else 0
   FuseRect r[kFuseRects];
 };
 
@@ -209,6 +210,11 @@ void tile_slots(const Plan& p, int rows, int& ntx, int& nty, std::vector<int32_t
 // The fused kernel's work map of p for elements of elem_bytes, in a launch of `nodes` nodes in
 // all (p's own, or those of a batch).
 FuseMap fuse_map(const Plan& p, int elem_bytes, int64_t nodes);
+
+// The same for small lattices: one block for every `rows` rows of a strip's columns.
+FuseMap tile_map(const Plan& p, int rows);
+// Rows of its tiles where they are the fastest form for an nx x ny lattice, else 0.
+int tile_rows(int precision, int collision, bool forces, int nx, int ny);
 
 // Whether fused launches are faster than single steps for `nodes` nodes, the share `body` of
 // them in the body rectangles (of one lattice, or of a batch's lattices together).

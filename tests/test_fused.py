@@ -195,3 +195,53 @@ def test_fused_launches_bitwise_equal_single_steps(name, precision, bc_x, bc_y, 
         # below N 2^-53 0.45 in any order, and a row holds two of them.
         N = (box[1] - box[0]) * (box[3] - box[2]) * 9
         assert np.abs(F0 - F1).max() <= 4 * N * 0.45 * 2.0 ** -53
+
+
+# Tiles: columns and rows around the sizes of a tile (64, 4 and 8 rows), 380 blocks of 4 rows.
+TILE_SIZES = [(5, 3), (63, 4), (65, 9), (130, 17), (200, 80), (600, 150)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision,bc_x,bc_y,collision,spin", [
+    ("fp64", 0, 0, "bgk", 0), ("fp64", 1, 1, "kbc", 0), ("fp32", 0, 1, "kbc", 1),
+    ("fp32", 1, 0, "bgk", 0), ("fp32dev", 0, 0, "bgk", 1), ("fp32sr", 0, 0, "bgk", 0),
+    ("fp32sr", 1, 0, "kbc", 0), ("fp16dev", 0, 1, "bgk", 1), ("fp16dev", 0, 0, "kbc", 0),
+    ("fp32dev", 1, 1, "kbc", 0)])
+def test_tiles_bitwise_equal_single_steps(precision, bc_x, bc_y, collision, spin):
+    """Calls of 7 steps (a single step and two launches of three) against calls of one and two
+    steps: bitwise, the forces included, as every strip sums in the same order; except DRTT,
+    whose J of the step after a call comes from a sweep over the box in another order (bound as
+    above)."""
+    from paper_2210_10377_amd import Sim
+    rng = np.random.default_rng(6)
+    for nx, ny in TILE_SIZES:
+        mask = np.zeros((ny, nx), np.uint8)
+        box = None
+        if nx >= 65:
+            mask[ny // 2 - 1:ny // 2 + 2, nx // 2:nx // 2 + 5] = 1
+            box = (nx // 2 - 3, nx // 2 + 9, ny // 2 - 3, ny // 2 + 4)
+            if nx >= 200:
+                box = (nx // 5, nx - 5, 2, ny - 2)  # strips wholly inside it
+        else:
+            mask[1, 2] = 1
+        uin = 0.05 * (1 + 0.1 * rng.uniform(-1, 1, ny))
+        S = workloads.NEAR_REST_BASE[:, None, None] * (
+            1 + 0.02 * rng.uniform(-1, 1, (9, ny, 1)) * rng.uniform(-1, 1, (9, 1, nx)))
+        runs = []
+        for calls in ([7], [2, 2, 2, 1]):
+            print(f"tiles {nx}x{ny} {precision} bc {bc_x}{bc_y} {collision} {calls}", flush=True)
+            sim = Sim(mask, 0.7, uin, precision=precision, bc_x=bc_x, bc_y=bc_y, box=box,
+                      max_record=7, collision=collision)
+            sim.set_populations(S)
+            if spin:
+                sim.set_body_motion(ux=0.01, omega=1e-4, xc=nx / 3, yc=ny / 2)
+            for k in calls:
+                sim.step(k)
+            runs.append((sim.populations(), sim.forces()))
+            del sim
+        (P0, F0), (P1, F1) = runs
+        np.testing.assert_array_equal(P0, P1)
+        np.testing.assert_array_equal(F0[:, [0, 1, 3]], F1[:, [0, 1, 3]])
+        if box is not None:
+            N = (box[1] - box[0]) * (box[3] - box[2]) * 9
+            assert np.abs(F0 - F1).max() <= 4 * N * 0.45 * 2.0 ** -53
