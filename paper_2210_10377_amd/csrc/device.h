@@ -572,18 +572,22 @@ __device__ __forceinline__ void wave_sum_store(const double (&v)[N], double* out
   if (col < N / 4) out[at] = t;
 }
 
-// Fixed-order reduction of [nslots][N] partials by one 256-thread block; returns the N
-// sums in threads 0..N-1.  The first G*N threads (G = 256 / N groups) read element
-// j*N + k (k = thread % N) of every G-th slot, so each keeps one component.
+// Fixed-order reduction of [nslots][N] partials by one block, in two parts with a barrier
+// between them: G = 256 / N groups of threads first read element j * N + k (k = thread % N) of
+// every G-th slot, so each keeps one component, and leave their sums in red; then thread k < N
+// adds those of component k.  What costs is latency, mostly of the loads (partials come from
+// other XCDs): eight are in flight, the last ones too, and the sums in red are all read before
+// they are added.  A 200 x 80 lattice with 80 slots took 6 us to reduce while the last loads
+// went one by one, which was the time of the whole launch.
 template <int N>
-__device__ __forceinline__ double reduce_partials(const double* in, int nslots) {
-  constexpr int kG = kThreads / N;  // slot groups
-  __shared__ double red[kG][N];
-  const int k = threadIdx.x % N, grp = threadIdx.x / N;
-  if (grp < kG) {
-    // Eight independent partial sums per lane keep eight loads in flight (this block
-    // runs beside the step's tiles and must finish with them); they are combined in a
-    // fixed order, so the result depends on nslots only.
+struct Partials {
+  static constexpr int kG = kThreads / N;  // slot groups
+  double red[kG][N];
+  __device__ __forceinline__ void gather(const double* in, int nslots) {
+    const int k = threadIdx.x % N, grp = threadIdx.x / N;
+    if (grp >= kG) return;
+    // Eight independent partial sums per lane, combined in a fixed order, so the result depends
+    // on nslots only; the rounds that are not full add to the first one.
     constexpr int kU = 8;
     double acc[kU];
 #pragma unroll
@@ -593,15 +597,23 @@ __device__ __forceinline__ double reduce_partials(const double* in, int nslots) 
 #pragma unroll
       for (int u = 0; u < kU; ++u) acc[u] += in[int64_t(j + u * kG) * N + k];
     }
-    for (; j < nslots; j += kG) acc[0] += in[int64_t(j) * N + k];
+    double v[kU - 1];
+#pragma unroll
+    for (int u = 0; u < kU - 1; ++u)
+      v[u] = j + u * kG < nslots ? in[int64_t(j + u * kG) * N + k] : 0.0;
+#pragma unroll
+    for (int u = 0; u < kU - 1; ++u) acc[0] += v[u];
     red[grp][k] = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
   }
-  __syncthreads();
-  double t = 0.0;
-  if (threadIdx.x < N)
-    for (int gI = 0; gI < kG; ++gI) t += red[gI][threadIdx.x];
-  return t;
-}
+  __device__ __forceinline__ double sum(int k) const {
+    double v[kG], t = 0.0;
+#pragma unroll
+    for (int g = 0; g < kG; ++g) v[g] = red[g][k];
+#pragma unroll
+    for (int g = 0; g < kG; ++g) t += v[g];
+    return t;
+  }
+};
 
 }  // namespace dev
 }  // namespace lbm

@@ -156,17 +156,25 @@ __device__ __forceinline__ void stress_terms(const StepArgs& a, uint32_t w,
 // Force row of the previous step from its partial slots (fixed order).
 __device__ __forceinline__ void reduce_row(const double* red_in, int nslots, int njslots,
                                            double* row, double* prev_jnext) {
-  // General strips, then the box momenta of the box-interior strips (J before and after
-  // collision, added to the two J sums).
-  double t = reduce_partials<kPart>(red_in, nslots);
-  const double tj = reduce_partials<kBoxPart>(red_in + int64_t(nslots) * kPart, njslots);
+  // General strips, and the box momenta of the box-interior strips (J before and after
+  // collision, added to the two J sums; two waves share the last sums).
+  __shared__ Partials<kPart> general;
+  __shared__ Partials<kBoxPart> interior;
+  __shared__ double ji[kBoxPart];
+  general.gather(red_in, nslots);
+  if (njslots > 0) interior.gather(red_in + int64_t(nslots) * kPart, njslots);
+  __syncthreads();
   const int tid = int(threadIdx.x);
-  const bool pre = tid == 4 || tid == 5, post = tid == kJpost || tid == kJpost + 1;
-  const double tjs = __shfl(tj, pre ? tid - 4 : (post ? tid - kJpost + 2 : 0), 64);
-  if (pre || post) t += tjs;
-  if (threadIdx.x < kPart) {
-    row[threadIdx.x] = t;
-    if (prev_jnext && (threadIdx.x == 4 || threadIdx.x == 5)) prev_jnext[threadIdx.x - 4] = t;
+  double t = 0.0;
+  if (tid < kPart) t = general.sum(tid);
+  if (tid >= 64 && tid < 64 + kBoxPart) ji[tid - 64] = njslots > 0 ? interior.sum(tid - 64) : 0.0;
+  __syncthreads();
+  if (tid < kPart) {
+    const bool pre = tid == 4 || tid == 5, post = tid == kJpost || tid == kJpost + 1;
+    if (pre) t += ji[tid - 4];
+    if (post) t += ji[tid - kJpost + 2];
+    row[tid] = t;
+    if (prev_jnext && pre) prev_jnext[tid - 4] = t;
   }
 }
 

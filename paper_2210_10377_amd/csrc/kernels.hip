@@ -388,8 +388,16 @@ __device__ __forceinline__ void finalize_body(const FinalArgs& a, int r) {
     red[threadIdx.x][1] = jy;
     __syncthreads();
     if (threadIdx.x < 2) {
+      // (Read 32 at a time, added one by one; those past njblocks are zero.)
       double s = 0.0;
-      for (int k = 0; k < kThreads; ++k) s += red[k][threadIdx.x];
+      const int n = min(a.njblocks, kThreads);
+      for (int k0 = 0; k0 < n; k0 += 32) {
+        double v[32];
+#pragma unroll
+        for (int k = 0; k < 32; ++k) v[k] = red[k0 + k][threadIdx.x];
+#pragma unroll
+        for (int k = 0; k < 32; ++k) s += v[k];
+      }
       row[kJnext + threadIdx.x] = s;
     }
   } else if (threadIdx.x < 2) {

@@ -352,32 +352,25 @@ __device__ void reduce_row(const double* __restrict__ in, int nslots, int njslot
                            double* prev_jnext, const double* __restrict__ jpart, int njblocks) {
   __shared__ double red[16][16];
   const int t = threadIdx.x, c = t & 15, g = t >> 4;
+  // Loads in flight together (their latency is what the reduction of a few hundred slots
+  // costs), added in slot order.
+  constexpr int kU = 24;
+  auto slots = [&](const double* p, int n, int stride, int at, double acc) {
+    for (int s0 = g; s0 < n; s0 += 16 * kU) {
+      double v[kU];
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        const int s = s0 + 16 * u;
+        v[u] = s < n ? p[int64_t(s) * stride + at] : 0.0;
+      }
+#pragma unroll
+      for (int u = 0; u < kU; ++u) acc += v[u];
+    }
+    return acc;
+  };
   double acc = 0.0;
-  // Eight loads in flight, added in slot order.
-  if (c < kPart)
-    for (int s0 = g; s0 < nslots; s0 += 16 * 8) {
-      double v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int s = s0 + 16 * u;
-        v[u] = s < nslots ? in[int64_t(s) * kPart + c] : 0.0;
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) acc += v[u];
-    }
-  if (c >= 6 && c < 9) {
-    const double* jin = in + int64_t(nslots) * kPart;
-    for (int s0 = g; s0 < njslots; s0 += 16 * 8) {
-      double v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int s = s0 + 16 * u;
-        v[u] = s < njslots ? jin[int64_t(s) * 3 + (c - 6)] : 0.0;
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) acc += v[u];
-    }
-  }
+  if (c < kPart) acc = slots(in, nslots, kPart, c, acc);
+  if (c >= 6 && c < 9) acc = slots(in + int64_t(nslots) * kPart, njslots, 3, c - 6, acc);
   red[g][c] = acc;
   __syncthreads();
   if (t < kPart) {
