@@ -347,10 +347,27 @@ FuseMap fuse_for(const lbm_t* h, const DevTables& t, int32_t n, bool forces) {
   return fuse_pays(h->g.precision, h->g.collision, nodes, body) ? m : none;
 }
 
+// The same for n steps without forces whose states are all kept: 12 bytes read and 36 written a
+// step and node in binary32, where single steps read 36 as well.  The recomputation for an adjoint
+// run, which is beside the reverse steps, took, single steps : tiles, in ms of the whole reverse
+// sweep: binary32 1024 x 512 10.9 : 10.5, 2048 x 1024 13.0 : 12.9, binary64 21.5 : 19.3,
+// 26.2 : 23.7.
+FuseMap keep_for(const lbm_t* h, int32_t n) {
+  if (n < kFuse || h->buf_bytes32() == 0) return FuseMap{};
+  int rows = tile_rows(h->g.precision, h->g.collision, false, h->g.nx, h->g.ny);
+  const bool wide = h->g.precision == LBM_FP64;
+  if (rows == 0 && h->g.collision == LBM_COLL_BGK &&
+      (wide || ((h->g.precision == LBM_FP32 || h->g.precision == LBM_FP32DEV) &&
+                double(h->g.nx) * h->g.ny <= 1e6)))
+    rows = 8;
+  return rows > 0 ? tile_map(h->plan, rows) : FuseMap{};
+}
+
 // Enqueue n >= 1 steps; step k reads io(k).first and writes io(k).second.  With a
 // non-null ring, the force row of step k goes to ring row k (rows are self-contained:
 // the J of the following step, or of the pull after the last one, is stored with it).
-// `alternate`: io takes two buffers in turns, so that kFuse (odd) steps may go in one launch.
+// `alternate`: io takes two buffers in turns, so that kFuse (odd) steps may go in one launch;
+// else every state is kept.
 template <class IO>
 int enqueue_steps(lbm_t* h, const DevTables& t, hipStream_t stream, int32_t n, double* ring,
                   int64_t step0, bool alternate, IO&& io) {
@@ -358,7 +375,7 @@ int enqueue_steps(lbm_t* h, const DevTables& t, hipStream_t stream, int32_t n, d
   const bool forces = ring != nullptr;
   StepArgs a = step_args(h, t);
   FuseArgs q{};
-  q.map = alternate ? fuse_for(h, t, n, forces) : FuseMap{};
+  q.map = alternate ? fuse_for(h, t, n, forces) : (forces ? FuseMap{} : keep_for(h, n));
   q.step.part_stride = t.part_stride;
   const void* last = nullptr;
   // Single steps first, then the fused launches: a launch reduces the rows of the one before
@@ -385,6 +402,7 @@ int enqueue_steps(lbm_t* h, const DevTables& t, hipStream_t stream, int32_t n, d
       in_last = 1;
     } else {
       a.dst = io(k + kFuse - 1).second;
+      for (int j = 0; j + 1 < kFuse; ++j) q.step.mid[j] = alternate ? nullptr : io(k + j).second;
       for (int j = 0; j < kFuse; ++j) q.step.step_key[j] = sr_step_key(step0 + k + j);
       q.step.part_out = forces ? t.part[turn] : nullptr;
       q.nred = forces ? in_last : 0;

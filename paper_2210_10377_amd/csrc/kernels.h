@@ -98,6 +98,8 @@ struct FuseStep {
   double* part_out;       // force partials of the first step, or null
   int64_t part_stride;    // doubles between the partials of successive steps
   uint32_t step_key[kFuse];
+  // Where the states after all steps but the last go (tiles without forces), or null: nowhere.
+  void* mid[kFuse - 1];
 };
 
 // Arguments of a fused launch besides the step's own (src is the state kFuse steps before

@@ -1,6 +1,7 @@
 // kFuse time steps of a small lattice in one launch.  Each block takes some rows of one strip's
 // columns with kFuseM nodes around them, one thread a node: the first step pulls from memory,
-// the others from LDS, and only the block's own nodes are stored.  A node's codes, inlet
+// the others from LDS, and only the block's own nodes are stored (after every step where each
+// state is kept).  A node's codes, inlet
 // velocity and force slot are read once for all steps.
 #include <hip/hip_runtime.h>
 
@@ -83,7 +84,6 @@ __global__ __launch_bounds__(64 * tile_waves(ROWS)) void tile_kernel(StepArgs a,
                       ya - kM + e) == kStripBoxInterior;
   }
   const Planes<T, true> src(a.src, a.plane, a.buf_bytes);
-  const Planes<T, true> dst(a.dst, a.plane, a.buf_bytes);
   T v[kQ] = {}, s[kQ] = {};
   if (valid) pull_raw<P>(src, a.pitch, a.nx, a.ny, w, x, y, v);
   valid = valid && !(w & kSolidBit);
@@ -112,10 +112,13 @@ __global__ __launch_bounds__(64 * tile_waves(ROWS)) void tile_kernel(StepArgs a,
       if constexpr (j < kFuse - 1) {
 #pragma unroll
         for (int i = 1; i < kQ; ++i) st[j][i - 1][e][p] = n[i];
-      } else if (mine) {
+      }
+      if (mine && (j == kFuse - 1 || (!FORCES && q.step.mid[j % (kFuse - 1)]))) {
+        const Planes<T, true> out(j == kFuse - 1 ? a.dst : q.step.mid[j % (kFuse - 1)], a.plane,
+                                  a.buf_bytes);
         const int32_t o = y * a.pitch + x;
 #pragma unroll
-        for (int i = 0; i < kQ; ++i) dst.st(i, o, n[i]);
+        for (int i = 0; i < kQ; ++i) out.st(i, o, n[i]);
       }
 #pragma unroll
       for (int i = 0; i < kQ; ++i) s[i] = n[i];
