@@ -203,6 +203,9 @@ hipError_t launch_step(int precision, bool forces, const StepArgs& a, hipStream_
 // kFuse steps in one launch (state buffers below 4 GiB).
 hipError_t launch_fused(int precision, bool forces, const StepArgs& a, const FuseArgs& q,
                         hipStream_t s);
+// kFuse steps of the body rectangles of a batch, with forces: the items are blocks of
+// kBatchTileRows rows of a strip, rows before strips (state buffers below 4 GiB).
+hipError_t launch_batch_tiles(int precision, const BatchFuse& b, hipStream_t s);
 // The same with a work map of tiles.
 hipError_t launch_tiles(int precision, bool forces, const StepArgs& a, const FuseArgs& q,
                         hipStream_t s);

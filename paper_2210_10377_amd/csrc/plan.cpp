@@ -357,8 +357,8 @@ bool fuse_pays(int precision, int collision, double nodes, double body) {
   // forces 8.1 : 9.5, a moving airfoil with forces 12.4 : 13.3.  A node of the body rectangle
   // costs several times what a plain one costs.  Batches behave alike (body share 0.11, with
   // forces and without): binary32, 16 lattices of 43 000 nodes 20 : 19 and 16 : 15, 64
-  // 47 : 47 and 42 : 34, 256 175 : 148 and 170 : 106; binary64 31 : 24 and 29 : 18, 84 : 61 and
-  // 84 : 45, 336 : 230 and 349 : 169; stochastically rounded 256 193 : 237.
+  // 47 : 47 and 42 : 34, 256 175 : 139 and 170 : 106; binary64 31 : 24 and 29 : 18, 84 : 56 and
+  // 84 : 45, 336 : 210 and 349 : 169; stochastically rounded 256 193 : 237.
   if (collision != LBM_COLL_BGK) return false;
   switch (precision) {
     case LBM_FP64: return nodes >= 2.5e5 && body <= 0.4;

@@ -156,6 +156,7 @@ constexpr int kFuseM = kFuse - 1;
 constexpr int kFuseLanes = 56;
 constexpr int kFuseEdgeW = 64 - 2 * kFuseM;
 constexpr int kHalf = kStripW / 2;
+constexpr int kBatchTileRows = 8;
 enum FuseKind { kFuseBody = 0, kFuseEdge = 1, kFuseSides = 2, kFusePlain = 3 };
 // Lanes of a kFuseSides window: column l in lane l < kSideRight, the columns from x1 - kFuseM
 // on from lane kSideRight, columns -kFuseM .. -1 in the last lanes.

@@ -25,29 +25,20 @@ constexpr int tile_waves(int rows) {
   return rows + 2 * kM + ((rows + 2 * kM) * 2 * kM + 63) / 64;
 }
 
+// Stored populations of the directions 1 .. 8 of a tile, after the first step and after the second.
+template <int P, int ROWS>
+using TileState = typename Storage<P>::T[kFuse - 1][kQ - 1][ROWS + 2 * kM][kTileCols];
+
+// kFuse steps of rows [ya, min(ya + ROWS, y1)) of the strip from column x0; columns [c0, c1) of
+// it are stored.
 template <int P, bool FORCES, int COLL, bool MOV, int ROWS>
-__global__ __launch_bounds__(64 * tile_waves(ROWS)) void tile_kernel(StepArgs a, FuseArgs q) {
+__device__ __forceinline__ void tile_block(const StepArgs& a, const FuseStep& q, int x0, int ya,
+                                           int y1, int c0, int c1, TileState<P, ROWS>& st) {
   using S = Storage<P>;
   using T = typename S::T;
   using C = typename S::C;
   constexpr int kRows = ROWS + 2 * kM;
-  // Stored populations of the directions 1 .. 8, after the first step and after the second.
-  __shared__ T st[kFuse - 1][kQ - 1][kRows][kTileCols];
-
-  int b = int(blockIdx.x);
-  if (q.nred > 0) {
-    // The first eight blocks (one per XCD) reduce the force rows of the launch before this one.
-    if (b < 8) {
-      if (b < q.nred)
-        reduce_row(q.red_in + b * q.step.part_stride, a.nslots, a.njslots, q.red_row + b * kRingRow,
-                   b > 0 || q.red_has_prev ? q.red_row + (b - 1) * kRingRow + kJnext : nullptr);
-      return;
-    }
-    b -= 8;
-  }
-  const int ns = (a.nx + kStripW - 1) / kStripW;
-  const int chunk = b / ns, x0 = (b - chunk * ns) * kStripW, ya = chunk * ROWS;
-  const int width = min(kStripW, a.nx - x0), yb = min(ya + ROWS, a.ny);
+  const int width = min(kStripW, a.nx - x0), yb = min(ya + ROWS, y1);
   const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
   const int lane = int(threadIdx.x) & 63;
   const bool periodic_x = a.bc_x == LBM_BCX_PERIODIC, periodic_y = a.bc_y == LBM_BCY_PERIODIC;
@@ -108,13 +99,13 @@ __global__ __launch_bounds__(64 * tile_waves(ROWS)) void tile_kernel(StepArgs a,
       }
       finish_pull<P>(v, u, a.rho_w6, w, x, y, f, MOV ? a.motion : nullptr);
       T n[kQ];
-      collide_pack<P, COLL>(a, f, q.step.step_key[j], x, y, n);
+      collide_pack<P, COLL>(a, f, q.step_key[j], x, y, n);
       if constexpr (j < kFuse - 1) {
 #pragma unroll
         for (int i = 1; i < kQ; ++i) st[j][i - 1][e][p] = n[i];
       }
-      if (mine && (j == kFuse - 1 || (!FORCES && q.step.mid[j % (kFuse - 1)]))) {
-        const Planes<T, true> out(j == kFuse - 1 ? a.dst : q.step.mid[j % (kFuse - 1)], a.plane,
+      if (mine && x >= c0 && x < c1 && (j == kFuse - 1 || (!FORCES && q.mid[j % (kFuse - 1)]))) {
+        const Planes<T, true> out(j == kFuse - 1 ? a.dst : q.mid[j % (kFuse - 1)], a.plane,
                                   a.buf_bytes);
         const int32_t o = y * a.pitch + x;
 #pragma unroll
@@ -124,7 +115,7 @@ __global__ __launch_bounds__(64 * tile_waves(ROWS)) void tile_kernel(StepArgs a,
       for (int i = 0; i < kQ; ++i) s[i] = n[i];
     }
     if (FORCES && slot >= 0) {
-      double* part = q.step.part_out + j * q.step.part_stride;
+      double* part = q.part_out + j * q.part_stride;
       double acc[kPart] = {};
       if (box) {
         double jb[kBoxPart] = {};
@@ -153,6 +144,49 @@ __global__ __launch_bounds__(64 * tile_waves(ROWS)) void tile_kernel(StepArgs a,
   step(std::integral_constant<int, 0>{});
   step(std::integral_constant<int, 1>{});
   step(std::integral_constant<int, 2>{});
+}
+
+template <int P, bool FORCES, int COLL, bool MOV, int ROWS>
+__global__ __launch_bounds__(64 * tile_waves(ROWS)) void tile_kernel(StepArgs a, FuseArgs q) {
+  __shared__ TileState<P, ROWS> st;
+  int b = int(blockIdx.x);
+  if (q.nred > 0) {
+    // The first eight blocks (one per XCD) reduce the force rows of the launch before this one.
+    if (b < 8) {
+      if (b < q.nred)
+        reduce_row(q.red_in + b * q.step.part_stride, a.nslots, a.njslots, q.red_row + b * kRingRow,
+                   b > 0 || q.red_has_prev ? q.red_row + (b - 1) * kRingRow + kJnext : nullptr);
+      return;
+    }
+    b -= 8;
+  }
+  const int ns = (a.nx + kStripW - 1) / kStripW, chunk = b / ns;
+  tile_block<P, FORCES, COLL, MOV, ROWS>(a, q.step, (b - chunk * ns) * kStripW, chunk * ROWS, a.ny,
+                                         0, a.nx, st);
+}
+
+// The body rectangles of a batch, with forces: kBatchTileRows rows of a strip a block, in the
+// order of the item list.
+template <int P, bool MOV>
+__global__ __launch_bounds__(64 * tile_waves(kBatchTileRows)) void batch_tile_kernel(BatchFuse b) {
+  __shared__ TileState<P, kBatchTileRows> st;
+  const int t = int(blockIdx.x), i = b.item_inst[t];
+  const BatchInst& I = b.inst[i];
+  StepArgs a = I.a;
+  a.src = I.buf[b.parity];
+  a.dst = I.buf[1 - b.parity];
+  FuseStep q{};
+  q.part_out = I.part[b.turn];
+  q.part_stride = I.part_stride;
+#pragma unroll
+  for (int j = 0; j < kFuse; ++j)
+    q.step_key[j] = Storage<P>::kSR ? sr_step_key(b.step0 + I.step_off + j) : 0u;
+  const FuseRect r = b.map[i].r[0];
+  const int first = r.x0 / kStripW, ns = (r.x1 + kStripW - 1) / kStripW - first;
+  const int local = b.item_local[t], chunk = local / ns;
+  tile_block<P, true, LBM_COLL_BGK, MOV, kBatchTileRows>(
+      a, q, (first + local - chunk * ns) * kStripW, r.y0 + chunk * kBatchTileRows, r.y1, r.x0, r.x1,
+      st);
 }
 
 template <int P, bool FORCES, int COLL, bool MOV>
@@ -191,7 +225,28 @@ hipError_t tile_go(bool forces, const StepArgs& a, const FuseArgs& q, hipStream_
   }
 }
 
+template <int P>
+hipError_t batch_tile_go(const BatchFuse& b, hipStream_t s) {
+  const dim3 grid(unsigned(b.nitems)), block(64 * tile_waves(kBatchTileRows));
+  if (b.moving)
+    hipLaunchKernelGGL((batch_tile_kernel<P, true>), grid, block, 0, s, b);
+  else
+    hipLaunchKernelGGL((batch_tile_kernel<P, false>), grid, block, 0, s, b);
+  return hipGetLastError();
+}
+
 }  // namespace
+
+hipError_t launch_batch_tiles(int precision, const BatchFuse& b, hipStream_t s) {
+  switch (precision) {
+    case LBM_FP64: return batch_tile_go<LBM_FP64>(b, s);
+    case LBM_FP32: return batch_tile_go<LBM_FP32>(b, s);
+    case LBM_FP32DEV: return batch_tile_go<LBM_FP32DEV>(b, s);
+    case LBM_FP32SR: return batch_tile_go<LBM_FP32SR>(b, s);
+    case LBM_FP16DEV: return batch_tile_go<LBM_FP16DEV>(b, s);
+    default: return hipErrorInvalidValue;
+  }
+}
 
 hipError_t launch_tiles(int precision, bool forces, const StepArgs& a, const FuseArgs& q,
                         hipStream_t s) {

@@ -427,3 +427,34 @@ def test_fused_batch_bitwise_equals_singles(precision):
     for a, c in zip(*runs):
         for x, y in zip(a, c):
             np.testing.assert_array_equal(x, y)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_batch_with_tiled_body_rectangles_bitwise_equals_singles(precision):
+    """Above 1e6 nodes the body rectangles of a batch take a launch of tiles with forces:
+    every instance bitwise equal to the member stepped alone, in calls of 4 and 3 steps."""
+    from paper_2210_10377_amd import Batch, Sim
+    ws = workloads.batched_instances(28, seed=13)
+    runs = []
+    for batched in (True, False):
+        sims = [Sim(w.mask, w.tau, w.uin, precision=precision, box=w.box, max_record=8,
+                    u_ref=w.u_ref, l_ref=w.l_ref) for w in ws]
+        assert sum(s.nx * s.ny for s in sims) >= 1_000_000
+        b = Batch(sims, max_record=8) if batched else None
+        out = []
+        for k in (4, 3):
+            print(f"tiled batch {precision} batched={batched} k={k}", flush=True)
+            if batched:
+                b.step(k)
+                out.append(list(b.forces()[0]))
+            else:
+                for s in sims:
+                    s.step(k)
+                out.append([s.forces() for s in sims])
+        out.append([s.populations() for s in sims])
+        runs.append(out)
+        del b, sims
+    for a, c in zip(*runs):
+        for x, y in zip(a, c):
+            np.testing.assert_array_equal(x, y)
