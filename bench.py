@@ -57,7 +57,7 @@ def measured_traffic(workload: str, precision: str, three_d: bool = False):
     rec = t.get(f"{workload}/{precision}")
     if not rec or rec.get("sources_sha256") != kernel_hash(three_d):
         return None
-    return rec["hbm_bytes_per_launch"]
+    return rec["hbm_bytes_per_launch"] / rec.get("steps_per_launch", 1)
 
 
 def host_cpu_model() -> str:
@@ -1189,9 +1189,13 @@ def main():
                    "box_nodes": int(info.n_box), **{k: v for k, v in w.meta.items()},
                    **({"body_motion": {"omega": motion[2], "xc": motion[3], "yc": motion[4]}}
                       if motion else {})},
+        # achieved: one read and one write of every population a step, as single steps make
+        # them (launches of three steps move about a third); hbm_frac: the counted bytes.
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
-                     "traffic": traffic},
+                     "traffic": traffic,
+                     "hbm_frac": round(traffic / t_step / 1e9 / HBM_PEAK_GBS, 4)
+                     if traffic else None},
         "wall_s": round(wall, 3),
         "forces_off_ms_per_step": round(ms_off, 5),
         "force_cost_frac": round((ms / K - ms_off) / ms_off, 4),

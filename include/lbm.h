@@ -399,7 +399,8 @@ const char* lbm_last_error(const lbm_t* h);
  * precision and advances all of them together: each step is ONE kernel launch that
  * updates every instance (a sweep over the concatenated tile lists of all instances,
  * optionally by a persistent grid), and runs of launches can be replayed from captured
- * HIP graphs.  Every instance computes exactly what lbm_step computes for it (same
+ * HIP graphs.  Batches large enough take three steps a launch instead (the schedule then
+ * covers the steps left over).  Every instance computes exactly what lbm_step computes for it (same
  * kernels per tile, same force reduction order): populations and forces are bitwise
  * those of the member stepped alone with the same call lengths.
  *
