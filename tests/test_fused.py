@@ -131,6 +131,45 @@ def test_work_map_owns_every_node_once_and_keeps_its_margins(tmp_path):
     assert out.returncode == 0 and out.stdout.strip() == "ok", out.stdout + out.stderr
 
 
+# The driver with a grid that the planner accepts (it refuses one without room for a force row),
+# counting the plans that are built and the kinds of rectangle that occur, and its verdict.
+COUNTED = (DRIVER
+           .replace("  std::mt19937 rng(7);", "  std::mt19937 rng(7);\n  int built = 0, kinds[4] = {};")
+           .replace("    g.tile = pick(0, 2);", "    g.tile = pick(0, 2);\n    g.max_record = 1;")
+           .replace("    for (int e = 0; e < 3; ++e) {", "    ++built;\n    for (int e = 0; e < 3; ++e) {")
+           .replace("        const FuseRect& r = m.r[k];", "        const FuseRect& r = m.r[k];\n        ++kinds[r.kind];")
+           .replace('  std::printf("ok\\n");',
+                    '  std::printf("%d %d %d %d %d\\n", built, kinds[0], kinds[1], kinds[2], kinds[3]);'))
+
+
+def _run_map_driver(tmp_path, text):
+    src = tmp_path / "driver.cpp"
+    src.write_text(text)
+    exe = tmp_path / "driver"
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-fsanitize=address,undefined",
+                           "-I", CSRC, "-I", os.path.join(ROOT, "include"), str(src),
+                           os.path.join(CSRC, "plan.cpp"), "-o", str(exe)])
+    return subprocess.run([str(exe)], capture_output=True, text=True, timeout=300)
+
+
+def test_work_map_checks_are_made_on_built_plans(tmp_path):
+    """The same checks of the work map, over plans that are built: all 600, with rectangles of
+    every kind among them."""
+    out = _run_map_driver(tmp_path, COUNTED)
+    assert out.returncode == 0, out.stdout + out.stderr
+    built, *kinds = (int(v) for v in out.stdout.split())
+    assert built == 600 and min(kinds) >= 100, (built, kinds)
+
+
+def test_work_map_checks_notice_a_margin_too_small(tmp_path):
+    """With one node of margin more asked for than the map has, the checks fail: they see where
+    its rectangles end."""
+    wider = COUNTED.replace("const int mar = kFuseM;", "const int mar = kFuseM + 1;")
+    assert wider != COUNTED
+    out = _run_map_driver(tmp_path, wider)
+    assert out.returncode == 1 and out.stdout.startswith("line "), out.stdout + out.stderr
+
+
 def _case(name):
     z = lambda nx, ny: np.zeros((ny, nx), np.uint8)  # noqa: E731
     if name == "airfoil":            # 725 x 701, the box inside the grid
