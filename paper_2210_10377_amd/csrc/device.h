@@ -1,6 +1,6 @@
 // Device building blocks shared by the forward step and the adjoint kernels: storage
-// formats, buffer addressing, the BGK and regularized collisions, the pull of one node with its boundary
-// rules, and fixed-order wave / block reductions.
+// formats, buffer addressing, the collisions, the pull of one node with its boundary rules, and
+// fixed-order wave / block reductions.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -254,57 +254,118 @@ struct Planes<T, false> {
   }
 };
 
-// BGK collision (see collide) with every fused operation named and none left to the compiler,
-// so that each kernel that inlines it rounds alike.  Terms even in the velocity serve both
-// directions of an opposite pair; that changes no result, since c.u of the one is exactly minus
-// that of the other.  f^eq = w z, z = s + rho poly (deviations) or rho (1 + poly), poly = 3 c.u +
-// 4.5 (c.u)^2 - 1.5 u^2.  EXACT (32-bit storage): weights to more than their own precision, see
-// wmul.  With bare weights in binary16 storage the last operation rounds once, to binary16; the
-// compiler joins it with the conversion that follows in the kernels that only store the result,
-// and FP16 names the joint operation for the others.
-template <class C, bool DEV, bool EXACT, bool FP16>
-__device__ __forceinline__ void collide_bgk(const C (&f)[kQ], C om, C (&g)[kQ]) {
+// The collisions below name every fused operation and leave none to the compiler, so that each
+// kernel that inlines them rounds alike, whatever stands around them.
+template <class C>
+__device__ __forceinline__ C fused(C a, C b, C c) {
+  if constexpr (sizeof(C) == 8)
+    return __builtin_fma(a, b, c);
+  else
+    return __builtin_fmaf(a, b, c);
+}
+
+// f + k d rounded to storage.  Binary16 storage rounds the joint operation once, to binary16; the
+// compiler joins a fused operation with the conversion that follows in the kernels that only store
+// the result, and FP16 names the joint operation for the others.
+template <class C, bool FP16>
+__device__ __forceinline__ C relaxed(C k, C d, C f) {
+  if constexpr (FP16) {
+    _Float16 h;
+    asm("v_fma_mixlo_f16 %0, %1, %2, %3" : "=v"(h) : "v"(k), "v"(d), "v"(f));
+    return C(h);
+  } else {
+    return fused(k, d, f);
+  }
+}
+
+// Equilibrium (see collide) of every direction: calls use(i, z) with f^eq = w z, z = s + rho poly
+// (deviations, f^eq less its weight) or rho (1 + poly), poly = 3 c.u + 4.5 (c.u)^2 - 1.5 u^2, and
+// returns rho.  Terms even in the velocity serve both directions of an opposite pair; that
+// changes no result, since c.u of the one is exactly minus that of the other.
+template <class C, bool DEV, class Use>
+__device__ __forceinline__ C equilibrium(const C (&f)[kQ], Use&& use) {
 #pragma clang fp contract(off)
-  auto fma = [](C a, C b, C c) __attribute__((always_inline)) {
-    if constexpr (sizeof(C) == 8)
-      return __builtin_fma(a, b, c);
-    else
-      return __builtin_fmaf(a, b, c);
-  };
   const C s = ((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7])) + f[8];
   const C jx = (f[1] + f[5] + f[8]) - (f[3] + f[6] + f[7]);
   const C jy = (f[2] + f[5] + f[6]) - (f[4] + f[7] + f[8]);
   const C rho = DEV ? C(1) + s : s;
   const C ir = C(1) / rho;
   const C ux = jx * ir, uy = jy * ir;
-  const C uu = fma(ux, ux, uy * uy);
-  auto relax = [&](int i, C poly) __attribute__((always_inline)) {
-    const C z = DEV ? fma(rho, poly, s) : rho * (C(1) + poly);
-    const C w = weight<C>(i);
-    if constexpr (sizeof(C) == 4 && EXACT) {
-      const C fe = fma(w, z, weight_lo(i) * z);
-      g[i] = fma(om, fe - f[i], f[i]);
-    } else {
-      const C d = fma(w, z, -f[i]);
-      if constexpr (FP16) {
-        _Float16 h;
-        asm("v_fma_mixlo_f16 %0, %1, %2, %3" : "=v"(h) : "v"(om), "v"(d), "v"(f[i]));
-        g[i] = C(h);
-      } else {
-        g[i] = fma(om, d, f[i]);
-      }
-    }
+  const C uu = fused(ux, ux, uy * uy);
+  auto z = [&](C poly) __attribute__((always_inline)) {
+    return DEV ? fused(rho, poly, s) : rho * (C(1) + poly);
   };
-  relax(0, C(-1.5) * uu);
+  use(0, z(C(-1.5) * uu));
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     constexpr int kPair[4] = {1, 2, 5, 6};
     const int i = kPair[k];
-    const C cu = i == 1 ? ux : (i == 2 ? uy : (i == 5 ? fma(jx, ir, uy) : fma(-jx, ir, uy)));
+    const C cu = i == 1 ? ux : (i == 2 ? uy : (i == 5 ? fused(jx, ir, uy) : fused(-jx, ir, uy)));
     const C sq = (C(4.5) * cu) * cu;
-    relax(i, fma(C(-1.5), uu, fma(C(3), cu, sq)));
-    relax(i + 2, fma(C(-1.5), uu, fma(C(-3), cu, sq)));
+    use(i, z(fused(C(-1.5), uu, fused(C(3), cu, sq))));
+    use(i + 2, z(fused(C(-1.5), uu, fused(C(-3), cu, sq))));
   }
+  return rho;
+}
+
+// w_i z with the weight to more than binary32 precision (wmul), of a 32-bit storage.
+__device__ __forceinline__ float exact_eq(int i, float z) {
+#pragma clang fp contract(off)
+  return __builtin_fmaf(weight<float>(i), z, weight_lo(i) * z);
+}
+
+// BGK collision (see collide).
+template <class C, bool DEV, bool EXACT, bool FP16>
+__device__ __forceinline__ void collide_bgk(const C (&f)[kQ], C om, C (&g)[kQ]) {
+#pragma clang fp contract(off)
+  equilibrium<C, DEV>(f, [&](int i, C z) __attribute__((always_inline)) {
+    if constexpr (sizeof(C) == 4 && EXACT)
+      g[i] = fused(om, exact_eq(i, z) - f[i], f[i]);
+    else
+      g[i] = relaxed<C, FP16>(om, fused(weight<C>(i), z, -f[i]), f[i]);
+  });
+}
+
+// Entropic collision (see collide).
+template <class C, bool DEV, bool EXACT, bool FP16>
+__device__ __forceinline__ void collide_kbc(const C (&f)[kQ], C om, C (&g)[kQ]) {
+#pragma clang fp contract(off)
+  C d[kQ], fq[kQ];  // f - f^eq, and f^eq itself
+  const C rho = equilibrium<C, DEV>(f, [&](int i, C z) __attribute__((always_inline)) {
+    const C w = weight<C>(i);
+    if constexpr (sizeof(C) == 4 && EXACT) {
+      const C fe = exact_eq(i, z);
+      d[i] = f[i] - fe;
+      fq[i] = DEV ? w + fe : fe;
+    } else {
+      d[i] = fused(-w, z, f[i]);
+      fq[i] = DEV ? fused(w, z, w) : w * z;
+    }
+  });
+  const C qn = C(0.25) * ((d[1] + d[3]) - (d[2] + d[4]));
+  const C qp = C(0.25) * ((d[5] + d[7]) - (d[6] + d[8]));
+  // Entropic weights 1/f^eq: exact division in binary64, the hardware reciprocal (1 ulp) in
+  // binary32, where they only weigh the stabilizer.
+  C ds[kQ], dh[kQ], sh = C(0), hh = C(0);
+#pragma unroll
+  for (int i = 0; i < kQ; ++i) {
+    ds[i] = i == 0 ? C(0) : (i < 5 ? (kCy[i] == 0 ? qn : -qn) : (kCx[i] * kCy[i] > 0 ? qp : -qp));
+    dh[i] = d[i] - ds[i];
+    C wi;
+    if constexpr (sizeof(C) == 8)
+      wi = C(1) / fq[i];
+    else
+      wi = __builtin_amdgcn_rcpf(fq[i]);
+    sh = fused(ds[i] * dh[i], wi, sh);
+    hh = fused(dh[i] * dh[i], wi, hh);
+  }
+  const C beta = C(0.5) * om;
+  const C ib = C(1) / beta;
+  const C thr = sizeof(C) == 8 ? C(0x1p-90) : C(0x1p-40);
+  const C gamma = hh > thr * rho ? ib - (C(2) - ib) * sh / hh : C(2);
+#pragma unroll
+  for (int i = 0; i < kQ; ++i)
+    g[i] = relaxed<C, FP16>(-beta, fused(gamma, dh[i], C(2) * ds[i]), f[i]);
 }
 
 // Collision of one node; COLL selects the operator (LBM_COLL_*):
@@ -323,10 +384,16 @@ __device__ __forceinline__ void collide_bgk(const C (&f)[kQ], C om, C (&g)[kQ]) 
 // rho u = sum c_i h_i, f^eq_i - w_i = w_i [(rho - 1) + rho (3 c.u + 4.5 (c.u)^2 -
 // 1.5 u^2)] and Pi^neq = sum c c h - rho u u - (rho - 1) I/3, so no quantity of order one
 // is formed except the entropic weights f^eq_i.
+// The regularized collision leaves its fused operations to the compiler, which chooses them
+// otherwise in kernels of several steps: only step_kernel and batch_step_kernel take it.
 template <class C, bool DEV, int COLL, bool EXACT = true, bool FP16 = false>
 __device__ __forceinline__ void collide(const C (&f)[kQ], C omega, C (&g)[kQ]) {
   if constexpr (COLL == LBM_COLL_BGK) {
     collide_bgk<C, DEV, EXACT, FP16>(f, omega, g);
+    return;
+  }
+  if constexpr (COLL == LBM_COLL_KBC) {
+    collide_kbc<C, DEV, EXACT, FP16>(f, omega, g);
     return;
   }
   const C s = ((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7])) + f[8];
@@ -344,51 +411,17 @@ __device__ __forceinline__ void collide(const C (&f)[kQ], C omega, C (&g)[kQ]) {
     const C poly = C(3) * cu + C(4.5) * cu * cu - usq;
     fe[i] = DEV ? wmul<C, EXACT>(i, s + rho * poly) : wmul<C, EXACT>(i, rho * (C(1) + poly));
   }
-  if constexpr (COLL == LBM_COLL_REGULARIZED) {
-    const C diag = (f[5] + f[6]) + (f[7] + f[8]);
-    const C r3 = (DEV ? s : rho) * C(1.0 / 3.0);
-    const C pxx = ((f[1] + f[3]) + diag) - rho * ux * ux - r3;
-    const C pyy = ((f[2] + f[4]) + diag) - rho * uy * uy - r3;
-    const C pxy = (f[5] + f[7]) - (f[6] + f[8]) - rho * ux * uy;
-    const C k = (C(1) - om) * C(4.5);
+  const C diag = (f[5] + f[6]) + (f[7] + f[8]);
+  const C r3 = (DEV ? s : rho) * C(1.0 / 3.0);
+  const C pxx = ((f[1] + f[3]) + diag) - rho * ux * ux - r3;
+  const C pyy = ((f[2] + f[4]) + diag) - rho * uy * uy - r3;
+  const C pxy = (f[5] + f[7]) - (f[6] + f[8]) - rho * ux * uy;
+  const C k = (C(1) - om) * C(4.5);
 #pragma unroll
-    for (int i = 0; i < kQ; ++i) {
-      const C q = C(kCx[i] * kCx[i] - 1.0 / 3.0) * pxx + C(2 * kCx[i] * kCy[i]) * pxy +
-                  C(kCy[i] * kCy[i] - 1.0 / 3.0) * pyy;
-      g[i] = fe[i] + k * weight<C>(i) * q;
-    }
-  } else {
-    C d[kQ];
-#pragma unroll
-    for (int i = 0; i < kQ; ++i) d[i] = f[i] - fe[i];
-    const C qn = C(0.25) * ((d[1] + d[3]) - (d[2] + d[4]));
-    const C qp = C(0.25) * ((d[5] + d[7]) - (d[6] + d[8]));
-    C ds[kQ];
-    ds[0] = C(0);
-#pragma unroll
-    for (int i = 1; i < kQ; ++i) ds[i] = i < 5 ? (kCy[i] == 0 ? qn : -qn) : C(kCx[i] * kCy[i]) * qp;
-    // Entropic weights 1/f^eq: exact division in binary64, the hardware reciprocal
-    // (1 ulp) in binary32, where they only weigh the stabilizer.
-    C sh = C(0), hh = C(0);
-#pragma unroll
-    for (int i = 0; i < kQ; ++i) {
-      const C dh = d[i] - ds[i];
-      const C fq = DEV ? weight<C>(i) + fe[i] : fe[i];
-      C wi;
-      if constexpr (sizeof(C) == 8)
-        wi = C(1) / fq;
-      else
-        wi = __builtin_amdgcn_rcpf(fq);
-      sh += ds[i] * dh * wi;
-      hh += dh * dh * wi;
-    }
-    const C beta = C(0.5) * om;
-    const C ib = C(1) / beta;
-    const C thr = sizeof(C) == 8 ? C(0x1p-90) : C(0x1p-40);
-    const C gamma = hh > thr * rho ? ib - (C(2) - ib) * sh / hh : C(2);
-#pragma unroll
-    for (int i = 0; i < kQ; ++i)
-      g[i] = f[i] - beta * (C(2) * ds[i] + gamma * (d[i] - ds[i]));
+  for (int i = 0; i < kQ; ++i) {
+    const C q = C(kCx[i] * kCx[i] - 1.0 / 3.0) * pxx + C(2 * kCx[i] * kCy[i]) * pxy +
+                C(kCy[i] * kCy[i] - 1.0 / 3.0) * pyy;
+    g[i] = fe[i] + k * weight<C>(i) * q;
   }
 }
 

@@ -7,6 +7,7 @@ the reference.  States are bitwise alike whatever the calls, and so are the mome
 stress forces; the control-volume forces of a call's last step read a separately ordered sum
 of the box momentum, so they agree to binary64 rounding of that sum."""
 import os
+import re
 import subprocess
 
 import numpy as np
@@ -168,6 +169,44 @@ def test_work_map_checks_notice_a_margin_too_small(tmp_path):
     assert wider != COUNTED
     out = _run_map_driver(tmp_path, wider)
     assert out.returncode == 1 and out.stdout.startswith("line "), out.stdout + out.stderr
+
+
+# One node's collision and rounding in every storage, for the BGK (0) and entropic (2) operators.
+COLLIDE = r"""
+#include "force_terms.h"
+using namespace lbm;
+using namespace lbm::dev;
+template <int P, int COLL>
+__global__ void node(StepArgs a, const typename Storage<P>::T* in, typename Storage<P>::T* out) {
+  typename Storage<P>::C f[kQ];
+  typename Storage<P>::T s[kQ];
+  for (int i = 0; i < kQ; ++i) f[i] = unpack<P>(in[i * 64 + threadIdx.x], i);
+  collide_pack<P, COLL>(a, f, a.step_key, int(threadIdx.x), 0, s);
+  for (int i = 0; i < kQ; ++i) out[i * 64 + threadIdx.x] = s[i];
+}
+#define ALL(P) template __global__ void node<P, @>(StepArgs, const Storage<P>::T*, Storage<P>::T*);
+ALL(LBM_FP64) ALL(LBM_FP32) ALL(LBM_FP32DEV) ALL(LBM_FP32SR) ALL(LBM_FP16DEV)
+"""
+
+
+@pytest.mark.parametrize("collision", ["LBM_COLL_BGK", "LBM_COLL_KBC"])
+def test_collisions_leave_no_fused_operation_to_the_compiler(tmp_path, collision):
+    """Kernels of one and of several steps give the same bits only if the collision names its
+    fused operations: compiled with the build's flags it then has the arithmetic instructions
+    that it has where the compiler may fuse none."""
+    from paper_2210_10377_amd import build
+    src = tmp_path / "node.hip"
+    src.write_text(COLLIDE.replace("@", collision))
+    counts = []
+    for extra in ([], ["-ffp-contract=off"]):
+        out = tmp_path / ("node%d.s" % len(extra))
+        subprocess.check_call(["hipcc", *build._flags(), *extra, "-S", "--cuda-device-only", str(src),
+                               "-o", str(out)], stderr=subprocess.DEVNULL)
+        ops = re.findall(r"^\s+v_(add|sub|subrev|mul|fma|fmac|fmamk|fmaak|fma_mix|fma_mixlo|mad|mac)"
+                         r"_(f16|f32|f64)", out.read_text(), re.M)
+        fused = [("fma" if op.startswith(("fma", "mad", "mac")) else "other", t) for op, t in ops]
+        counts.append({k: fused.count(k) for k in set(fused)})
+    assert sum(counts[0].values()) > 500 and counts[0] == counts[1], counts
 
 
 def _case(name):
