@@ -228,8 +228,8 @@ template <int P>
 hipError_t tile_go(bool forces, const StepArgs& a, const FuseArgs& q, hipStream_t s) {
   switch (a.collision) {
     case LBM_COLL_BGK: return tile_coll<P, LBM_COLL_BGK>(forces, a, q, s);
-    case LBM_COLL_REGULARIZED: return tile_coll<P, LBM_COLL_REGULARIZED>(forces, a, q, s);
-    default: return tile_coll<P, LBM_COLL_KBC>(forces, a, q, s);
+    case LBM_COLL_KBC: return tile_coll<P, LBM_COLL_KBC>(forces, a, q, s);
+    default: return hipErrorInvalidValue;
   }
 }
 

@@ -209,6 +209,16 @@ def test_collisions_leave_no_fused_operation_to_the_compiler(tmp_path, collision
     assert sum(counts[0].values()) > 500 and counts[0] == counts[1], counts
 
 
+def test_tile_kernels_are_those_that_the_rule_can_take():
+    """tile_rows never picks tiles for the regularized collision, whose rounding differs between
+    kernels: the library holds tile kernels of the BGK and entropic collisions only (5 storages,
+    with and without forces and motion, 2 heights each)."""
+    from paper_2210_10377_amd import _capi as C
+    names = subprocess.run(["nm", "-C", C.LIB_PATH], capture_output=True, text=True, check=True).stdout
+    got = set(re.findall(r"__device_stub__tile_kernel<(\d), (\w+), (\d), (\w+), (\d)>", names))
+    assert len(got) == 80 and {g[2] for g in got} == {str(C.LBM_COLL_BGK), str(C.LBM_COLL_KBC)}, sorted(got)
+
+
 def _case(name):
     z = lambda nx, ny: np.zeros((ny, nx), np.uint8)  # noqa: E731
     if name == "airfoil":            # 725 x 701, the box inside the grid
