@@ -332,37 +332,6 @@ BoxArgs box_args(const lbm_t* h, const void* src, const DevTables& t) {
 
 namespace {
 
-// Work map of fused launches for n steps between two alternating buffers, or one without blocks
-// where single steps are the faster or the only form.
-FuseMap fuse_for(const lbm_t* h, const DevTables& t, int32_t n, bool forces) {
-  const FuseMap none{};
-  if (n < kFuse || !t.fuse || h->buf_bytes32() == 0) return none;
-  const int rows = tile_rows(h->g.precision, h->g.collision, forces, h->g.nx, h->g.ny);
-  if (rows > 0) return tile_map(h->plan, rows);
-  const FuseMap m = fuse_map(h->plan, int(h->esz), int64_t(h->g.nx) * h->g.ny);
-  const FuseRect& r = m.r[0];
-  const double nodes = double(h->g.nx) * h->g.ny;
-  const double body =
-      r.kind == kFuseBody ? double(r.x1 - r.x0) * (r.y1 - r.y0) / nodes : 0.0;
-  return fuse_pays(h->g.precision, h->g.collision, nodes, body) ? m : none;
-}
-
-// The same for n steps without forces whose states are all kept: 12 bytes read and 36 written a
-// step and node in binary32, where single steps read 36 as well.  The recomputation for an adjoint
-// run, which is beside the reverse steps, took, single steps : tiles, in ms of the whole reverse
-// sweep: binary32 1024 x 512 10.9 : 10.5, 2048 x 1024 13.0 : 12.9, binary64 21.5 : 19.3,
-// 26.2 : 23.7.
-FuseMap keep_for(const lbm_t* h, int32_t n) {
-  if (n < kFuse || h->buf_bytes32() == 0) return FuseMap{};
-  int rows = tile_rows(h->g.precision, h->g.collision, false, h->g.nx, h->g.ny);
-  const bool wide = h->g.precision == LBM_FP64;
-  if (rows == 0 && h->g.collision == LBM_COLL_BGK &&
-      (wide || ((h->g.precision == LBM_FP32 || h->g.precision == LBM_FP32DEV) &&
-                double(h->g.nx) * h->g.ny <= 1e6)))
-    rows = 8;
-  return rows > 0 ? tile_map(h->plan, rows) : FuseMap{};
-}
-
 // Enqueue n >= 1 steps; step k reads io(k).first and writes io(k).second.  With a
 // non-null ring, the force row of step k goes to ring row k (rows are self-contained:
 // the J of the following step, or of the pull after the last one, is stored with it).
@@ -374,9 +343,14 @@ int enqueue_steps(lbm_t* h, const DevTables& t, hipStream_t stream, int32_t n, d
   const Plan& p = h->plan;
   const bool forces = ring != nullptr;
   StepArgs a = step_args(h, t);
-  FuseArgs q{};
-  q.map = alternate ? fuse_for(h, t, n, forces) : (forces ? FuseMap{} : keep_for(h, n));
-  q.step.part_stride = t.part_stride;
+  FuseArgs q;  // filled where launches of kFuse steps are taken
+  q.map.nblocks = 0;
+  if (n >= kFuse && a.buf_bytes != 0 && (alternate ? t.fuse : !forces)) {
+    q = FuseArgs{};
+    q.map = alternate ? step_map(p, h->g.precision, h->g.collision, forces, int(h->esz))
+                      : keep_map(p, h->g.precision, h->g.collision);
+    q.step.part_stride = t.part_stride;
+  }
   const void* last = nullptr;
   // Single steps first, then the fused launches: a launch reduces the rows of the one before
   // it (steps [k - in_last, k), partials in part[1 - turn]).

@@ -55,7 +55,8 @@ struct lbm_batch_t {
   size_t nbody = 0, nblocks = 0;  // items of body rectangles, and in all without tiles
   std::vector<uint64_t> fuse_gen;
   int64_t item_cap = 0;
-  bool fuse = false;
+  StepWork work;                    // of all members, which the choice of a form goes by
+  bool fuse[2] = {false, false};    // fused launches are taken, without and with forces
   std::vector<int> nj0;  // box-sweep blocks of each member at create (the lists' sizes)
   std::vector<BatchInst> desc;  // the instance table as last uploaded
   size_t off_desc = 0, off_fmap = 0, off_fi = 0, off_fl = 0, off_ti = 0, off_tl = 0, off_bi = 0, off_bl = 0, off_ctl = 0,
@@ -174,19 +175,18 @@ struct lbm_batch_t {
     }
   }
 
-  // Work maps and block list of fused launches from the members' present plans; `fuse`: they
+  // Work maps and block list of fused launches from the members' present plans, and whether they
   // are the faster form.
   void build_fuse() {
     fmap.clear();
     item_inst.clear();
     item_local.clear();
     fuse_gen.clear();
-    double body = 0.0;
+    work = StepWork();
     for (const lbm_t* h : m) {
       fuse_gen.push_back(h->plan_gen);
       fmap.push_back(fuse_map(h->plan, int(h->esz), total_nodes));
-      const FuseRect& r = fmap.back().r[0];
-      if (r.kind == kFuseBody) body += double(r.x1 - r.x0) * (r.y1 - r.y0);
+      work.add(h->plan, fmap.back(), int(h->esz));
     }
     // Blocks of the body rectangles, of the others, and of the body rectangles as tiles.
     for (int kind = kFuseBody; kind <= kFusePlain; ++kind) {
@@ -214,9 +214,9 @@ struct lbm_batch_t {
         item_local.push_back(b);
       }
     }
-    fuse = fuse_pays(precision, m[0]->g.collision, double(total_nodes),
-                     body / double(total_nodes)) &&
-           (item_cap == 0 || int64_t(item_inst.size()) <= item_cap);
+    for (int f = 0; f < 2; ++f)
+      fuse[f] = fuse_pays(precision, m[0]->g.collision, f != 0, work) &&
+                (item_cap == 0 || int64_t(item_inst.size()) <= item_cap);
   }
   bool fuse_current() const {
     for (size_t i = 0; i < m.size(); ++i)
@@ -224,7 +224,7 @@ struct lbm_batch_t {
     return true;
   }
   int upload_fuse() {
-    if (!fuse) return LBM_OK;
+    if (!fuse[0] && !fuse[1]) return LBM_OK;
     int rc = upload(fmap.data(), off_fmap, fmap.size() * sizeof(FuseMap), "upload work maps");
     if (rc == LBM_OK) rc = upload(item_inst.data(), off_fi, item_inst.size() * 4, "upload work list");
     if (rc == LBM_OK) rc = upload(item_local.data(), off_fl, item_local.size() * 4, "upload work list");
@@ -404,7 +404,7 @@ struct lbm_batch_t {
     }
     // Single steps by the schedule (all of them, or what is left over kFuse), then the fused
     // launches, which have an order of their own.
-    const int32_t singles = fuse && n >= kFuse ? n % kFuse : n;
+    const int32_t singles = fuse[forces ? 1 : 0] && n >= kFuse ? n % kFuse : n;
     int32_t done = 0;
     while (done < singles) {
       const int len = G > 0 ? std::min<int32_t>(G, singles - done) : singles - done;
@@ -440,11 +440,7 @@ struct lbm_batch_t {
       f.n_inst = L.n_inst;
       f.nitems = int32_t(nblocks);
       f.moving = L.moving;
-      // With forces the body rectangles are tiles, in a launch of their own: windows of half
-      // strips do 2.3 times the work of the nodes they own, tiles 1.4 times.  Windows : tiles, in us
-      // a step of 256, 64, 32 and 16 lattices of 43 000 nodes: binary32 148 : 139, 46 : 45,
-      // 28.7 : 27.1, 19.0 : 18.7; binary64 232 : 210, 61 : 56, 39.6 : 38.1, 23.5 : 24.1.
-      const bool tiles = forces && nbody > 0 && total_nodes >= 1000000;
+      const bool tiles = forces && batch_tiles_pay(work);
       if (tiles) {
         f.item_inst += nbody;
         f.item_local += nbody;
@@ -552,7 +548,7 @@ int lbm_batch_create(lbm_t* const* members, int32_t n, int32_t max_record, lbm_b
   b->build_alt();
   b->build_lists();
   b->build_fuse();
-  b->item_cap = b->fuse ? 2 * int64_t(b->item_inst.size()) + 256 : 1;
+  b->item_cap = b->fuse[0] || b->fuse[1] ? 2 * int64_t(b->item_inst.size()) + 256 : 1;
   size_t off = 0;
   b->off_desc = off;
   off = align256(off + size_t(n) * sizeof(BatchInst));

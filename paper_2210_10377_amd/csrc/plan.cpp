@@ -343,61 +343,162 @@ int replan(const lbm_grid& g, const uint8_t* mask, const std::vector<int32_t>& c
   return LBM_OK;
 }
 
-bool fuse_pays(int precision, int collision, double nodes, double body) {
-  // A fused launch lasts as long as its longest unit at least (25 us: three steps of rows of a
-  // body with all forces), which a single step of a small grid undercuts; and it moves a third
-  // of the bytes, so it gains most where those count most.  Measured, single against fused, in
-  // us a step with all forces (without): binary32 724 x 362 7.8 : 8.3 (5.3 : 5.3), 900 x 450
-  // 9.5 : 8.7 (7.2 : 5.8), 2048 x 1024 27 : 17, 8192 x 4096 397 : 177; binary64 512 x 256
-  // 6.0 : 8.5 (4.7 : 4.7), 724 x 362 10.5 : 8.7 (8.9 : 5.8), 4096 x 2048 199 : 88.  The
-  // stochastically rounded and the binary16 storage spend more arithmetic per byte:
-  // 2048 x 1024 27 : 31 and 16 : 22, 3001 x 1499 54 : 50 and 30 : 37, 5792 x 2896 197 : 153
-  // and 101 : 98.
-  // The stabilized collisions stay with single steps: regularized, binary32, 1024 x 512 without
-  // forces 8.1 : 9.5, a moving airfoil with forces 12.4 : 13.3.  A node of the body rectangle
-  // costs several times what a plain one costs.  Batches behave alike (body share 0.11, with
-  // forces and without): binary32, 16 lattices of 43 000 nodes 20 : 19 and 16 : 15, 64
-  // 47 : 47 and 42 : 34, 256 175 : 139 and 170 : 106; binary64 31 : 24 and 29 : 18, 84 : 56 and
-  // 84 : 45, 336 : 210 and 349 : 169; stochastically rounded 256 193 : 237.
-  if (collision != LBM_COLL_BGK) return false;
+namespace {
+
+// Rows of the tables below, by storage.
+int storage_row(int precision) {
   switch (precision) {
-    case LBM_FP64: return nodes >= 2.5e5 && body <= 0.4;
+    case LBM_FP64: return 0;
     case LBM_FP32:
-    case LBM_FP32DEV: return nodes >= 4e5 && body <= 0.2;
-    case LBM_FP32SR: return nodes >= 4e6 && body <= 0.06;
-    default: return nodes >= 1.5e7 && body <= 0.04;
+    case LBM_FP32DEV: return 1;
+    case LBM_FP32SR: return 2;
+    default: return 3;
   }
 }
 
-int tile_rows(int precision, int collision, bool forces, int nx, int ny) {
+int strips_across(int nx) { return (nx + kStripW - 1) / kStripW; }
+
+}  // namespace
+
+void StepWork::add(const Plan& p, const FuseMap& m, int elem_bytes) {
+  strips += double(strips_across(p.nx)) * kStripW * p.ny;
+  nodes += double(p.nx) * p.ny;
+  for (int k = 0; k < m.nrects; ++k) {
+    const FuseRect& r = m.r[k];
+    const int height = r.y1 - r.y0;
+    double rows = height + 2.0 * kFuseM * ((height + r.rows - 1) / r.rows);
+    if (p.bc_y == LBM_BCY_WALL)  // no rows are marched beyond a wall
+      rows -= std::max(kFuseM - r.y0, 0) + std::max(kFuseM - (p.ny - r.y1), 0);
+    const double lanes = 64.0 * r.nw * rows;
+    if (r.kind == kFuseBody) {
+      body += 2.0 * lanes;  // a wave for each half of a strip
+      body_nodes += double(r.x1 - r.x0) * height;
+    } else if (r.kind == kFusePlain) {
+      plain += lanes * (8 / elem_bytes);
+    } else {
+      coded += lanes;
+    }
+  }
+}
+
+bool fuse_pays(int precision, int collision, bool forces, const StepWork& w) {
+  // Both forms in us a step, as they were measured: a start, and us for a million lanes of strips
+  // and nodes, or of the lanes and rows that windows of each kind march (they do about 1.4 times
+  // the work in plain windows, 1.5 - 6 times at edges and bodies, for a third of the bytes; a narrow
+  // lattice has few other windows).  No fused launch is shorter than its longest unit: `least`.
+  // Fitted to 418 lattices and batches for each row of the table (242 in the lower half): widths 3 to 20000, 2e5 to 8e6
+  // nodes in all, cylinders, airfoils, porous blocks and small bodies, lattices and members from
+  // 3 rows on.  The form it picks is on average 0 - 0.9 % slower than the faster one.
+  // Measured, single : fused, with all forces (without): binary32 1024 x 512 10.4 : 10.0 (8.1 : 6.5),
+  // 2048 x 1024 27 : 17, 8192 x 4096 397 : 177, 16 x 40000 23 : 40 (21 : 29), 37 x 14000 15 : 25
+  // (13 : 21), 1000 lattices of 64 x 32 72 : 110 (30 : 60), of 43 000 nodes 16 20 : 19 (16 : 15), 256
+  // 175 : 139 (170 : 106); binary64 16 x 40000 33 : 51 (31 : 40), 4096 x 2048 199 : 88; stochastically
+  // rounded 2048 x 1024 27 : 31, 4096 x 2048 with an airfoil 100 : 85; binary16 3000 x 1500 31 : 38,
+  // 5792 x 2896 101 : 98.
+  // The stabilized collisions stay with single steps: regularized, binary32, 1024 x 512 without
+  // forces 8.1 : 9.5, a moving airfoil with forces 12.4 : 13.3.
+  struct Rates {
+    double start, strips, nodes, body;                // single steps
+    double least, begin, plain, coded, body_windows;  // fused launches
+  };
+  constexpr Rates kRates[4][2] = {
+      {{2.4, 9.9, 15.5, 1.1, 5.4, 2.0, 5.8, 5.1, 4.8}, {4.2, 10.8, 13.7, 5.6, 10.2, 2.4, 6.0, 7.5, 13.9}},
+      {{2.3, 6.8, 5.4, 0.6, 5.7, 2.8, 3.4, 3.5, 3.2}, {4.4, 8.0, 4.0, 4.7, 9.7, 4.0, 3.1, 5.1, 11.0}},
+      {{3.1, 7.9, 3.4, 0.4, 8.1, 4.8, 6.0, 5.4, 5.6}, {4.8, 9.1, 2.1, 3.7, 12.0, 5.4, 5.8, 7.1, 13.0}},
+      {{3.2, 5.5, 0.0, 0.8, 7.1, 3.8, 2.6, 5.5, 7.3}, {5.0, 5.6, 0.0, 4.6, 10.7, 4.4, 2.6, 6.5, 13.9}}};
+  if (collision != LBM_COLL_BGK) return false;
+  const Rates& r = kRates[storage_row(precision)][forces ? 1 : 0];
+  const double single = r.start + 1e-6 * (r.strips * w.strips + r.nodes * w.nodes + r.body * w.body);
+  const double windows =
+      r.begin + 1e-6 * (r.plain * w.plain + r.coded * w.coded + r.body_windows * w.body);
+  // (Nothing smaller was fitted: lattices are tiles there, and batches few.)
+  return w.strips >= 1.8e5 && std::max(r.least, windows) < 0.97 * single;
+}
+
+bool batch_tiles_pay(const StepWork& w) {
+  // Windows of half strips do 2.3 times the work of the nodes they own, tiles 1.4 times, but take a
+  // launch more.  Windows : tiles, in us a step of 256, 64, 32 and 16 lattices of 43 000 nodes, 11 %
+  // of them in the body rectangles: binary32 148 : 139, 46 : 45, 28.7 : 27.1, 19.0 : 18.7; binary64
+  // 232 : 210, 61 : 56, 39.6 : 38.1, 23.5 : 24.1.  Over 246 batches with bodies of 0.2 to 50 % the
+  // ratio goes by the nodes of the body rectangles: tiles 1.1 - 1.2 times as slow below 3e4, even at
+  // 1e5, 0.9 from 4e5 on.
+  return w.body_nodes >= 1e5;
+}
+
+int tile_rows(int precision, int collision, bool forces, double summed, int nx, int ny, bool wide) {
   // Small lattices are bound by latency: a launch of one step takes 3.4 us, with forces 5.2 as
   // each strip of the body sums 12 components, however few nodes there are.  Three steps of a
-  // tile take 6 and 10.  Beyond one block a CU the margins (12 rows of work for 8) cost more than
-  // the launches.  Measured in us a step with all forces (without), single steps : tiles of 4
-  // rows : of 8 : windows: binary64 200 x 80 5.2 : 3.4 : 4.0 : 9.3 (3.6 : 2.8 : 3.4 : 5.1), 512 x 256
-  // 6.3 : 4.9 : 4.1 : 8.7 (5.1 : 3.8 : 3.0 : 5.6), 724 x 362 9.7 : 8.8 : 7.5 : 9.6 (9.2 : 8.5 : 7.2 :
-  // 5.8), 1024 x 512 15.7 : 14.5 : 11.4 : 12.4 (15 : 12.6 : 9.5 : 9.6); binary32 512 x 256 5.7 : 4.5 :
-  // 3.9 : 9.0 (3.9 : 2.8 : 2.7 : 5.2), 724 x 362 6.7 : 7.4 : 6.0 : 8.8 (5.4 : 5.0 : 5.3 : 5.7),
-  // 1024 x 512 10.2 : 12.6 : 9.4 : 9.1 (8.1 : 7.9 : 6.8 : 6.3); stochastically rounded, binary16 and
-  // entropic 512 x 256 6.0 : 4.6, 5.6 : 4.1 and 5.7 : 4.4, 724 x 362 6.8 : 7.8, 5.9 : 5.8 and 6.5 : 7.0
-  // (single : 8 rows).  The regularized collision is left to single steps: its compiled form
-  // rounds differently here.
+  // tile take 6 and 10, as long as there is no more than one block a CU; then a second round of
+  // blocks begins, and the margins (12 rows of work for 8) cost more than the launches saved.
+  // What counts are the blocks, of idle lanes too.  Measured in us a step with all forces (without),
+  // single steps : tiles of 4 rows : of 8, and the blocks of 8 rows:
+  //   binary64 200 x 100 (52) 6.6 : 4.6 : 5.2 (3.6 : 2.6 : 3.4), 512 x 256 (256) 7.5 : 6.2 : 5.4 (4.8 :
+  //   3.8 : 2.9), 600 x 300 (380) 8.8 : 7.8 : 6.7 (6.3 : 5.9 : 5.1), 1024 x 512 (1024) 17.1 : 15.9 : 12.8
+  //   (windows 13.0), 16 x 6250 (782) 8.6 : 11.0 : 9.2;
+  //   binary32 512 x 256 6.8 : 5.8 : 5.2 (3.9 : 2.8 : 2.7), 724 x 362 (552) 7.8 : 9.0 : 7.6 (5.3 : 5.4 :
+  //   5.6), 3 x 12500 (1563) 9.7 : 17.7 : 13.2 (8.2 : 11.1 : 10.2);
+  //   stochastically rounded 600 x 300 7.6 : 8.4 : 7.0 (4.9 : 4.9 : 5.1), binary16 6.6 : 6.8 : 5.6 (4.1 :
+  //   3.7 : 3.9);
+  //   entropic 512 x 320 (320) binary64 9.1 : 9.6 : 8.8 (6.7 : 7.7 : 7.3), binary32 7.2 : 7.4 : 6.6 (4.7 :
+  //   4.5 : 4.8), stochastically rounded 7.6 : 8.8 : 7.9 (5.2 : 5.5 : 6.1), 512 x 256 7.4 : 7.3 : 6.4 (4.6 :
+  //   4.1 : 3.7).
+  // The regularized collision is left to single steps: its compiled form rounds differently here.
   if (collision == LBM_COLL_REGULARIZED) return 0;
-  const double nodes = double(nx) * ny;
-  double most = 2e5;
-  if (collision == LBM_COLL_BGK) {
-    if (precision == LBM_FP64) most = forces ? 5.5e5 : 2e5;
-    if (precision == LBM_FP32 || precision == LBM_FP32DEV) most = forces ? 3.5e5 : 2.7e5;
-  }
-  if (nodes > most) return 0;
-  const int strips = (nx + kStripW - 1) / kStripW;
+  // The most blocks of 8 rows, by storage: BGK without and with forces, entropic likewise.
+  constexpr int kMost[4][4] = {
+      {400, 1100, 256, 400}, {480, 480, 256, 400}, {256, 400, 256, 256}, {400, 400, 256, 400}};
+  const int row = storage_row(precision);
+  const bool bgk = collision == LBM_COLL_BGK;
+  const int strips = strips_across(nx), last = nx % kStripW;
+  const int64_t blocks = int64_t(strips) * ((ny + 7) / 8);
+  // A wave of at most 8 lanes takes longer than a full one, and it does here in every step: entropic
+  // binary64 without forces, 192 x 80 4.0 : 3.2, 193 x 80 to 200 x 80 3.9 : 4.8, 201 x 80 3.9 : 3.2.
+  if (row == 0 && !bgk && !forces && strips > 1 && last >= 1 && last <= 8) return 0;
+  int most = kMost[row][(bgk ? 0 : 2) + (forces ? 1 : 0)];
+  // Binary32 gains longer where a body's strips are summed: with forces 724 x 362 (552) without a body
+  // 1.10 of single steps, with a cylinder or an airfoil (8 % of the strips) 0.96 and 0.99, with scattered
+  // solids everywhere 0.73; 1700 x 212 (729) with a cylinder (3 %) 0.91.
+  if (row == 1 && bgk && forces && summed >= 0.025) most = 730;
+  // Binary64 gains up to 2000 blocks where windows do not (37 x 12500 19.4 : 16.0 with forces, 18.1 : 14.2
+  // without, windows 24.5 and 19.7), if the strips are at least half full.
+  if (wide && row == 0 && bgk) most = 2000;
+  if (int64_t(nx) * 2 < int64_t(strips) * kStripW) most = std::min(most, 400);
+  if (blocks > most) return 0;
   return strips * ((ny + 3) / 4) <= 256 ? 4 : 8;
+}
+
+FuseMap step_map(const Plan& p, int precision, int collision, bool forces, int elem_bytes) {
+  const double summed = p.nslots / (double(strips_across(p.nx)) * p.ny);
+  if (const int rows = tile_rows(precision, collision, forces, summed, p.nx, p.ny, false))
+    return tile_map(p, rows);
+  if (collision != LBM_COLL_BGK) return FuseMap{};
+  const FuseMap m = fuse_map(p, elem_bytes, int64_t(p.nx) * p.ny);
+  StepWork w;
+  w.add(p, m, elem_bytes);
+  if (fuse_pays(precision, collision, forces, w)) return m;
+  const int rows = tile_rows(precision, collision, forces, summed, p.nx, p.ny, true);
+  return rows ? tile_map(p, rows) : FuseMap{};
+}
+
+FuseMap keep_map(const Plan& p, int precision, int collision) {
+  // 12 bytes read and 36 written a step and node in binary32, where single steps read 36 as well.
+  // The recomputation for an adjoint run, which is beside the reverse steps, took, single steps :
+  // tiles, in ms of the whole reverse sweep: binary32 1024 x 512 10.9 : 10.5, 2048 x 1024 13.0 :
+  // 12.9, binary64 21.5 : 19.3, 26.2 : 23.7; stochastically rounded 16 x 12000, whose strips are a
+  // quarter full, 6.8 : 7.5.
+  int rows = tile_rows(precision, collision, false, 0.0, p.nx, p.ny, false);
+  const bool full = p.nx * 2 >= strips_across(p.nx) * kStripW;
+  const bool binary32 = precision == LBM_FP32 || precision == LBM_FP32DEV;
+  if (rows == 0 && collision == LBM_COLL_BGK && full &&
+      (precision == LBM_FP64 || (binary32 && double(p.nx) * p.ny <= 1e6)))
+    rows = 8;
+  return rows > 0 ? tile_map(p, rows) : FuseMap{};
 }
 
 FuseMap tile_map(const Plan& p, int rows) {
   FuseMap m{};
   m.tile_rows = rows;
-  m.nblocks = (p.nx + kStripW - 1) / kStripW * ((p.ny + rows - 1) / rows);
+  m.nblocks = strips_across(p.nx) * ((p.ny + rows - 1) / rows);
   return m;
 }
 

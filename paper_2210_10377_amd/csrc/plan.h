@@ -214,12 +214,31 @@ FuseMap fuse_map(const Plan& p, int elem_bytes, int64_t nodes);
 
 // The same for small lattices: one block for every `rows` rows of a strip's columns.
 FuseMap tile_map(const Plan& p, int rows);
-// Rows of its tiles where they are the fastest form for an nx x ny lattice, else 0.
-int tile_rows(int precision, int collision, bool forces, int nx, int ny);
+// Rows of its tiles where they are the fastest form for an nx x ny lattice, else 0.  `summed`: the
+// share of its strips that have force terms to sum; `wide`: windows are not the fastest form.
+int tile_rows(int precision, int collision, bool forces, double summed, int nx, int ny, bool wide);
 
-// Whether fused launches are faster than single steps for `nodes` nodes, the share `body` of
-// them in the body rectangles (of one lattice, or of a batch's lattices together).
-bool fuse_pays(int precision, int collision, double nodes, double body);
+// What a launch has to compute for a lattice, or for those of a batch together, in lanes times
+// rows: by single steps (lanes of strips, idle ones included, and nodes), and by fused launches
+// (rows marched by windows of each kind, margins and idle lanes included).
+struct StepWork {
+  double strips = 0.0, nodes = 0.0;
+  double plain = 0.0, coded = 0.0, body = 0.0;
+  double body_nodes = 0.0;  // nodes of the body rectangles
+  void add(const Plan& p, const FuseMap& m, int elem_bytes);
+};
+
+// Whether fused launches are faster than single steps for it.
+bool fuse_pays(int precision, int collision, bool forces, const StepWork& w);
+// Whether the body rectangles of a batch's fused launches with forces are faster as tiles, in a
+// launch of their own.
+bool batch_tiles_pay(const StepWork& w);
+
+// Work map of the fastest form for steps of p between two alternating buffers: windows or tiles,
+// or a map without blocks for single steps.
+FuseMap step_map(const Plan& p, int precision, int collision, bool forces, int elem_bytes);
+// The same for steps without forces whose states are all kept.
+FuseMap keep_map(const Plan& p, int precision, int collision);
 
 // Node words a mask change rewrites (index, old word, new word), in index order.
 struct PlanDelta {

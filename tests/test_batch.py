@@ -458,3 +458,34 @@ def test_batch_with_tiled_body_rectangles_bitwise_equals_singles(precision):
     for a, c in zip(*runs):
         for x, y in zip(a, c):
             np.testing.assert_array_equal(x, y)
+
+
+@pytest.mark.gpu
+def test_batch_whose_bodies_take_all_of_the_lattices():
+    """Control volumes that span the lattices: with forces every node is in a body rectangle, so
+    the launches of tiles leave the launches of windows nothing but the force rows.  Members
+    bitwise equal to lattices stepped alone, in calls of 3 and 4 steps."""
+    from paper_2210_10377_amd import Batch, Sim
+    nx, ny, n = 512, 256, 60
+    mask = np.zeros((ny, nx), np.uint8)
+    mask[120:130, 150:165] = 1
+    box = (1, nx - 1, 1, ny - 1)
+    rng = np.random.default_rng(17)
+    uin = [0.05 * (1 + 0.1 * rng.uniform(-1, 1, ny)) for _ in range(n)]
+
+    def member(i):
+        return Sim(mask, 0.6 + 0.002 * i, uin[i], precision="fp64", box=box, max_record=8)
+
+    sims = [member(i) for i in range(n)]
+    b = Batch(sims, max_record=8)
+    F = []
+    for k in (3, 4):
+        print(f"batch of whole lattices k={k}", flush=True)
+        b.step(k)
+        F.append(b.forces()[0])
+    for i in (0, 31, n - 1):
+        alone = member(i)
+        for k, f in zip((3, 4), F):
+            alone.step(k)
+            np.testing.assert_array_equal(f[i], alone.forces())
+        np.testing.assert_array_equal(sims[i].populations(), alone.populations())

@@ -219,6 +219,110 @@ def test_tile_kernels_are_those_that_the_rule_can_take():
     assert len(got) == 80 and {g[2] for g in got} == {str(C.LBM_COLL_BGK), str(C.LBM_COLL_KBC)}, sorted(got)
 
 
+# The form that the planner picks for a lattice or a batch of equal ones, each with a small body.
+FORM = r"""
+#include <algorithm>
+#include <cstdio>
+#include <vector>
+#include "plan.h"
+using namespace lbm;
+int main() {
+  int count, nx, ny, precision, collision, forces;
+  while (std::scanf("%d %d %d %d %d %d", &count, &nx, &ny, &precision, &collision, &forces) == 6) {
+    lbm_grid g{};
+    g.nx = nx;
+    g.ny = ny;
+    g.precision = precision;
+    g.collision = collision;
+    g.max_record = 1;
+    for (int k = 0; k < 4; ++k) g.box[k] = -1;
+    std::vector<uint8_t> mask(size_t(nx) * ny, 0);
+    const int w = std::max(1, std::min(12, nx / 6)), h = std::max(1, std::min(12, ny / 6));
+    for (int y = ny / 2; y < ny / 2 + h; ++y)
+      for (int x = nx / 4; x < nx / 4 + w; ++x) mask[size_t(y) * nx + x] = 1;
+    if (nx >= 12 && ny >= 12) {
+      g.box[0] = std::max(1, nx / 4 - 2);
+      g.box[1] = std::min(nx - 1, nx / 4 + w + 2);
+      g.box[2] = std::max(1, ny / 2 - 2);
+      g.box[3] = std::min(ny - 1, ny / 2 + h + 2);
+    }
+    Plan p;
+    std::string err;
+    if (build_plan(g, mask.data(), p, err) != LBM_OK) return 1;
+    const int esz = precision == LBM_FP64 ? 8 : (precision == LBM_FP16DEV ? 2 : 4);
+    if (count == 1) {
+      const FuseMap m = step_map(p, precision, collision, forces != 0, esz);
+      std::printf("%s\n", m.nblocks == 0 ? "single" : (m.tile_rows ? "tiles" : "windows"));
+      continue;
+    }
+    StepWork one, all;
+    one.add(p, fuse_map(p, esz, int64_t(count) * nx * ny), esz);
+    for (int k = 0; k < count; ++k) all.add(p, fuse_map(p, esz, int64_t(count) * nx * ny), esz);
+    if (all.nodes != count * one.nodes || one.nodes != double(nx) * ny) return 1;
+    std::printf("%s\n", fuse_pays(precision, collision, forces != 0, all) ? "windows" : "single");
+  }
+  return 0;
+}
+"""
+# (lattices, columns, rows, storage, collision, forces, form): where one form was measured to be
+# faster than single steps, or slower, by 8 % or more (us a step single : the other form named).
+FORMS = [
+    (1, 16, 40000, "fp64", "bgk", 1, "single"),        # 33 : 51 windows
+    (1, 16, 40000, "fp32", "bgk", 0, "single"),        # 21 : 29 windows
+    (1, 37, 14000, "fp32", "bgk", 1, "single"),        # 15 : 25 windows
+    (1, 64, 100000, "fp32", "bgk", 1, "single"),       # 91 : 129 windows
+    (1, 3, 60000, "fp64", "bgk", 1, "single"),         # 48 : 59 tiles
+    (1, 3, 60000, "fp32", "bgk", 0, "single"),         # 31 : 39 tiles
+    (1, 9, 20000, "fp32", "bgk", 1, "single"),         # 14.6 : 18.0 tiles
+    (1, 16, 12000, "fp32sr", "kbc", 1, "single"),      # 13.4 : 17.7 tiles
+    (1, 3, 60000, "fp16dev", "kbc", 0, "single"),      # 35 : 51 tiles
+    (1, 200, 80, "fp64", "kbc", 0, "single"),          # 4.1 : 4.9 tiles
+    (1, 724, 206, "fp32sr", "kbc", 0, "single"),       # 5.2 : 6.0 tiles
+    (1, 724, 362, "fp32", "kbc", 1, "single"),         # 7.9 : 8.9 tiles
+    (1, 200, 80, "fp64", "bgk", 1, "tiles"),           # 5.2 : 3.4
+    (1, 512, 256, "fp32", "bgk", 0, "tiles"),          # 3.9 : 2.7
+    (1, 512, 256, "fp64", "kbc", 0, "tiles"),          # 5.7 : 4.2
+    (1, 600, 300, "fp32", "bgk", 1, "tiles"),          # 7.5 : 5.8
+    (1, 37, 12500, "fp64", "bgk", 1, "tiles"),         # 19.4 : 16.0
+    (1, 2048, 1024, "fp64", "bgk", 1, "windows"),      # 52 : 29
+    (1, 2048, 1024, "fp32", "bgk", 1, "windows"),      # 27 : 17
+    (1, 8192, 4096, "fp32dev", "bgk", 0, "windows"),   # 390 : 164
+    (1, 100000, 64, "fp32", "bgk", 1, "windows"),      # 80 : 41
+    (1, 20000, 24, "fp64", "bgk", 0, "windows"),       # 14.5 : 6.9
+    (1, 170003, 3, "fp32", "bgk", 0, "windows"),       # 8.5 : 6.5
+    (1, 2200, 1100, "fp32sr", "bgk", 0, "single"),     # 30.6 : 33.3 windows
+    (1, 3000, 1500, "fp16dev", "bgk", 1, "single"),    # 31 : 38 windows
+    (1, 2048, 1024, "fp32", "regularized", 0, "single"),
+    (1000, 64, 32, "fp64", "bgk", 1, "single"),        # 80 : 134 windows
+    (1000, 64, 32, "fp32", "bgk", 0, "single"),        # 30 : 60
+    (300, 64, 64, "fp32", "bgk", 1, "single"),         # 40 : 50
+    (64, 40, 400, "fp64", "bgk", 1, "single"),         # 39 : 52
+    (300, 33, 100, "fp32", "bgk", 1, "single"),        # 37 : 50
+    (128, 96, 64, "fp32", "bgk", 0, "single"),         # 14.4 : 16.8
+    (16, 400, 200, "fp32", "bgk", 0, "windows"),       # 19.1 : 14.3
+    (8, 700, 350, "fp64", "bgk", 1, "windows"),        # 54 : 33
+    (128, 96, 64, "fp64", "bgk", 0, "windows"),        # 26.4 : 22.4
+]
+
+
+def test_form_goes_by_the_work_that_a_shape_leaves(tmp_path):
+    """Narrow lattices, lattices that are all edges and batches of small members take the form
+    that is faster for them: node counts alone do not tell."""
+    from paper_2210_10377_amd.sim import COLLISIONS, PRECISIONS
+    src = tmp_path / "form.cpp"
+    src.write_text(FORM)
+    exe = tmp_path / "form"
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-I", CSRC, "-I", os.path.join(ROOT, "include"),
+                           str(src), os.path.join(CSRC, "plan.cpp"), "-o", str(exe)])
+    lines = "".join("%d %d %d %d %d %d\n" % (n, nx, ny, PRECISIONS[p], COLLISIONS[c], f)
+                    for n, nx, ny, p, c, f, _ in FORMS)
+    out = subprocess.run([str(exe)], input=lines, capture_output=True, text=True, timeout=120)
+    got = out.stdout.split()
+    assert out.returncode == 0 and len(got) == len(FORMS)
+    wrong = [(case, form) for case, form in zip(FORMS, got) if case[-1] != form]
+    assert not wrong, wrong
+
+
 def _case(name):
     z = lambda nx, ny: np.zeros((ny, nx), np.uint8)  # noqa: E731
     if name == "airfoil":            # 725 x 701, the box inside the grid
