@@ -139,6 +139,7 @@ int enqueue3(lbm3d* h, int32_t n, double* ring) {
   a.collision = h->g.collision;
   a.nslots = p.nslots;
   a.njslots = p.njslots;
+  a.joined = forces && join_forces(p, h->g.precision);
   const int c0 = h->cur;
   for (int32_t k = 0; k < n; ++k) {
     const int s = (c0 + k) & 1;

@@ -40,7 +40,8 @@ struct Step3Args {
   int32_t collision;         // LBM_COLL_BGK or LBM_COLL_REGULARIZED
   int32_t nslots, njslots;   // force slots (15 doubles), J slots (3 doubles)
   double* part_out;          // partials of this step: [nslots][15] then [njslots][3]
-  int32_t force_blocks;      // blocks of the strips with force slots (set at launch)
+  int32_t joined;            // the strips with force slots run in the step's launch
+  int32_t force_blocks;      // their blocks there (set at launch)
   // Reducer (last block of the launch): the previous step's partials into its ring row,
   // and its J into the J(t+1) of the row before.
   const double* red_in;

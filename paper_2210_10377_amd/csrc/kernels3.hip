@@ -823,27 +823,12 @@ __global__ __launch_bounds__(kThreads) void fill_rest3_kernel(void* buf, int64_t
   }
 }
 
-// Whether the strips with force terms join the step's launch.  That saves a launch and hides
-// them behind the other strips, but leaves those three waves a SIMD instead of six or seven,
-// too few to keep HBM busy with binary16 loads or behind the stochastic rounding.  Measured on
-// grids with a sphere, joined against apart, in us a step: binary32 64 x 32 x 32 11.0 : 18.3,
-// 200 x 100 x 100 93 : 98, 1280 x 128 x 64 389 : 405; binary64 12 : 20, 157 : 167, 790 : 812;
-// stochastically rounded 128 x 65 x 64 35.8 : 36.4, 200 x 100 x 100 108 : 101; binary16
-// 96 x 48 x 48 17.2 : 22.1, 128 x 65 x 64 28.6 : 27.2, 1280 x 128 x 64 270 : 205.
-bool join3(int precision, int64_t nodes) {
-  switch (precision) {
-    case LBM_FP32SR: return nodes <= 1000000;
-    case LBM_FP16DEV: return nodes <= 400000;
-    default: return true;
-  }
-}
-
 template <int P, int COLL, bool MOV>
 hipError_t step_pcm(bool forces, Step3Args a, hipStream_t s) {
   const int64_t tiles = (a.ntiles + 8 * kXcdRun - 1) / (8 * kXcdRun) * (8 * kXcdRun);
   // Whole rounds over the XCDs, so that the tile blocks keep their alignment.
   const int force_blocks = (a.nslots + kStrips * 8 - 1) / (kStrips * 8) * 8;
-  const bool joined = forces && join3(P, int64_t(a.g.nx) * a.g.ny * a.g.nz);
+  const bool joined = forces && a.joined;
   a.force_blocks = joined ? force_blocks : 0;
   const dim3 grid(unsigned(tiles + a.force_blocks + (a.red_in ? 8 : 0)));
   if (joined) {

@@ -279,6 +279,32 @@ int build_plan3(const lbm3d_grid& g, const uint8_t* mask, Plan3& p, std::string&
   return LBM_OK;
 }
 
+bool join_forces(const Plan3& p, int precision) {
+  // Joined they save a launch (`start`, in us) and hide behind the other strips, but leave those
+  // three waves a SIMD instead of six or seven: too few to hide the latency of the general path, nor of
+  // binary16 loads (us saved for a thousand strips with force terms, and streaming ones, and lost
+  // for a thousand other general ones; binary64 loses nothing there).  Fitted to 90 lattices for each
+  // row, 12 x 12 x 12 to 1280 x 128 x 64 and 20 x 20 x 1500, with spheres, single solid nodes,
+  // scattered ones and control volumes of the whole lattice; the choice is on average 0.2 - 0.5 %
+  // slower than the better one.  Joined against apart in us a step: binary32 64 x 32 x 32 with a sphere
+  // 13.8 : 23.5, 200 x 100 x 100 94 : 99, 1280 x 128 x 64 388 : 403, 64 x 160 x 160 (all strips general)
+  // 100 : 73, 20 x 20 x 1500 110 : 72, 65 x 65 x 65 without force terms 27.7 : 20.1; binary64 13.8 : 24.5,
+  // 158 : 169, 789 : 809; stochastically rounded 200 x 100 x 100 108 : 102, 64 x 160 x 160 105 : 78;
+  // binary16 96 x 48 x 48 18.4 : 26.7, 128 x 65 x 64 29.1 : 28.2, 1280 x 128 x 64 270 : 206.
+  if (p.nslots == 0) return false;
+  double start = 0.0, edge = 0.0, plain = 0.0, slot = 0.0;
+  switch (precision) {
+    case LBM_FP64: return true;
+    case LBM_FP32:
+    case LBM_FP32DEV: start = 5.8, edge = 0.76, plain = 0.48, slot = 1.42; break;
+    case LBM_FP32SR: start = 6.4, edge = 0.81, plain = 0.31, slot = 1.54; break;
+    default: start = 6.1, edge = 1.02, plain = -0.28, slot = 1.71;
+  }
+  const double strips = double((p.nx + kStripW - 1) / kStripW) * p.ny * p.nz;
+  return start + 1e-3 * (slot * p.nslots + plain * (strips - p.ngeneral) -
+                         edge * (p.ngeneral - p.nslots)) > 0.0;
+}
+
 int replan3(const lbm3d_grid& g, const uint8_t* mask, const std::vector<int32_t>& changed,
             Plan3& p, Plan3& np, Plan3Delta& d, std::string& err) {
   int64_t nsolid = 0;

@@ -62,6 +62,9 @@ struct Plan3 {
 
 int build_plan3(const lbm3d_grid& g, const uint8_t* mask, Plan3& p, std::string& err);
 
+// Whether the strips with force terms are faster in the step's own launch than in one of theirs.
+bool join_forces(const Plan3& p, int precision);
+
 // Node words a mask change rewrites (index, old word, new word), in index order.
 struct Plan3Delta {
   std::vector<int64_t> idx;

@@ -310,3 +310,64 @@ def test_parameter_and_state_calls_validate_without_a_gpu(capi):
     assert L.lbm3d_get_state(h, buf, n.value) == capi.LBM_ESTATE
     assert L.lbm3d_set_state(h, buf, n.value) == capi.LBM_ESTATE
     assert L.lbm3d_reset(h) == capi.LBM_ESTATE
+
+
+JOIN = r"""
+#include <cstdio>
+#include <vector>
+#include "plan3.h"
+using namespace lbm3;
+int main() {
+  int nx, ny, nz, kind, precision;
+  while (std::scanf("%d %d %d %d %d", &nx, &ny, &nz, &kind, &precision) == 5) {
+    lbm3d_grid g{};
+    g.nx = nx;
+    g.ny = ny;
+    g.nz = nz;
+    g.precision = precision;
+    g.max_record = 1;
+    for (int k = 0; k < 6; ++k) g.box[k] = -1;
+    std::vector<uint8_t> mask(size_t(nx) * ny * nz, 0);
+    if (kind)  // a cube in a control volume
+      for (int z = nz / 2 - 2; z < nz / 2 + 2; ++z)
+        for (int y = ny / 2 - 2; y < ny / 2 + 2; ++y)
+          for (int x = nx / 3; x < nx / 3 + 4; ++x) mask[(size_t(z) * ny + y) * nx + x] = 1;
+    if (kind) {
+      const int b[6] = {nx / 3 - 1, nx / 3 + 5, ny / 2 - 3, ny / 2 + 3, nz / 2 - 3, nz / 2 + 3};
+      for (int k = 0; k < 6; ++k) g.box[k] = b[k];
+    }
+    Plan3 p;
+    std::string err;
+    if (build_plan3(g, mask.data(), p, err) != LBM_OK) return 1;
+    std::printf("%d\n", join_forces(p, precision) ? 1 : 0);
+  }
+  return 0;
+}
+"""
+# (nx, ny, nz, with a body, storage, joined): joined and apart measured 8 % apart or more.
+JOINS = [
+    (65, 65, 65, 0, "fp32", 0), (65, 65, 65, 0, "fp32sr", 0), (40, 100, 100, 0, "fp64", 0),
+    (20, 40, 40, 0, "fp16dev", 0), (128, 128, 100, 0, "fp32", 0),       # no force terms at all
+    (64, 160, 160, 1, "fp32", 0), (20, 20, 1500, 1, "fp32", 0),         # every strip general
+    (64, 160, 160, 1, "fp32sr", 0), (64, 160, 160, 1, "fp16dev", 0), (200, 100, 100, 1, "fp16dev", 0),
+    (64, 32, 32, 1, "fp32", 1), (64, 32, 32, 1, "fp64", 1), (20, 40, 40, 1, "fp32sr", 1),
+    (96, 48, 48, 1, "fp16dev", 1), (256, 64, 64, 1, "fp32dev", 1), (500, 40, 40, 1, "fp32sr", 1),
+]
+
+
+def test_force_strips_join_the_launch_where_that_is_faster(tmp_path):
+    """What joining costs the other strips goes by their classes, not by the number of nodes; a
+    lattice without force terms has nothing to join."""
+    from paper_2210_10377_amd.sim import PRECISIONS
+    csrc = os.path.join(ROOT, "paper_2210_10377_amd", "csrc")
+    src = tmp_path / "join.cpp"
+    src.write_text(JOIN)
+    exe = tmp_path / "join"
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-I", csrc, "-I", os.path.join(ROOT, "include"),
+                           str(src), os.path.join(csrc, "plan3.cpp"), "-o", str(exe)])
+    lines = "".join("%d %d %d %d %d\n" % (*c[:4], PRECISIONS[c[4]]) for c in JOINS)
+    out = subprocess.run([str(exe)], input=lines, capture_output=True, text=True, timeout=120)
+    got = [int(v) for v in out.stdout.split()]
+    assert out.returncode == 0 and len(got) == len(JOINS)
+    wrong = [(c, j) for c, j in zip(JOINS, got) if c[5] != j]
+    assert not wrong, wrong

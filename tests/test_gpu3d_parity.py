@@ -356,3 +356,30 @@ def test_force_strips_joined_and_apart(precision, shape):
     tol = {"fp64": np.full(4, TOL64), "fp16dev": np.full(4, 5e-2)}.get(
         precision, np.array([2e-4, 2e-4, 1e-2, 1e-3]))
     assert np.all(e <= tol), e
+
+
+@pytest.mark.parametrize("precision,shape", [("fp32", (60, 110, 110)), ("fp32dev", (60, 110, 110)),
+                                             ("fp32sr", (60, 110, 110)), ("fp16dev", (60, 90, 90)),
+                                             ("fp16dev", (200, 71, 70))])
+def test_force_strips_apart_where_other_strips_are_general(precision, shape):
+    """Lattices of one strip a row, all of whose strips take the general path, and a wide one in
+    binary16, where the strips with force terms keep a launch of their own (a lattice of 60 x 40
+    x 40, which joins them, is the other side): two steps of a random state against the oracle,
+    with the tolerances of the test above."""
+    for nx, ny, nz in (shape, (60, 40, 40)):
+        mask = d3.sphere_mask(nx, ny, nz, 0.4 * nx, ny / 2, nz / 2, 6.3)
+        c = (int(0.4 * nx), ny // 2, nz // 2)
+        box = tuple(v for m in c for v in (m - 10, m + 11))
+        S0 = d3.near_rest_state3(nx, ny, nz, seed=8, amp=0.02, dtype=np.float32)
+        sims = [_sim3(mask, 0.56, 0.04, precision=precision, box=box, max_record=4) for _ in range(2)]
+        for g, schemes in zip(sims, (None, ())):
+            g.set_populations(S0)
+            g.step(2, **({} if schemes is None else {"schemes": schemes}))
+        np.testing.assert_array_equal(sims[0].populations(), sims[1].populations())
+        o = D.OracleSim3(mask, tau=0.56, uin=np.full((nz, ny), 0.04), box=box)
+        o.set_state(S0)
+        o.step(2)
+        e = _force_err(sims[0].forces(), o.forces())
+        print(precision, (nx, ny, nz), "force errors", e, flush=True)
+        tol = np.full(4, 5e-2) if precision == "fp16dev" else np.array([2e-4, 2e-4, 1e-2, 1e-3])
+        assert np.all(e <= tol), e
