@@ -471,10 +471,12 @@ int lbm_batch_set_schedule(lbm_batch_t* b, const lbm_batch_schedule* s);
  * direct launches and with graphs of up to 64 launches; the tile order seed and the
  * tile shape are kept; then the fastest of those with each of the two other tile
  * shapes) over `steps` steps each, after a warm-up run of the same length, with forces
- * force_scheme (0 = none).  Keeps the fastest and returns it in *best and its
- * milliseconds per step in *ms_per_step (either may be NULL).  Every instance advances
- * by 2 x steps per candidate (40 x steps in all: 18 schedules, then 2 tile shapes);
- * those force rows are not kept.
+ * force_scheme (0 = none).  The steps are taken in launches of one step, which are what a
+ * schedule governs: in a batch that takes three steps a launch, calls of one or two steps
+ * and the steps left over.  Keeps the fastest and returns it in *best and its
+ * milliseconds per such step in *ms_per_step (either may be NULL).  Every instance
+ * advances by 2 x steps per candidate (40 x steps in all: 18 schedules, then 2 tile
+ * shapes); those force rows are not kept.
  * LBM_EOVERFLOW if the ring cannot hold `steps` rows beside the rows recorded;
  * LBM_ESTATE if a member's control volume changed size since create.  Synchronises the
  * stream. */
@@ -495,6 +497,11 @@ int lbm_batch_forces(lbm_batch_t* b, double* out, int64_t cap, int64_t* k_out,
                      uint8_t* nonfinite);
 
 int lbm_batch_get_info(const lbm_batch_t* b, lbm_batch_info* info);
+
+/* What the batch has enqueued so far, autotuning included: *single_steps the steps taken in
+ * launches of one step (directly or in graphs), *fused the launches of three steps (either
+ * may be NULL). */
+int lbm_batch_launches(const lbm_batch_t* b, int64_t* single_steps, int64_t* fused);
 
 /* Free the batch's host state, graphs and private stream (not the members). */
 int lbm_batch_destroy(lbm_batch_t* b);

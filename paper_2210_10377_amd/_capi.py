@@ -35,7 +35,7 @@ EXPORTS = ("lbm_create", "lbm_workspace_bytes", "lbm_bind", "lbm_step", "lbm_for
            "lbm_set_body_motion", "lbm_set_mask", "lbm_boundary_cp", "lbm_step_static",
            "lbm_batch_create", "lbm_batch_workspace_bytes", "lbm_batch_bind",
            "lbm_batch_set_schedule", "lbm_batch_autotune", "lbm_batch_step",
-           "lbm_batch_forces", "lbm_batch_get_info", "lbm_batch_destroy",
+           "lbm_batch_forces", "lbm_batch_get_info", "lbm_batch_launches", "lbm_batch_destroy",
            "lbm_batch_last_error")
 
 # Every entry point of include/lbm3d.h.
@@ -158,6 +158,7 @@ def load():
     L.lbm_batch_forces.argtypes = [vp, dp, i64, ctypes.POINTER(i64),
                                    ctypes.POINTER(ctypes.c_uint8)]
     L.lbm_batch_get_info.argtypes = [vp, ctypes.POINTER(lbm_batch_info)]
+    L.lbm_batch_launches.argtypes = [vp, ctypes.POINTER(i64), ctypes.POINTER(i64)]
     L.lbm_batch_destroy.argtypes = [vp]
     L.lbm_batch_last_error.argtypes = [vp]
     L.lbm_batch_last_error.restype = ctypes.c_char_p

@@ -1,6 +1,6 @@
-"""Batched stepping of many independent lattices (one kernel launch per step for all of
-them, optionally replayed from captured HIP graphs), over the C ABI's lbm_batch_*
-calls.  Every instance computes exactly what ``Sim.step`` computes for it."""
+"""Batched stepping of many independent lattices (one kernel launch per step, or per three
+steps, for all of them; the former optionally replayed from captured HIP graphs), over the C
+ABI's lbm_batch_* calls.  Every instance computes exactly what ``Sim.step`` computes for it."""
 from __future__ import annotations
 
 import ctypes
@@ -73,8 +73,9 @@ class Batch:
         C.check_batch(self._lib.lbm_batch_set_schedule(self._h, ctypes.byref(s)), self._h)
 
     def autotune(self, steps: int = 10, schemes=ALL_SCHEMES):
-        """Time the candidate schedules (each advances every instance by 2 x steps) and
-        keep the fastest; returns (schedule dict, milliseconds per step)."""
+        """Time the candidate schedules (each advances every instance by 2 x steps) on launches
+        of one step, which they govern, and keep the fastest; returns (schedule dict,
+        milliseconds per such step)."""
         best = C.lbm_batch_schedule()
         ms = ctypes.c_double()
         C.check_batch(self._lib.lbm_batch_autotune(self._h, int(steps), scheme_mask(schemes),
@@ -88,6 +89,13 @@ class Batch:
         inf = C.lbm_batch_info()
         C.check_batch(self._lib.lbm_batch_get_info(self._h, ctypes.byref(inf)), self._h)
         return inf
+
+    def launches(self) -> tuple[int, int]:
+        """(steps taken in launches of one step, launches of three steps) so far."""
+        one, three = ctypes.c_int64(), ctypes.c_int64()
+        C.check_batch(self._lib.lbm_batch_launches(self._h, ctypes.byref(one), ctypes.byref(three)),
+                      self._h)
+        return one.value, three.value
 
     # -- stepping ---------------------------------------------------------------------
     def step(self, n: int, schemes=ALL_SCHEMES):

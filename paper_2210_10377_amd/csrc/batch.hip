@@ -76,6 +76,7 @@ struct lbm_batch_t {
   // (launches, parity, forces, some body in motion): the last selects the kernel variant
   std::map<std::tuple<int, int, int, int>, hipGraphExec_t> graphs;
   int64_t nrec = 0, steps_done = 0;
+  int64_t single_steps = 0, fused_launches = 0;  // taken so far, by form
   std::vector<uint32_t> rec_scheme;
   std::string err;
 
@@ -392,8 +393,8 @@ struct lbm_batch_t {
   }
 
   // Enqueue n >= 1 steps of every instance; with forces, step k's row goes to ring row
-  // row0 + k of every instance.
-  int enqueue(int32_t n, bool forces, int64_t row0) {
+  // row0 + k of every instance.  `scheduled`: all of them by the schedule.
+  int enqueue(int32_t n, bool forces, int64_t row0, bool scheduled = false) {
     int rc = refresh();
     if (rc != LBM_OK) return rc;
     const BatchLaunch L = launch();
@@ -404,7 +405,7 @@ struct lbm_batch_t {
     }
     // Single steps by the schedule (all of them, or what is left over kFuse), then the fused
     // launches, which have an order of their own.
-    const int32_t singles = fuse[forces ? 1 : 0] && n >= kFuse ? n % kFuse : n;
+    const int32_t singles = fuse[forces ? 1 : 0] && n >= kFuse && !scheduled ? n % kFuse : n;
     int32_t done = 0;
     while (done < singles) {
       const int len = G > 0 ? std::min<int32_t>(G, singles - done) : singles - done;
@@ -482,6 +483,8 @@ struct lbm_batch_t {
       h->adj_valid = false;
     }
     steps_done += n;
+    single_steps += singles;
+    fused_launches += (n - singles) / kFuse;
     // The table is unchanged: buf[bpar] is again every member's current buffer.
     return LBM_OK;
   }
@@ -676,14 +679,15 @@ int lbm_batch_autotune(lbm_batch_t* b, int32_t steps, uint32_t force_scheme,
   const lbm_batch_schedule keep = b->sched;
   lbm_batch_schedule win = keep;
   double win_ms = INFINITY;
-  // Warm-up of the same length (captures the graphs), then the timed run.
+  // Warm-up of the same length (captures the graphs), then the timed run, both in launches of one
+  // step: those of three steps are the same whatever the schedule.
   auto time_candidate = [&](const lbm_batch_schedule& s) -> int {
     b->drop_graphs();
     int r = b->use_schedule(s);
-    if (r == LBM_OK) r = b->enqueue(steps, forces, b->nrec);
+    if (r == LBM_OK) r = b->enqueue(steps, forces, b->nrec, true);
     if (r != LBM_OK) return r;
     e = hipEventRecord(e0, b->stream);
-    if (e == hipSuccess) r = b->enqueue(steps, forces, b->nrec);
+    if (e == hipSuccess) r = b->enqueue(steps, forces, b->nrec, true);
     if (r != LBM_OK) return r;
     if (e == hipSuccess) e = hipEventRecord(e1, b->stream);
     if (e == hipSuccess) e = hipEventSynchronize(e1);
@@ -779,6 +783,13 @@ int lbm_batch_get_info(const lbm_batch_t* b, lbm_batch_info* info) {
   info->n_graphs = int32_t(b->graphs.size());
   info->compute_units = b->cus;
   info->schedule = b->sched;
+  return LBM_OK;
+}
+
+int lbm_batch_launches(const lbm_batch_t* b, int64_t* single_steps, int64_t* fused) {
+  if (!b) return LBM_EINVAL;
+  if (single_steps) *single_steps = b->single_steps;
+  if (fused) *fused = b->fused_launches;
   return LBM_OK;
 }
 

@@ -11,6 +11,7 @@ import numpy as np
 import pytest
 
 import workloads
+from paper_2210_10377_amd.sim import ALL_SCHEMES
 from oracle import OracleSim
 
 pytestmark = pytest.mark.gpu
@@ -489,3 +490,24 @@ def test_batch_whose_bodies_take_all_of_the_lattices():
             alone.step(k)
             np.testing.assert_array_equal(f[i], alone.forces())
         np.testing.assert_array_equal(sims[i].populations(), alone.populations())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("schemes", [ALL_SCHEMES, ()])
+def test_autotune_times_what_the_schedule_governs(schemes):
+    """In a batch that takes three steps a launch the candidates are timed on launches of one
+    step: the others are the same whatever the schedule.  Results stay those of 40 x 9 steps."""
+    from paper_2210_10377_amd import Batch
+    ws = workloads.batched_instances(28, seed=13)
+    b = Batch.from_workloads(ws, precision="fp64", max_record=24)
+    b.step(7, schemes)
+    assert b.launches() == (1, 2)
+    _, ms = b.autotune(steps=9, schemes=() if not schemes else ("A",))
+    assert b.launches() == (1 + 40 * 9, 2) and ms > 0
+    b.step(6, schemes)
+    assert b.launches() == (1 + 40 * 9, 4)
+    assert b.info().steps_done == 7 + 40 * 9 + 6
+    for i in (0, 13, 27):
+        alone = Batch.from_workloads([ws[i]], precision="fp64", max_record=12).members[0]
+        alone.step(7 + 40 * 9 + 6, schemes=())
+        np.testing.assert_array_equal(b.members[i].populations(), alone.populations())
