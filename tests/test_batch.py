@@ -511,3 +511,150 @@ def test_autotune_times_what_the_schedule_governs(schemes):
         alone = Batch.from_workloads([ws[i]], precision="fp64", max_record=12).members[0]
         alone.step(7 + 40 * 9 + 6, schemes=())
         np.testing.assert_array_equal(b.members[i].populations(), alone.populations())
+
+
+@pytest.fixture(scope="module")
+def few_singles():
+    return _singles(MINI[:4], CALLS)
+
+
+@pytest.mark.parametrize("name", list(SCHEDULES))
+def test_schedules_of_a_batch_of_single_steps(name, few_singles):
+    """Every schedule on a batch that takes all of its steps in launches of one step, replaying
+    whole graphs and reducing each row in the launch after it."""
+    ws = MINI[:4]
+    b = _batch(ws)
+    _seed_states(b.members, ws)
+    b.set_schedule(**SCHEDULES[name])
+    F = []
+    for n in CALLS:
+        b.step(n)
+        Fi, bad = b.forces()
+        assert not bad.any()
+        F.append(Fi)
+    assert b.launches() == (sum(CALLS), 0)
+    F = np.concatenate(F, axis=1)
+    ps, fs = few_singles
+    _assert_same(ps, fs, [m.populations() for m in b.members], [F[i] for i in range(len(ws))])
+
+
+def test_many_members_of_single_steps_with_a_persistent_schedule():
+    """Sixty-four lattices rounded stochastically, which take single steps: a persistent grid,
+    graphs of four launches and a shuffled list."""
+    ws = workloads.batched_instances(64)
+    from paper_2210_10377_amd import Batch
+    b = Batch.from_workloads(ws, precision="fp32sr", max_record=16)
+    b.set_schedule(grid_blocks=1024, graph_steps=4, tile_order=7)
+    b.step(10)
+    F, bad = b.forces()
+    assert not bad.any() and b.launches() == (10, 0)
+    for i in (0, 17, 40, 63):
+        r = _members([ws[i]], "fp32sr")[0]
+        r.step(10)
+        np.testing.assert_array_equal(r.forces(), F[i])
+        np.testing.assert_array_equal(r.populations(), b.members[i].populations())
+
+
+def _box_around(mask, grow):
+    ys, xs = np.nonzero(mask.any(1))[0], np.nonzero(mask.any(0))[0]
+    return int(xs[0]) - grow, int(xs[-1]) + 1 + grow, int(ys[0]) - grow, int(ys[-1]) + 1 + grow
+
+
+def _odd_members(precision):
+    """Lattices of all kinds and boundaries in one batch: two that make launches of three steps
+    worth taking, and narrow, thin, tiny and full ones."""
+    from paper_2210_10377_amd import Sim
+    rng = np.random.default_rng(23)
+    sims = []
+    shapes = [(900, 700), (251, 300), (203, 201), (500, 3), (3, 400), (37, 300), (5, 5), (64, 64), (65, 90),
+              (130, 17), (111, 130), (200, 120), (1501, 803)]
+    for i, (nx, ny) in enumerate(shapes):
+        mask = np.zeros((ny, nx), np.uint8)
+        box, bc = None, (0, 0)
+        if i == 0:
+            mask[300:330, 200:260] = 1
+            box = _box_around(mask, 20)
+        elif i == 1:  # at the outlet, at a wall and across the wrap
+            mask[100:120, nx - 1] = 1
+            mask[0:3, 90:100] = 1
+            bc = (0, 1)
+        elif i == 2:
+            mask[5:9, 0:2] = 1
+            bc = (1, 0)
+        elif i == 8:
+            mask[20:25, 30:34] = 1
+            box = (1, nx - 1, 1, ny - 1)  # every node has force terms
+        elif i == 10:  # scattered solids
+            mask[4:-4, 4:-4] = rng.uniform(size=(ny - 8, nx - 8)) < 0.05
+            bc = (1, 1)
+        elif min(nx, ny) >= 17:
+            mask[ny // 2:ny // 2 + 3, nx // 3:nx // 3 + 4] = 1
+            box = _box_around(mask, 2)
+        uin = 0.05 * (1 + 0.1 * rng.uniform(-1, 1, ny))
+        s = Sim(mask, 0.55 + 0.01 * i, uin, precision=precision, bc_x=bc[0], bc_y=bc[1], box=box, max_record=16)
+        s.set_populations(workloads.NEAR_REST_BASE[:, None, None] * (
+            1 + 0.02 * rng.uniform(-1, 1, (9, ny, 1)) * rng.uniform(-1, 1, (9, 1, nx))))
+        if i in (0, 11):
+            s.set_body_motion(ux=0.004, omega=1e-4, xc=nx / 3, yc=ny / 2)
+        sims.append(s)
+    return sims
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "fp32dev"])
+@pytest.mark.parametrize("schemes", [ALL_SCHEMES, ()])
+def test_odd_members_in_launches_of_three_steps(precision, schemes):
+    """Every member bitwise equal to itself in single steps (DRTT of a call's last step to the
+    rounding of the sum over its box)."""
+    from paper_2210_10377_amd import Batch
+    sims, ref = _odd_members(precision), _odd_members(precision)
+    b = Batch(sims, max_record=16)
+    b.step(7, schemes)
+    assert b.launches() == (1, 2)
+    F = b.forces()[0] if schemes else None
+    for i, (s, r) in enumerate(zip(sims, ref)):
+        for n in (2, 2, 2, 1):
+            r.step(n, schemes)
+        np.testing.assert_array_equal(s.populations(), r.populations(), err_msg=f"member {i}")
+        if schemes:
+            Fr = r.forces()
+            np.testing.assert_array_equal(F[i][:, [0, 1, 3]], Fr[:, [0, 1, 3]], err_msg=f"member {i}")
+            if i in (0, 8):
+                box = (1, 64, 1, 89) if i == 8 else (180, 280, 280, 350)
+                N = (box[1] - box[0]) * (box[3] - box[2]) * 9
+                assert np.abs(F[i] - Fr).max() <= 4 * N * 0.45 * 2.0 ** -53
+
+
+@pytest.mark.parametrize("precision,nx,ny", [("fp32sr", 2803, 801), ("fp16dev", 3003, 2001)])
+def test_large_members_of_the_other_storages_in_launches_of_three_steps(precision, nx, ny):
+    """Stochastically rounded and binary16 lattices large enough for launches of three steps, one
+    with a control volume of 1.2e5 nodes (which takes tiles with forces), without forces and with
+    them: bitwise those of single steps."""
+    from paper_2210_10377_amd import Batch, Sim
+
+    def members():
+        rng = np.random.default_rng(29)
+        sims = []
+        for i in range(3):
+            mask = np.zeros((ny, nx), np.uint8)
+            mask[ny // 2 - 20:ny // 2 + 20, 600:660] = 1
+            box = (500, 900, ny // 2 - 150, ny // 2 + 150) if i == 0 else (590, 670, ny // 2 - 30, ny // 2 + 30)
+            s = Sim(mask, 0.55 + 0.01 * i, np.full(ny, 0.05), precision=precision, box=box, max_record=8)
+            if i < 2:
+                s.set_populations(workloads.NEAR_REST_BASE[:, None, None] * (
+                    1 + 0.02 * rng.uniform(-1, 1, (9, ny, 1)) * rng.uniform(-1, 1, (9, 1, nx))))
+            sims.append(s)
+        return sims
+
+    sims, ref = members(), members()
+    b = Batch(sims, max_record=8)
+    b.step(4, ())
+    print(f"large members {precision}: without forces", flush=True)
+    b.step(3, ALL_SCHEMES)
+    print(f"large members {precision}: with forces", flush=True)
+    assert b.launches() == (1, 2)
+    F = b.forces()[0]
+    for i, (s, r) in enumerate(zip(sims, ref)):
+        for n, sch in ((2, ()), (2, ()), (2, ALL_SCHEMES), (1, ALL_SCHEMES)):
+            r.step(n, sch)
+        np.testing.assert_array_equal(F[i][:, [0, 1, 3]], r.forces()[:, [0, 1, 3]], err_msg=f"member {i}")
+        np.testing.assert_array_equal(s.populations(), r.populations(), err_msg=f"member {i}")

@@ -437,3 +437,117 @@ def test_tiles_bitwise_equal_single_steps(precision, bc_x, bc_y, collision, spin
         if box is not None:
             N = (box[1] - box[0]) * (box[3] - box[2]) * 9
             assert np.abs(F0 - F1).max() <= 4 * N * 0.45 * 2.0 ** -53
+
+
+def _small_body(nx, ny):
+    """The body and control volume of FORM's lattices."""
+    mask = np.zeros((ny, nx), np.uint8)
+    w, h = max(1, min(12, nx // 6)), max(1, min(12, ny // 6))
+    mask[ny // 2:ny // 2 + h, nx // 4:nx // 4 + w] = 1
+    if nx < 12 or ny < 12:
+        return mask, None
+    return mask, (max(1, nx // 4 - 2), min(nx - 1, nx // 4 + w + 2),
+                  max(1, ny // 2 - 2), min(ny - 1, ny // 2 + h + 2))
+
+
+# Lattices that FORM's rule gives to windows, without forces and with them.
+WINDOWS = [("fp64", 725, 701, 0), ("fp32", 725, 701, 0), ("fp32dev", 726, 703, 0), ("fp64", 1203, 605, 1),
+           ("fp32", 1203, 605, 1), ("fp32", 170003, 3, 0), ("fp64", 20001, 24, 0), ("fp32sr", 2803, 1499, 0),
+           ("fp32sr", 2803, 1499, 1), ("fp16dev", 6007, 2501, 0)]
+# And to tiles: storage, collision, columns, rows, forces.
+TILES = [(p, c, nx, ny, f) for p in ("fp64", "fp32", "fp32dev", "fp32sr", "fp16dev") for c in ("bgk", "kbc")
+         for nx, ny in ((131, 17), (333, 60), (430, 250)) for f in (0, 1)]
+
+
+def test_window_and_tile_cases_take_their_forms(tmp_path):
+    """The lattices of the two tests below, by the planner's own rule."""
+    from paper_2210_10377_amd.sim import COLLISIONS, PRECISIONS
+    src = tmp_path / "form.cpp"
+    src.write_text(FORM)
+    exe = tmp_path / "form"
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-I", CSRC, "-I", os.path.join(ROOT, "include"),
+                           str(src), os.path.join(CSRC, "plan.cpp"), "-o", str(exe)])
+    cases = [(1, nx, ny, PRECISIONS[p], 0, f, "windows") for p, nx, ny, f in WINDOWS]
+    cases += [(1, nx, ny, PRECISIONS[p], COLLISIONS[c], f, "tiles") for p, c, nx, ny, f in TILES
+              if not (p == "fp64" and c == "kbc" and not f and 1 <= nx % 64 <= 8)]
+    out = subprocess.run([str(exe)], input="".join("%d %d %d %d %d %d\n" % c[:6] for c in cases),
+                         capture_output=True, text=True, timeout=120)
+    got = out.stdout.split()
+    wrong = [(c, g) for c, g in zip(cases, got) if c[6] != g]
+    assert len(got) == len(cases) and not wrong, wrong
+
+
+def _runs(precision, collision, nx, ny, bc, forces, spin, seed):
+    """Populations and forces of 7 steps in one call and in calls of 2, 2, 2 and 1."""
+    from paper_2210_10377_amd import Sim
+    rng = np.random.default_rng(seed)
+    mask, box = _small_body(nx, ny)
+    uin = 0.05 * (1 + 0.1 * rng.uniform(-1, 1, ny))
+    S = workloads.NEAR_REST_BASE[:, None, None] * (
+        1 + 0.02 * rng.uniform(-1, 1, (9, ny, 1)) * rng.uniform(-1, 1, (9, 1, nx)))
+    runs = []
+    for calls in ([7], [2, 2, 2, 1]):
+        print(f"{precision} {collision} {nx}x{ny} bc {bc} forces {forces} spin {spin} {calls}", flush=True)
+        sim = Sim(mask, 0.55, uin, precision=precision, bc_x=bc[0], bc_y=bc[1], box=box, max_record=7,
+                  collision=collision)
+        sim.set_populations(S)
+        if spin:
+            sim.set_body_motion(ux=0.01, omega=1e-4, xc=nx / 3, yc=ny / 2)
+        for k in calls:
+            sim.step(k) if forces else sim.step(k, schemes=())
+        runs.append((sim.populations(), sim.forces() if forces else None))
+        del sim
+    (P0, F0), (P1, F1) = runs
+    np.testing.assert_array_equal(P0, P1)
+    if forces:  # (DRTT as in the tests above)
+        np.testing.assert_array_equal(F0[:, [0, 1, 3]], F1[:, [0, 1, 3]])
+        if box is not None:
+            N = (box[1] - box[0]) * (box[3] - box[2]) * 9
+            assert np.abs(F0 - F1).max() <= 4 * N * 0.45 * 2.0 ** -53
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision,nx,ny,forces", WINDOWS)
+def test_windows_without_and_with_forces_bitwise_equal_single_steps(precision, nx, ny, forces):
+    """Windows in every storage, also without forces: bounded, periodic and moving."""
+    large = nx * ny > 3_000_000
+    for bc, spin in ([((0, 0), 0)] if large else [((0, 0), 0), ((0, 1), 1), ((1, 0), 0)]):
+        _runs(precision, "bgk", nx, ny, bc, forces, spin, 8)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "fp32dev", "fp32sr", "fp16dev"])
+@pytest.mark.parametrize("collision", ["bgk", "kbc"])
+def test_tiles_without_and_with_forces_bitwise_equal_single_steps(precision, collision):
+    """Tiles of both collisions in every storage, without forces and with them, of bodies at rest
+    and in motion."""
+    for p, c, nx, ny, forces in TILES:
+        if (p, c) == (precision, collision):
+            for bc, spin in (((0, 0), 0), ((0, 0), 1), ((1, 1), 0)):
+                _runs(p, c, nx, ny, bc, forces, spin, 9)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "fp32dev", "fp32sr"])
+def test_kept_states_of_the_adjoint_equal_single_steps(precision):
+    """Segments of two steps are recomputed by a single step each, longer ones by tiles that store
+    every state: the objective and its gradients are bitwise alike."""
+    import torch
+    from paper_2210_10377_amd import Sim
+    from paper_2210_10377_amd.autograd import ObjectiveSpec, objective
+    for nx, ny in ((130, 37), (330, 90)):
+        mask, box = _small_body(nx, ny)
+        uin = 0.05 * (1 + 0.05 * np.random.default_rng(4).uniform(-1, 1, ny))
+        got = []
+        for every in (2, 11, 40):
+            print(f"adjoint {precision} {nx}x{ny} every {every}", flush=True)
+            sim = Sim(mask, 0.6, uin, precision=precision, box=box, max_record=8)
+            u = torch.from_numpy(uin).cuda().requires_grad_()
+            tau = torch.tensor(0.6, dtype=torch.float64, requires_grad=True)
+            J = objective(u, tau, sim, ObjectiveSpec(40, every, 30, 10, (1.0, 0.25)))
+            J.backward()
+            got.append((J.item(), u.grad.cpu().numpy(), tau.grad.item()))
+            del sim
+        for J, g, t in got[1:]:
+            assert J == got[0][0] and t == got[0][2]
+            np.testing.assert_array_equal(g, got[0][1])
