@@ -47,13 +47,14 @@ struct lbm_batch_t {
   int64_t total_tiles = 0, total_box = 0, total_fluid = 0, total_nodes = 0;
   int64_t max_tiles = 0;  // tile-list capacity: the most tiles of the three tile shapes
   std::vector<int32_t> tile_inst, tile_local, box_inst, box_local;
-  // Fused launches: the members' work maps, the blocks of all of them (the longest kinds
-  // first), and the plan generations they were built from.  Blocks are reserved at create
-  // (item_cap) so that a new mask of a member fits; without room single steps are taken.
-  std::vector<FuseMap> fmap;
-  std::vector<int32_t> item_inst, item_local;
-  size_t nbody = 0, nblocks = 0;  // items of body rectangles, and in all without tiles
+  // Fused launches: the members' work maps and the blocks of all of them, and the plan
+  // generations they were built from; what of them the device does not hold yet.  Blocks are
+  // reserved at create (item_cap; one where no call can take fused launches) so that a new mask of
+  // a member fits; without room single steps are taken.
+  BatchWork bw;
   std::vector<uint64_t> fuse_gen;
+  std::vector<uint8_t> map_stale;
+  bool list_stale = true;
   int64_t item_cap = 0;
   StepWork work;                    // of all members, which the choice of a form goes by
   bool fuse[2] = {false, false};    // fused launches are taken, without and with forces
@@ -176,62 +177,54 @@ struct lbm_batch_t {
     }
   }
 
-  // Work maps and block list of fused launches from the members' present plans, and whether they
-  // are the faster form.
-  void build_fuse() {
-    fmap.clear();
-    item_inst.clear();
-    item_local.clear();
-    fuse_gen.clear();
-    work = StepWork();
-    for (const lbm_t* h : m) {
-      fuse_gen.push_back(h->plan_gen);
-      fmap.push_back(fuse_map(h->plan, int(h->esz), total_nodes));
-      work.add(h->plan, fmap.back(), int(h->esz));
+  // Work maps and blocks of the members whose plans are others than when they were last taken (all
+  // of them the first time), and whether fused launches are the faster form with them.
+  void update_work() {
+    if (bw.map.size() != m.size()) {
+      bw = BatchWork(m.size());
+      fuse_gen.assign(m.size(), ~uint64_t(0));
+      map_stale.assign(m.size(), 1);
     }
-    // Blocks of the body rectangles, of the others, and of the body rectangles as tiles.
-    for (int kind = kFuseBody; kind <= kFusePlain; ++kind) {
-      for (size_t i = 0; i < m.size(); ++i) {
-        const FuseMap& f = fmap[i];
-        for (int k = 0; k < f.nrects; ++k) {
-          if (f.r[k].kind != kind) continue;
-          const int end = k + 1 < f.nrects ? f.r[k + 1].first : f.nblocks;
-          for (int b = f.r[k].first; b < end; ++b) {
-            item_inst.push_back(int32_t(i));
-            item_local.push_back(b);
-          }
-        }
-      }
-      if (kind == kFuseBody) nbody = item_inst.size();
-    }
-    nblocks = item_inst.size();
+    bool any = false, lists = false;
     for (size_t i = 0; i < m.size(); ++i) {
-      const FuseRect& r = fmap[i].r[0];
-      if (r.kind != kFuseBody) continue;
-      const int strips = (r.x1 + kStripW - 1) / kStripW - r.x0 / kStripW;
-      const int n = strips * ((r.y1 - r.y0 + kBatchTileRows - 1) / kBatchTileRows);
-      for (int b = 0; b < n; ++b) {
-        item_inst.push_back(int32_t(i));
-        item_local.push_back(b);
-      }
+      if (fuse_gen[i] == m[i]->plan_gen) continue;
+      lists |= bw.set(i, m[i]->plan, int(m[i]->esz), total_nodes);
+      fuse_gen[i] = m[i]->plan_gen;
+      map_stale[i] = 1;
+      any = true;
     }
+    if (!any) return;
+    if (lists) {
+      bw.list();
+      list_stale = true;
+    }
+    work = bw.total();
     for (int f = 0; f < 2; ++f)
       fuse[f] = fuse_pays(precision, m[0]->g.collision, f != 0, work) &&
-                (item_cap == 0 || int64_t(item_inst.size()) <= item_cap);
+                (item_cap == 0 || int64_t(bw.inst.size()) <= item_cap);
   }
-  bool fuse_current() const {
-    for (size_t i = 0; i < m.size(); ++i)
-      if (fuse_gen[i] != m[i]->plan_gen) return false;
-    return true;
-  }
-  int upload_fuse() {
+  // Upload what changed of them, if fused launches are taken.
+  int upload_work(bool* uploaded) {
     if (!fuse[0] && !fuse[1]) return LBM_OK;
-    int rc = upload(fmap.data(), off_fmap, fmap.size() * sizeof(FuseMap), "upload work maps");
-    if (rc == LBM_OK) rc = upload(item_inst.data(), off_fi, item_inst.size() * 4, "upload work list");
-    if (rc == LBM_OK) rc = upload(item_local.data(), off_fl, item_local.size() * 4, "upload work list");
-    if (rc != LBM_OK) return rc;
-    const hipError_t e = hipStreamSynchronize(stream);
-    return e == hipSuccess ? LBM_OK : hip_fail(e, "upload synchronize");
+    for (size_t i = 0; i < m.size(); ++i) {
+      size_t end = i;
+      while (end < m.size() && map_stale[end]) ++end;
+      if (end == i) continue;
+      const int rc = upload(&bw.map[i], off_fmap + i * sizeof(FuseMap), (end - i) * sizeof(FuseMap),
+                            "upload work maps");
+      if (rc != LBM_OK) return rc;
+      std::fill(map_stale.begin() + i, map_stale.begin() + end, 0);
+      *uploaded = true;
+      i = end;
+    }
+    if (list_stale) {
+      int rc = upload(bw.inst.data(), off_fi, bw.inst.size() * 4, "upload work list");
+      if (rc == LBM_OK) rc = upload(bw.local.data(), off_fl, bw.local.size() * 4, "upload work list");
+      if (rc != LBM_OK) return rc;
+      list_stale = false;
+      *uploaded = true;
+    }
+    return LBM_OK;
   }
 
   // Instance table for the members' present state, with buf[bpar] the current buffer.
@@ -332,8 +325,9 @@ struct lbm_batch_t {
   }
 
   // Bring the device instance table up to date with the members (a member stepped,
-  // re-bound or given a new tau since the last call).
-  int refresh() {
+  // re-bound or given a new tau since the last call), and what fused launches read if the call
+  // may take some.
+  int refresh(bool may_fuse) {
     for (const lbm_t* h : m)
       if (!h->bound) return fail(LBM_ESTATE, "a member is no longer bound");
     if (!sizes_kept())
@@ -344,20 +338,23 @@ struct lbm_batch_t {
       const int rc = upload(alt_host.data(), off_alt, alt_host.size() * 4, "upload strip slots");
       if (rc != LBM_OK) return rc;
     }
-    if (!fuse_current()) {
-      build_fuse();
-      const int rc = upload_fuse();
+    bool uploaded = false;
+    if (may_fuse) {
+      update_work();
+      const int rc = upload_work(&uploaded);
       if (rc != LBM_OK) return rc;
     }
     std::vector<BatchInst> d = make_desc();
-    if (d.size() == desc.size() &&
-        std::memcmp(d.data(), desc.data(), d.size() * sizeof(BatchInst)) == 0)
-      return LBM_OK;
-    // The previous upload may still be read by queued kernels; the copy is ordered
-    // after them, and the host copy is kept until the stream has consumed it.
-    desc.swap(d);
-    int rc = upload(desc.data(), off_desc, desc.size() * sizeof(BatchInst), "upload instances");
-    if (rc != LBM_OK) return rc;
+    if (d.size() != desc.size() ||
+        std::memcmp(d.data(), desc.data(), d.size() * sizeof(BatchInst)) != 0) {
+      // The previous upload may still be read by queued kernels; the copy is ordered
+      // after them, and the host copy is kept until the stream has consumed it.
+      desc.swap(d);
+      const int rc = upload(desc.data(), off_desc, desc.size() * sizeof(BatchInst), "upload instances");
+      if (rc != LBM_OK) return rc;
+      uploaded = true;
+    }
+    if (!uploaded) return LBM_OK;
     const hipError_t e = hipStreamSynchronize(stream);
     return e == hipSuccess ? LBM_OK : hip_fail(e, "upload synchronize");
   }
@@ -395,7 +392,8 @@ struct lbm_batch_t {
   // Enqueue n >= 1 steps of every instance; with forces, step k's row goes to ring row
   // row0 + k of every instance.  `scheduled`: all of them by the schedule.
   int enqueue(int32_t n, bool forces, int64_t row0, bool scheduled = false) {
-    int rc = refresh();
+    const bool may_fuse = n >= kFuse && !scheduled && item_cap > 1;
+    int rc = refresh(may_fuse);
     if (rc != LBM_OK) return rc;
     const BatchLaunch L = launch();
     const int G = sched.graph_steps;
@@ -405,7 +403,7 @@ struct lbm_batch_t {
     }
     // Single steps by the schedule (all of them, or what is left over kFuse), then the fused
     // launches, which have an order of their own.
-    const int32_t singles = fuse[forces ? 1 : 0] && n >= kFuse && !scheduled ? n % kFuse : n;
+    const int32_t singles = may_fuse && fuse[forces ? 1 : 0] ? n % kFuse : n;
     int32_t done = 0;
     while (done < singles) {
       const int len = G > 0 ? std::min<int32_t>(G, singles - done) : singles - done;
@@ -439,13 +437,13 @@ struct lbm_batch_t {
       f.item_inst = reinterpret_cast<const int32_t*>(ws + off_fi);
       f.item_local = reinterpret_cast<const int32_t*>(ws + off_fl);
       f.n_inst = L.n_inst;
-      f.nitems = int32_t(nblocks);
+      f.nitems = int32_t(bw.nblocks);
       f.moving = L.moving;
       const bool tiles = forces && batch_tiles_pay(work);
       if (tiles) {
-        f.item_inst += nbody;
-        f.item_local += nbody;
-        f.nitems -= int32_t(nbody);
+        f.item_inst += bw.nbody;
+        f.item_local += bw.nbody;
+        f.nitems -= int32_t(bw.nbody);
       }
       in_last = done > 0 ? 1 : 0;
       turn = (done - 1) & 1;
@@ -460,9 +458,9 @@ struct lbm_batch_t {
         hipError_t e = hipSuccess;
         if (tiles) {
           BatchFuse b = f;
-          b.item_inst += nblocks - nbody;
-          b.item_local += nblocks - nbody;
-          b.nitems = int32_t(item_inst.size() - nblocks);
+          b.item_inst += bw.nblocks - bw.nbody;
+          b.item_local += bw.nblocks - bw.nbody;
+          b.nitems = int32_t(bw.inst.size() - bw.nblocks);
           e = launch_batch_tiles(precision, b, stream);
         }
         if (e == hipSuccess) e = launch_batch_fused(precision, forces, f, stream);
@@ -550,8 +548,8 @@ int lbm_batch_create(lbm_t* const* members, int32_t n, int32_t max_record, lbm_b
   }
   b->build_alt();
   b->build_lists();
-  b->build_fuse();
-  b->item_cap = b->fuse[0] || b->fuse[1] ? 2 * int64_t(b->item_inst.size()) + 256 : 1;
+  b->update_work();
+  b->item_cap = b->fuse[0] || b->fuse[1] ? 2 * int64_t(b->bw.inst.size()) + 256 : 1;
   size_t off = 0;
   b->off_desc = off;
   off = align256(off + size_t(n) * sizeof(BatchInst));
@@ -607,10 +605,10 @@ int lbm_batch_bind(lbm_batch_t* b, void* device_workspace, size_t bytes, void* h
   b->desc.clear();
   b->nrec = 0;
   b->rec_scheme.clear();
-  b->build_fuse();
+  b->map_stale.assign(b->m.size(), 1);
+  b->list_stale = true;
   int rc = b->upload_lists();
-  if (rc == LBM_OK) rc = b->upload_fuse();
-  if (rc == LBM_OK) rc = b->refresh();
+  if (rc == LBM_OK) rc = b->refresh(b->item_cap > 1);
   if (rc != LBM_OK) return rc;
   b->bound = true;
   return LBM_OK;

@@ -617,6 +617,65 @@ FuseMap fuse_map(const Plan& p, int elem_bytes, int64_t nodes) {
   return m;
 }
 
+namespace {
+
+// Blocks of kBatchTileRows rows of a strip's columns in the body rectangle of m, if it has one.
+int body_tiles(const FuseMap& m) {
+  const FuseRect& r = m.r[0];
+  if (m.nrects == 0 || r.kind != kFuseBody) return 0;
+  const int strips = (r.x1 + kStripW - 1) / kStripW - r.x0 / kStripW;
+  return strips * ((r.y1 - r.y0 + kBatchTileRows - 1) / kBatchTileRows);
+}
+
+}  // namespace
+
+bool BatchWork::set(size_t i, const Plan& p, int elem_bytes, int64_t nodes) {
+  const FuseMap m = fuse_map(p, elem_bytes, nodes), &old = map[i];
+  bool other = m.nrects != old.nrects || m.nblocks != old.nblocks || body_tiles(m) != body_tiles(old);
+  for (int k = 0; k < m.nrects && !other; ++k)
+    other = m.r[k].kind != old.r[k].kind || m.r[k].first != old.r[k].first;
+  map[i] = m;
+  work[i] = StepWork();
+  work[i].add(p, m, elem_bytes);
+  return other;
+}
+
+void BatchWork::list() {
+  inst.clear();
+  local.clear();
+  auto add = [&](size_t i, int b) {
+    inst.push_back(int32_t(i));
+    local.push_back(b);
+  };
+  for (int kind = kFuseBody; kind <= kFusePlain; ++kind) {
+    for (size_t i = 0; i < map.size(); ++i) {
+      const FuseMap& f = map[i];
+      for (int k = 0; k < f.nrects; ++k) {
+        if (f.r[k].kind != kind) continue;
+        const int end = k + 1 < f.nrects ? f.r[k + 1].first : f.nblocks;
+        for (int b = f.r[k].first; b < end; ++b) add(i, b);
+      }
+    }
+    if (kind == kFuseBody) nbody = inst.size();
+  }
+  nblocks = inst.size();
+  for (size_t i = 0; i < map.size(); ++i)
+    for (int b = 0; b < body_tiles(map[i]); ++b) add(i, b);
+}
+
+StepWork BatchWork::total() const {
+  StepWork t;
+  for (const StepWork& w : work) {
+    t.strips += w.strips;
+    t.nodes += w.nodes;
+    t.plain += w.plain;
+    t.coded += w.coded;
+    t.body += w.body;
+    t.body_nodes += w.body_nodes;
+  }
+  return t;
+}
+
 void tile_slots(const Plan& p, int rows, int& ntx, int& nty, std::vector<int32_t>& out) {
   const int tile_w = kTileW / rows;
   ntx = (p.nx + tile_w - 1) / tile_w;

@@ -240,6 +240,23 @@ FuseMap step_map(const Plan& p, int precision, int collision, bool forces, int e
 // The same for steps without forces whose states are all kept.
 FuseMap keep_map(const Plan& p, int precision, int collision);
 
+// Fused launches of a batch: every member's work map, and the items (a member and a block of its
+// map) of all of them: the blocks of the body rectangles, then those of the other rectangles, the
+// longest kinds first, then the body rectangles once more as blocks of kBatchTileRows rows of a
+// strip's columns.
+struct BatchWork {
+  std::vector<FuseMap> map;
+  std::vector<StepWork> work;
+  std::vector<int32_t> inst, local;
+  size_t nbody = 0, nblocks = 0;  // items of body rectangles, and in all without the last ones
+  explicit BatchWork(size_t members = 0) : map(members), work(members) {}
+  // Member i's plan, in a launch of `nodes` nodes in all.  Returns whether its blocks are others than
+  // before, so that the items have to be listed anew.
+  bool set(size_t i, const Plan& p, int elem_bytes, int64_t nodes);
+  void list();
+  StepWork total() const;
+};
+
 // Node words a mask change rewrites (index, old word, new word), in index order.
 struct PlanDelta {
   std::vector<int64_t> idx;

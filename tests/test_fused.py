@@ -439,6 +439,110 @@ def test_tiles_bitwise_equal_single_steps(precision, bc_x, bc_y, collision, spin
             assert np.abs(F0 - F1).max() <= 4 * N * 0.45 * 2.0 ** -53
 
 
+BATCH_WORK = r"""
+#include <algorithm>
+#include <cstdio>
+#include <set>
+#include <string>
+#include <utility>
+#include <vector>
+#include "plan.h"
+using namespace lbm;
+#define CHECK(c) do { if (!(c)) { std::printf("line %d: %s\n", __LINE__, #c); return 1; } } while (0)
+static Plan lattice(int nx, int ny, int x, int y, bool body) {
+  lbm_grid g{};
+  g.nx = nx;
+  g.ny = ny;
+  g.precision = LBM_FP32;
+  g.max_record = 1;
+  for (int k = 0; k < 4; ++k) g.box[k] = -1;
+  std::vector<uint8_t> mask(size_t(nx) * ny, 0);
+  if (body) {
+    for (int j = 0; j < 9; ++j)
+      for (int i = 0; i < 9; ++i) mask[size_t(y + j) * nx + x + i] = 1;
+    const int b[4] = {x - 3, x + 12, y - 3, y + 12};
+    std::copy(b, b + 4, g.box);
+  }
+  Plan p;
+  std::string err;
+  build_plan(g, mask.data(), p, err);
+  return p;
+}
+int main() {
+  std::vector<Plan> m;
+  for (int k = 0; k < 12; ++k) m.push_back(lattice(150 + 37 * k, 90 + 11 * k, 30 + k, 40, k % 4 != 3));
+  int64_t nodes = 0;
+  for (const Plan& p : m) nodes += int64_t(p.nx) * p.ny;
+  BatchWork w(m.size());
+  for (size_t i = 0; i < m.size(); ++i) CHECK(w.set(i, m[i], 4, nodes));
+  w.list();
+  auto whole = [&]() {  // every block of every map once, the longest kinds first
+    std::set<std::pair<int, int>> seen;
+    int last = 0;
+    size_t blocks = 0;
+    for (size_t k = 0; k < w.nblocks; ++k) {
+      const FuseMap& f = w.map[w.inst[k]];
+      int r = f.nrects - 1;
+      while (r > 0 && w.local[k] < f.r[r].first) --r;
+      if (w.local[k] < 0 || w.local[k] >= f.nblocks || f.r[r].kind < last) return false;
+      if ((f.r[r].kind == kFuseBody) != (k < w.nbody)) return false;
+      last = f.r[r].kind;
+      if (!seen.insert({w.inst[k], w.local[k]}).second) return false;
+    }
+    for (const FuseMap& f : w.map) blocks += f.nblocks;
+    return blocks == w.nblocks && w.inst.size() == w.local.size();
+  };
+  CHECK(whole());
+  auto same = [&](const BatchWork& a) {
+    bool maps = true;
+    for (size_t i = 0; i < m.size(); ++i)
+      for (int k = 0; k < a.map[i].nrects; ++k) {
+        const FuseRect &p = a.map[i].r[k], &q = w.map[i].r[k];
+        maps = maps && a.map[i].nrects == w.map[i].nrects && p.x0 == q.x0 && p.x1 == q.x1 && p.y0 == q.y0 &&
+               p.y1 == q.y1 && p.kind == q.kind && p.rows == q.rows && p.nw == q.nw && p.first == q.first;
+      }
+    const StepWork s = a.total(), t = w.total();
+    return maps && a.inst == w.inst && a.local == w.local && a.nbody == w.nbody && a.nblocks == w.nblocks &&
+           s.plain == t.plain && s.coded == t.coded && s.body == t.body && s.body_nodes == t.body_nodes;
+  };
+  int kept = 0, listed = 0;
+  for (int step = 0; step < 60; ++step) {  // bodies that move, appear and go, a node or many at a time
+    const int i = step * 7 % 12;
+    const int x = 30 + (step * 5) % 40, y = 40 + step % 3;
+    m[i] = lattice(m[i].nx, m[i].ny, step % 2 ? 31 + i + step % 4 : x, y, step % 9 != 8);
+    if (w.set(i, m[i], 4, nodes)) {
+      w.list();
+      ++listed;
+    } else {
+      ++kept;
+    }
+    BatchWork fresh(m.size());
+    for (size_t k = 0; k < m.size(); ++k) fresh.set(k, m[k], 4, nodes);
+    fresh.list();
+    CHECK(same(fresh));
+    CHECK(whole());
+  }
+  std::printf("%d %d\n", kept, listed);
+  return 0;
+}
+"""
+
+
+def test_batch_work_follows_one_member_at_a_time(tmp_path):
+    """After a mask change of one member the maps and the list of blocks are those built from all
+    members anew, and the list is kept where the member's blocks are as before."""
+    src = tmp_path / "batch_work.cpp"
+    src.write_text(BATCH_WORK)
+    exe = tmp_path / "batch_work"
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-fsanitize=address,undefined", "-I", CSRC,
+                           "-I", os.path.join(ROOT, "include"), str(src), os.path.join(CSRC, "plan.cpp"),
+                           "-o", str(exe)])
+    out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
+    assert out.returncode == 0, out.stdout + out.stderr
+    kept, listed = (int(v) for v in out.stdout.split())
+    assert kept >= 10 and listed >= 10, (kept, listed)
+
+
 def _small_body(nx, ny):
     """The body and control volume of FORM's lattices."""
     mask = np.zeros((ny, nx), np.uint8)
