@@ -424,8 +424,8 @@ typedef struct lbm_batch_schedule {
   int32_t tile_queue;  /* persistent grids only: 0 = each workgroup takes every
                           grid_blocks-th tile of the list; 1 = workgroups take the
                           next 16 tiles from a device counter (one global atomic per
-                          16 tiles, reset by a small kernel at each lbm_batch_step
-                          call and by each launch for the next), over a list ordered
+                          16 tiles, reset by a small kernel at each lbm_batch_step call
+                          that takes launches of one step, and by each for the next), over a list ordered
                           largest instance first.  Results do not depend on it.      */
   int32_t tile_shape;  /* LBM_TILE_AUTO (0): every instance keeps its own tile shape;
                           LBM_TILE_WIDE / LBM_TILE_NARROW: every instance runs in

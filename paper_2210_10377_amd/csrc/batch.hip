@@ -397,13 +397,13 @@ struct lbm_batch_t {
     if (rc != LBM_OK) return rc;
     const BatchLaunch L = launch();
     const int G = sched.graph_steps;
-    if (L.queue) {
-      const hipError_t e = launch_batch_queue_reset(L.queue, stream);
-      if (e != hipSuccess) return hip_fail(e, "reset tile queue");
-    }
     // Single steps by the schedule (all of them, or what is left over kFuse), then the fused
     // launches, which have an order of their own.
     const int32_t singles = may_fuse && fuse[forces ? 1 : 0] ? n % kFuse : n;
+    if (L.queue && singles > 0) {
+      const hipError_t e = launch_batch_queue_reset(L.queue, stream);
+      if (e != hipSuccess) return hip_fail(e, "reset tile queue");
+    }
     int32_t done = 0;
     while (done < singles) {
       const int len = G > 0 ? std::min<int32_t>(G, singles - done) : singles - done;

@@ -658,3 +658,38 @@ def test_large_members_of_the_other_storages_in_launches_of_three_steps(precisio
             r.step(n, sch)
         np.testing.assert_array_equal(F[i][:, [0, 1, 3]], r.forces()[:, [0, 1, 3]], err_msg=f"member {i}")
         np.testing.assert_array_equal(s.populations(), r.populations(), err_msg=f"member {i}")
+
+
+def _captured_launches(stream, call):
+    """Kernel launches that `call` enqueues on a stream (by capturing them; they are not run)."""
+    import ctypes
+    import torch
+    hip = ctypes.CDLL("libamdhip64.so")
+    st = ctypes.c_void_p(stream.cuda_stream)
+    graph, n = ctypes.c_void_p(), ctypes.c_size_t()
+    torch.cuda.synchronize()
+    assert hip.hipStreamBeginCapture(st, 1) == 0
+    try:
+        call()
+    finally:
+        rc = hip.hipStreamEndCapture(st, ctypes.byref(graph))
+    assert rc == 0 and hip.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0
+    hip.hipGraphDestroy(graph)
+    return n.value
+
+
+def test_calls_without_single_steps_do_not_reset_the_tile_queue():
+    """The tile queue belongs to launches of one step: a call that takes none enqueues the
+    launches of three steps alone."""
+    import torch
+    from paper_2210_10377_amd import Batch
+    st = torch.cuda.Stream()
+    with torch.cuda.stream(st):
+        b = Batch.from_workloads(workloads.batched_instances(28, seed=13), precision="fp64", max_record=8,
+                                 stream=st)
+        b.set_schedule(grid_blocks=256, tile_queue=1)
+        b.step(4, ())
+        assert b.launches() == (1, 1)
+        # (A step by the schedule comes with the reset of the queue.)
+        assert _captured_launches(st, lambda: b.step(6, ())) == 2
+        assert _captured_launches(st, lambda: b.step(4, ())) == 3
