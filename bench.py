@@ -46,9 +46,9 @@ def kernel_hash(three_d: bool = False) -> str:
     return h.hexdigest()
 
 
-def measured_traffic(workload: str, precision: str, three_d: bool = False):
-    """HBM bytes per step from the committed rocprofv3 counter summary, or None when the
-    path's sources changed since the counters were taken."""
+def traffic_record(workload: str, precision: str, three_d: bool = False):
+    """The committed rocprofv3 counter summary of a workload, or None when the path's sources
+    changed since the counters were taken."""
     try:
         with open(TRAFFIC_FILE) as f:
             t = json.load(f)
@@ -57,7 +57,31 @@ def measured_traffic(workload: str, precision: str, three_d: bool = False):
     rec = t.get(f"{workload}/{precision}")
     if not rec or rec.get("sources_sha256") != kernel_hash(three_d):
         return None
-    return rec["hbm_bytes_per_launch"] / rec.get("steps_per_launch", 1)
+    return rec
+
+
+def measured_traffic(workload: str, precision: str, three_d: bool = False):
+    """HBM bytes per step of it, or None."""
+    rec = traffic_record(workload, precision, three_d)
+    return rec["hbm_bytes_per_launch"] / rec.get("steps_per_launch", 1) if rec else None
+
+
+def step_roofline(rec, single_bytes: float, steps: int, t_step: float) -> dict:
+    """HBM rate of a run of `steps` steps of t_step seconds, of the bytes that it moved: by the
+    counters of launches of several steps (rec), the steps left over by `single_bytes`, one
+    read and one write of every population.  Without counters the bytes moved are not known and
+    only the rate that single steps would need (single_step_gbs) is given; it is no share of
+    the peak, as launches of three steps move about a third."""
+    out = {"bound": "hbm", "achieved": None, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": None,
+           "traffic": None, "single_step_gbs": round(single_bytes / t_step / 1e9, 1)}
+    if rec:
+        k = rec.get("steps_per_launch", 1)
+        left = steps % k
+        moved = (steps // k * rec["hbm_bytes_per_launch"] + left * single_bytes) / steps
+        out["traffic"] = round(moved)
+        out["achieved"] = round(moved / t_step / 1e9, 1)
+        out["frac"] = round(moved / t_step / 1e9 / HBM_PEAK_GBS, 4)
+    return out
 
 
 def host_cpu_model() -> str:
@@ -487,14 +511,12 @@ def slab_bench(precision: str, steps: int, warmup: int, k: int = 2, parts: int =
     torch.cuda.synchronize()
     ms = e0.elapsed_time(e1) / steps
     bpn = BYTES_PER_NODE[precision]
-    achieved = info.n_fluid * bpn / (ms / 1e3) / 1e9
     print(json.dumps({
         "metric": "slab MLUPS incl. per-step forces", "workload": f"{w.name}_slab{k}of{parts}",
         "nx": W, "ny": w.ny, "storage": precision, "steps": steps,
         "fluid_nodes": int(info.n_fluid), "links": int(info.n_links),
         "us_per_step": round(ms * 1e3, 3), "mlups": round(W * w.ny / ms / 1e3, 1),
-        "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
-                     "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4)},
+        "roofline": step_roofline(None, info.n_fluid * bpn, steps, ms / 1e3),
         "halo_bytes_per_cut_each_way": 3 * w.ny * (bpn // 18)}), flush=True)
 
 
@@ -645,17 +667,18 @@ def adjoint_bench(precision: str, large: bool = False, tile: str = "auto", emit:
     fluid = int(sim.info().n_fluid)
     s = BYTES_PER_NODE[precision] // 18          # bytes per stored population
     s_adj = 8 if precision == "fp64" else 4      # bytes per adjoint value
-    fwd_bytes = fluid * 18 * s * n               # the forward run (checkpoint copies aside)
-    # Backward: each segment of len steps recomputes len - 1 of them (2 Q s per node),
-    # n - ceil(n / every) in all; the reverse kernel runs every step (Q s + 2 Q s_adj).
+    fwd_bytes = fluid * 18 * s * n               # the forward run as single steps move it
+    # Backward: each segment of len steps recomputes len - 1 of them, n - ceil(n / every) in
+    # all, every state stored and at least each third one read (Q s + Q s / 3 per node); the
+    # reverse kernel runs every step (Q s + 2 Q s_adj).
     recomputed = n - (n + every - 1) // every
-    bwd_bytes = fluid * (18 * s * recomputed + (9 * s + 18 * s_adj) * n)
+    bwd_bytes = fluid * (12 * s * recomputed + (9 * s + 18 * s_adj) * n)
     out = {
         "metric": "adjoint MLUPS", "workload": w.name, "storage": precision, "steps": n,
         "tile": tile,
         "developed_steps": develop,
         "roofline": {"bound": "hbm", "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                     "forward_achieved": round(fwd_bytes / t_f / 1e9, 1),
+                     "forward_single_step_gbs": round(fwd_bytes / t_f / 1e9, 1),
                      "backward_achieved": round(bwd_bytes / t_b / 1e9, 1),
                      "backward_bytes_per_node_step": round(bwd_bytes / fluid / n, 2),
                      "backward_frac": round(bwd_bytes / t_b / 1e9 / HBM_PEAK_GBS, 4)},
@@ -790,7 +813,6 @@ def batched_bench(precision: str, steps: int, seq_steps: int, collision: str):
     fluid = int(info.total_fluid)
     t_step = ms / 1e3 / steps
     mlups = nodes / t_step / 1e6
-    achieved = fluid * BYTES_PER_NODE[precision] / t_step / 1e9
     # the same instances, one lbm_step call per instance per chunk, same stream
     seq = b.members
     torch.cuda.synchronize()
@@ -819,9 +841,8 @@ def batched_bench(precision: str, steps: int, seq_steps: int, collision: str):
                    "instances": len(ws), "nodes": nodes, "fluid_nodes": fluid,
                    "storage": precision, "collision": collision, "schedule": sched,
                    "autotune_ms_per_step": tune_ms},
-        "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
-                     "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
-                     "traffic": measured_traffic(BATCH_WORKLOAD, precision)},
+        "roofline": step_roofline(traffic_record(BATCH_WORKLOAD, precision),
+                                  fluid * BYTES_PER_NODE[precision], steps, t_step),
         "nonfinite_instances": int(bad.sum()),
         "sequential_single_calls_mlups": round(seq_mlups, 1),
         "batch_fp64_mlups": round(mlups64, 1),
@@ -1165,9 +1186,6 @@ def main():
     t_step = ms / 1e3 / K
     nodes = w.nx * w.ny
     mlups = nodes / t_step / 1e6
-    bytes_launch = info.n_fluid * BYTES_PER_NODE[args.precision]
-    achieved = bytes_launch / t_step / 1e9
-    traffic = measured_traffic(w.name, args.precision)
     out = {
         "metric": METRIC,
         "value": round(mlups, 1),
@@ -1189,13 +1207,8 @@ def main():
                    "box_nodes": int(info.n_box), **{k: v for k, v in w.meta.items()},
                    **({"body_motion": {"omega": motion[2], "xc": motion[3], "yc": motion[4]}}
                       if motion else {})},
-        # achieved: one read and one write of every population a step, as single steps make
-        # them (launches of three steps move about a third); hbm_frac: the counted bytes.
-        "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
-                     "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
-                     "traffic": traffic,
-                     "hbm_frac": round(traffic / t_step / 1e9 / HBM_PEAK_GBS, 4)
-                     if traffic else None},
+        "roofline": step_roofline(traffic_record(w.name, args.precision),
+                                  info.n_fluid * BYTES_PER_NODE[args.precision], K, t_step),
         "wall_s": round(wall, 3),
         "forces_off_ms_per_step": round(ms_off, 5),
         "force_cost_frac": round((ms / K - ms_off) / ms_off, 4),
