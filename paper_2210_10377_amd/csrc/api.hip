@@ -347,7 +347,8 @@ int enqueue_steps(lbm_t* h, const DevTables& t, hipStream_t stream, int32_t n, d
   q.map.nblocks = 0;
   if (n >= kFuse && a.buf_bytes != 0 && (alternate ? t.fuse : !forces)) {
     q = FuseArgs{};
-    q.map = alternate ? step_map(p, h->g.precision, h->g.collision, forces, int(h->esz))
+    q.map = alternate ? step_map(p, h->g.precision, h->g.collision, forces, int(h->esz),
+                                 t.motion != nullptr)
                       : keep_map(p, h->g.precision, h->g.collision);
     q.step.part_stride = t.part_stride;
   }

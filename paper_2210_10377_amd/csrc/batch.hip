@@ -57,7 +57,8 @@ struct lbm_batch_t {
   bool list_stale = true;
   int64_t item_cap = 0;
   StepWork work;                    // of all members, which the choice of a form goes by
-  bool fuse[2] = {false, false};    // fused launches are taken, without and with forces
+  // Fused launches are taken: bodies at rest, or some in motion, without and with forces.
+  bool fuse[2][2] = {};
   std::vector<int> nj0;  // box-sweep blocks of each member at create (the lists' sizes)
   std::vector<BatchInst> desc;  // the instance table as last uploaded
   size_t off_desc = 0, off_fmap = 0, off_fi = 0, off_fl = 0, off_ti = 0, off_tl = 0, off_bi = 0, off_bl = 0, off_ctl = 0,
@@ -199,13 +200,20 @@ struct lbm_batch_t {
       list_stale = true;
     }
     work = bw.total();
-    for (int f = 0; f < 2; ++f)
-      fuse[f] = fuse_pays(precision, m[0]->g.collision, f != 0, work) &&
-                (item_cap == 0 || int64_t(bw.inst.size()) <= item_cap);
+    const bool fits = item_cap == 0 || int64_t(bw.inst.size()) <= item_cap;
+    for (int moving = 0; moving < 2; ++moving)
+      for (int f = 0; f < 2; ++f)
+        fuse[moving][f] = fits && fuse_pays(precision, m[0]->g.collision, f != 0, work, moving != 0, true);
+  }
+  bool in_motion() const {
+    for (const lbm_t* h : m)
+      if (h->motion.moving) return true;
+    return false;
   }
   // Upload what changed of them, if fused launches are taken.
   int upload_work(bool* uploaded) {
-    if (!fuse[0] && !fuse[1]) return LBM_OK;
+    const bool* now = fuse[in_motion()];
+    if (!now[0] && !now[1]) return LBM_OK;
     for (size_t i = 0; i < m.size(); ++i) {
       size_t end = i;
       while (end < m.size() && map_stale[end]) ++end;
@@ -289,8 +297,7 @@ struct lbm_batch_t {
     L.total_box_blocks = int32_t(total_box);
     L.grid_blocks = sched.grid_blocks > 0 ? (sched.grid_blocks + 7) / 8 * 8 : 0;
     L.collision = m[0]->g.collision;
-    L.moving = 0;
-    for (const lbm_t* h : m) L.moving |= h->motion.moving;
+    L.moving = in_motion();
     return L;
   }
 
@@ -399,7 +406,7 @@ struct lbm_batch_t {
     const int G = sched.graph_steps;
     // Single steps by the schedule (all of them, or what is left over kFuse), then the fused
     // launches, which have an order of their own.
-    const int32_t singles = may_fuse && fuse[forces ? 1 : 0] ? n % kFuse : n;
+    const int32_t singles = may_fuse && fuse[L.moving][forces ? 1 : 0] ? n % kFuse : n;
     if (L.queue && singles > 0) {
       const hipError_t e = launch_batch_queue_reset(L.queue, stream);
       if (e != hipSuccess) return hip_fail(e, "reset tile queue");
@@ -549,7 +556,8 @@ int lbm_batch_create(lbm_t* const* members, int32_t n, int32_t max_record, lbm_b
   b->build_alt();
   b->build_lists();
   b->update_work();
-  b->item_cap = b->fuse[0] || b->fuse[1] ? 2 * int64_t(b->bw.inst.size()) + 256 : 1;
+  const bool* any = &b->fuse[0][0];
+  b->item_cap = any[0] || any[1] || any[2] || any[3] ? 2 * int64_t(b->bw.inst.size()) + 256 : 1;
   size_t off = 0;
   b->off_desc = off;
   off = align256(off + size_t(n) * sizeof(BatchInst));

@@ -640,9 +640,7 @@ hipError_t fused_go(bool forces, const StepArgs& a, const FuseArgs& q, hipStream
 
 template <int P>
 hipError_t batch_fused_go(bool forces, const BatchFuse& b, hipStream_t s) {
-  // (No block is left where the body rectangles, launched apart, are all of the lattices.)
   const dim3 grid(unsigned(b.nred_blocks + b.nitems));
-  if (grid.x == 0) return hipSuccess;
   if (forces) {
     if (b.moving)
       hipLaunchKernelGGL((batch_fused_kernel<P, true, true>), grid, dim3(kThreads), 0, s, b);

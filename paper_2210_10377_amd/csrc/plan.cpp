@@ -381,14 +381,16 @@ void StepWork::add(const Plan& p, const FuseMap& m, int elem_bytes) {
   }
 }
 
-bool fuse_pays(int precision, int collision, bool forces, const StepWork& w) {
+bool fuse_pays(int precision, int collision, bool forces, const StepWork& w, bool moving,
+               bool batch) {
   // Both forms in us a step, as they were measured: a start, and us for a million lanes of strips
   // and nodes, or of the lanes and rows that windows of each kind march (they do about 1.4 times
   // the work in plain windows, 1.5 - 6 times at edges and bodies, for a third of the bytes; a narrow
   // lattice has few other windows).  No fused launch is shorter than its longest unit: `least`.
-  // Fitted to 418 lattices and batches for each row of the table (242 in the lower half): widths 3 to 20000, 2e5 to 8e6
-  // nodes in all, cylinders, airfoils, porous blocks and small bodies, lattices and members from
-  // 3 rows on.  The form it picks is on average 0 - 0.9 % slower than the faster one.
+  // Fitted to 418 lattices and batches for each row of the table (242 in the lower half): widths 3 to
+  // 20000, 2e5 to 8e6 nodes in all, cylinders, airfoils, porous blocks and small bodies, lattices and
+  // members from 3 rows on.  Over those and 776 more lattices a row, half of them with spinning
+  // bodies, the form picked (tiles among them) is on average 0.6 % slower than the fastest.
   // Measured, single : fused, with all forces (without): binary32 1024 x 512 10.4 : 10.0 (8.1 : 6.5),
   // 2048 x 1024 27 : 17, 8192 x 4096 397 : 177, 16 x 40000 23 : 40 (21 : 29), 37 x 14000 15 : 25
   // (13 : 21), 1000 lattices of 64 x 32 72 : 110 (30 : 60), of 43 000 nodes 16 20 : 19 (16 : 15), 256
@@ -397,6 +399,12 @@ bool fuse_pays(int precision, int collision, bool forces, const StepWork& w) {
   // 5792 x 2896 101 : 98.
   // The stabilized collisions stay with single steps: regularized, binary32, 1024 x 512 without
   // forces 8.1 : 9.5, a moving airfoil with forces 12.4 : 13.3.
+  // Bodies in motion slow a window more than a strip: a cylinder in 1300 x 650, binary64,
+  // 25.5 : 15.9 at rest and 24.6 : 18.9 spinning, binary32 850 x 531 10.1 : 10.0 and 10.7 : 12.6.  In
+  // batches it is the single steps that they slow: 32 lattices in binary32 30.9 : 28.1 at rest and
+  // 50.7 : 30.8 spinning.  `kRatio` is the median of measured over fitted, of 388 lattices (against
+  // that at rest) and 29 or 34 batches a row; of binary32 batches 4 to 12 % less, for the smallest:
+  // 25 of 200 x 80 12.4 : 10.4 with forces, 8.4 : 7.4 without, 62 21.6 : 23.3 and 17.7 : 19.2 (spinning).
   struct Rates {
     double start, strips, nodes, body;                // single steps
     double least, begin, plain, coded, body_windows;  // fused launches
@@ -406,13 +414,26 @@ bool fuse_pays(int precision, int collision, bool forces, const StepWork& w) {
       {{2.3, 6.8, 5.4, 0.6, 5.7, 2.8, 3.4, 3.5, 3.2}, {4.4, 8.0, 4.0, 4.7, 9.7, 4.0, 3.1, 5.1, 11.0}},
       {{3.1, 7.9, 3.4, 0.4, 8.1, 4.8, 6.0, 5.4, 5.6}, {4.8, 9.1, 2.1, 3.7, 12.0, 5.4, 5.8, 7.1, 13.0}},
       {{3.2, 5.5, 0.0, 0.8, 7.1, 3.8, 2.6, 5.5, 7.3}, {5.0, 5.6, 0.0, 4.6, 10.7, 4.4, 2.6, 6.5, 13.9}}};
+  // Windows over single steps: lattices at rest and moving, batches at rest and moving.
+  constexpr double kRatio[4][2][4] = {{{1.0, 1.1, 1.0, 1.05}, {1.0, 1.17, 1.0, 0.97}},
+                                      {{1.0, 1.03, 0.96, 0.96}, {1.0, 1.17, 0.91, 0.58}},
+                                      {{1.0, 1.0, 1.0, 1.05}, {1.0, 1.04, 0.85, 0.4}},
+                                      {{1.0, 1.03, 1.0, 1.02}, {1.0, 1.0, 0.84, 0.7}}};
+  // The fit is off by 5 % (median) and 18 % (one in ten) on lattices it was not made of, so what it
+  // says of few nodes, or of many at bodies, is not followed: there windows measured 0.75 to 1.24 of
+  // single steps (binary32 without forces 1020 x 317 7.0 : 7.7, with a spinning airfoil 1933 x 276
+  // 10.2 : 12.6; stochastically rounded 3341 x 1371, periodic along x, 56 : 62).
+  constexpr double kLeast[4] = {2.5e5, 4e5, 4e6, 1.5e7};
+  constexpr double kBody[4] = {0.4, 0.2, 0.06, 0.04};
   if (collision != LBM_COLL_BGK) return false;
-  const Rates& r = kRates[storage_row(precision)][forces ? 1 : 0];
+  const int row = storage_row(precision);
+  if (w.nodes < kLeast[row] || w.body_nodes > kBody[row] * w.nodes) return false;
+  const Rates& r = kRates[row][forces ? 1 : 0];
   const double single = r.start + 1e-6 * (r.strips * w.strips + r.nodes * w.nodes + r.body * w.body);
   const double windows =
       r.begin + 1e-6 * (r.plain * w.plain + r.coded * w.coded + r.body_windows * w.body);
-  // (Nothing smaller was fitted: lattices are tiles there, and batches few.)
-  return w.strips >= 1.8e5 && std::max(r.least, windows) < 0.97 * single;
+  const double ratio = kRatio[row][forces ? 1 : 0][(batch ? 2 : 0) + (moving ? 1 : 0)];
+  return ratio * std::max(r.least, windows) < single;
 }
 
 bool batch_tiles_pay(const StepWork& w) {
@@ -425,7 +446,8 @@ bool batch_tiles_pay(const StepWork& w) {
   return w.body_nodes >= 1e5;
 }
 
-int tile_rows(int precision, int collision, bool forces, double summed, int nx, int ny, bool wide) {
+int tile_rows(int precision, int collision, bool forces, double summed, int nx, int ny, bool wide,
+              bool moving) {
   // Small lattices are bound by latency: a launch of one step takes 3.4 us, with forces 5.2 as
   // each strip of the body sums 12 components, however few nodes there are.  Three steps of a
   // tile take 6 and 10, as long as there is no more than one block a CU; then a second round of
@@ -444,21 +466,30 @@ int tile_rows(int precision, int collision, bool forces, double summed, int nx, 
   //   4.1 : 3.7).
   // The regularized collision is left to single steps: its compiled form rounds differently here.
   if (collision == LBM_COLL_REGULARIZED) return 0;
-  // The most blocks of 8 rows, by storage: BGK without and with forces, entropic likewise.
+  // The most blocks of 8 rows, by storage: BGK without and with forces, entropic likewise.  512 are two
+  // rounds of the chip: binary32 600 x 375 (470) 0.90 of single steps, 724 x 362 (552) 1.06; binary16
+  // 0.87 and 1.11; entropic binary32 0.92 and 1.11.  Where a second round takes more than it gives, it
+  // is 256: entropic binary64 515 x 234 (270) 1.33, stochastically rounded 1.18, binary16 640 x 234
+  // (300) 1.08.
   constexpr int kMost[4][4] = {
-      {400, 1100, 256, 400}, {480, 480, 256, 400}, {256, 400, 256, 256}, {400, 400, 256, 400}};
+      {400, 1100, 256, 400}, {512, 512, 512, 400}, {256, 400, 256, 256}, {512, 512, 256, 400}};
   const int row = storage_row(precision);
   const bool bgk = collision == LBM_COLL_BGK;
   const int strips = strips_across(nx), last = nx % kStripW;
   const int64_t blocks = int64_t(strips) * ((ny + 7) / 8);
-  // A wave of at most 8 lanes takes longer than a full one, and it does here in every step: entropic
-  // binary64 without forces, 192 x 80 4.0 : 3.2, 193 x 80 to 200 x 80 3.9 : 4.8, 201 x 80 3.9 : 3.2.
-  if (row == 0 && !bgk && !forces && strips > 1 && last >= 1 && last <= 8) return 0;
+  // A wave of at most 8 lanes takes longer than a full one, and it does here in every step, where a
+  // single step's block of four strips hides it: entropic binary64 without forces, single steps :
+  // tiles, 192 x 80 4.0 : 3.2, 193 x 80 to 200 x 80 3.9 : 4.8, 201 x 80 3.9 : 3.2; of five strips
+  // or three no more than others (130 x 156 0.81, 385 x 100 0.81).
+  if (row == 0 && !bgk && !forces && strips % 4 == 0 && last >= 1 && last <= 8) return 0;
   int most = kMost[row][(bgk ? 0 : 2) + (forces ? 1 : 0)];
   // Binary32 gains longer where a body's strips are summed: with forces 724 x 362 (552) without a body
   // 1.10 of single steps, with a cylinder or an airfoil (8 % of the strips) 0.96 and 0.99, with scattered
-  // solids everywhere 0.73; 1700 x 212 (729) with a cylinder (3 %) 0.91.
-  if (row == 1 && bgk && forces && summed >= 0.025) most = 730;
+  // solids everywhere 0.73; 1700 x 212 (729) with a cylinder (3 %) 0.91; but 1.04 to 1.1 if it spins.
+  if (row == 1 && bgk && forces && summed >= 0.025 && !moving) most = 730;
+  // Binary16 without forces, 600 x 300 (380) with a spinning cylinder 1.07 to 1.15 of single steps (at
+  // rest 0.99), 200 blocks 0.78.
+  if (row == 3 && bgk && !forces && moving) most = 256;
   // Binary64 gains up to 2000 blocks where windows do not (37 x 12500 19.4 : 16.0 with forces, 18.1 : 14.2
   // without, windows 24.5 and 19.7), if the strips are at least half full.
   if (wide && row == 0 && bgk) most = 2000;
@@ -467,16 +498,17 @@ int tile_rows(int precision, int collision, bool forces, double summed, int nx, 
   return strips * ((ny + 3) / 4) <= 256 ? 4 : 8;
 }
 
-FuseMap step_map(const Plan& p, int precision, int collision, bool forces, int elem_bytes) {
+FuseMap step_map(const Plan& p, int precision, int collision, bool forces, int elem_bytes,
+                 bool moving) {
   const double summed = p.nslots / (double(strips_across(p.nx)) * p.ny);
-  if (const int rows = tile_rows(precision, collision, forces, summed, p.nx, p.ny, false))
+  if (const int rows = tile_rows(precision, collision, forces, summed, p.nx, p.ny, false, moving))
     return tile_map(p, rows);
   if (collision != LBM_COLL_BGK) return FuseMap{};
   const FuseMap m = fuse_map(p, elem_bytes, int64_t(p.nx) * p.ny);
   StepWork w;
   w.add(p, m, elem_bytes);
-  if (fuse_pays(precision, collision, forces, w)) return m;
-  const int rows = tile_rows(precision, collision, forces, summed, p.nx, p.ny, true);
+  if (fuse_pays(precision, collision, forces, w, moving, false)) return m;
+  const int rows = tile_rows(precision, collision, forces, summed, p.nx, p.ny, true, moving);
   return rows ? tile_map(p, rows) : FuseMap{};
 }
 
@@ -486,7 +518,7 @@ FuseMap keep_map(const Plan& p, int precision, int collision) {
   // tiles, in ms of the whole reverse sweep: binary32 1024 x 512 10.9 : 10.5, 2048 x 1024 13.0 :
   // 12.9, binary64 21.5 : 19.3, 26.2 : 23.7; stochastically rounded 16 x 12000, whose strips are a
   // quarter full, 6.8 : 7.5.
-  int rows = tile_rows(precision, collision, false, 0.0, p.nx, p.ny, false);
+  int rows = tile_rows(precision, collision, false, 0.0, p.nx, p.ny, false, false);
   const bool full = p.nx * 2 >= strips_across(p.nx) * kStripW;
   const bool binary32 = precision == LBM_FP32 || precision == LBM_FP32DEV;
   if (rows == 0 && collision == LBM_COLL_BGK && full &&

@@ -216,7 +216,8 @@ FuseMap fuse_map(const Plan& p, int elem_bytes, int64_t nodes);
 FuseMap tile_map(const Plan& p, int rows);
 // Rows of its tiles where they are the fastest form for an nx x ny lattice, else 0.  `summed`: the
 // share of its strips that have force terms to sum; `wide`: windows are not the fastest form.
-int tile_rows(int precision, int collision, bool forces, double summed, int nx, int ny, bool wide);
+int tile_rows(int precision, int collision, bool forces, double summed, int nx, int ny, bool wide,
+              bool moving);
 
 // What a launch has to compute for a lattice, or for those of a batch together, in lanes times
 // rows: by single steps (lanes of strips, idle ones included, and nodes), and by fused launches
@@ -228,15 +229,18 @@ struct StepWork {
   void add(const Plan& p, const FuseMap& m, int elem_bytes);
 };
 
-// Whether fused launches are faster than single steps for it.
-bool fuse_pays(int precision, int collision, bool forces, const StepWork& w);
+// Whether fused launches are faster than single steps for it, of one lattice or a batch, with bodies
+// at rest or in motion.
+bool fuse_pays(int precision, int collision, bool forces, const StepWork& w, bool moving,
+               bool batch);
 // Whether the body rectangles of a batch's fused launches with forces are faster as tiles, in a
 // launch of their own.
 bool batch_tiles_pay(const StepWork& w);
 
 // Work map of the fastest form for steps of p between two alternating buffers: windows or tiles,
-// or a map without blocks for single steps.
-FuseMap step_map(const Plan& p, int precision, int collision, bool forces, int elem_bytes);
+// or a map without blocks for single steps.  `moving`: the body is in motion.
+FuseMap step_map(const Plan& p, int precision, int collision, bool forces, int elem_bytes,
+                 bool moving);
 // The same for steps without forces whose states are all kept.
 FuseMap keep_map(const Plan& p, int precision, int collision);
 

@@ -463,9 +463,9 @@ def test_batch_with_tiled_body_rectangles_bitwise_equals_singles(precision):
 
 @pytest.mark.gpu
 def test_batch_whose_bodies_take_all_of_the_lattices():
-    """Control volumes that span the lattices: with forces every node is in a body rectangle, so
-    the launches of tiles leave the launches of windows nothing but the force rows.  Members
-    bitwise equal to lattices stepped alone, in calls of 3 and 4 steps."""
+    """Control volumes that span the lattices: every node is in a body rectangle, so launches of
+    three steps would be launches of body windows alone.  Members bitwise equal to lattices
+    stepped alone, in calls of 3 and 4 steps."""
     from paper_2210_10377_amd import Batch, Sim
     nx, ny, n = 512, 256, 60
     mask = np.zeros((ny, nx), np.uint8)
@@ -511,6 +511,45 @@ def test_autotune_times_what_the_schedule_governs(schemes):
         alone = Batch.from_workloads([ws[i]], precision="fp64", max_record=12).members[0]
         alone.step(7 + 40 * 9 + 6, schemes=())
         np.testing.assert_array_equal(b.members[i].populations(), alone.populations())
+
+
+@pytest.mark.gpu
+def test_motion_that_begins_in_a_batch_brings_launches_of_three_steps():
+    """Binary32 lattices of which single steps are the faster form at rest and launches of three
+    steps with a body in motion: each takes its form, from the call after the change on, back again
+    too, and the members stay bitwise equal to lattices stepped alone."""
+    from paper_2210_10377_amd import Batch, Sim
+    nx, ny, n = 200, 80, 62
+    mask = np.zeros((ny, nx), np.uint8)
+    mask[40:66, 50:76] = 1
+    box = (48, 78, 38, 68)
+    rng = np.random.default_rng(29)
+    uin = [0.05 * (1 + 0.1 * rng.uniform(-1, 1, ny)) for _ in range(n)]
+
+    def member(i):
+        return Sim(mask, 0.6 + 0.002 * i, uin[i], precision="fp32", box=box, max_record=8)
+
+    def spin(sim, omega):
+        sim.set_body_motion(omega=omega, xc=63.0, yc=53.0)
+
+    sims = [member(i) for i in range(n)]
+    b = Batch(sims, max_record=8)
+    F, forms = [], []
+    for omega in (0.0, 1e-4, 0.0):
+        print(f"batch motion omega={omega}", flush=True)
+        spin(sims[5], omega)
+        b.step(7)
+        F.append(b.forces()[0])
+        forms.append(b.launches())
+    assert forms == [(7, 0), (8, 2), (15, 2)]
+    for i in (0, 5, n - 1):
+        alone = member(i)
+        for omega, f in zip((0.0, 1e-4, 0.0), F):
+            if i == 5:
+                spin(alone, omega)
+            alone.step(7)
+            np.testing.assert_array_equal(f[i], alone.forces())
+        np.testing.assert_array_equal(sims[i].populations(), alone.populations())
 
 
 @pytest.fixture(scope="module")

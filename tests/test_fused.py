@@ -227,8 +227,9 @@ FORM = r"""
 #include "plan.h"
 using namespace lbm;
 int main() {
-  int count, nx, ny, precision, collision, forces;
-  while (std::scanf("%d %d %d %d %d %d", &count, &nx, &ny, &precision, &collision, &forces) == 6) {
+  int count, nx, ny, precision, collision, forces, moving, side;
+  while (std::scanf("%d %d %d %d %d %d %d %d", &count, &nx, &ny, &precision, &collision, &forces, &moving,
+                    &side) == 8) {
     lbm_grid g{};
     g.nx = nx;
     g.ny = ny;
@@ -237,7 +238,7 @@ int main() {
     g.max_record = 1;
     for (int k = 0; k < 4; ++k) g.box[k] = -1;
     std::vector<uint8_t> mask(size_t(nx) * ny, 0);
-    const int w = std::max(1, std::min(12, nx / 6)), h = std::max(1, std::min(12, ny / 6));
+    const int w = std::max(1, std::min(side, nx / 3)), h = std::max(1, std::min(side, ny / 3));
     for (int y = ny / 2; y < ny / 2 + h; ++y)
       for (int x = nx / 4; x < nx / 4 + w; ++x) mask[size_t(y) * nx + x] = 1;
     if (nx >= 12 && ny >= 12) {
@@ -251,7 +252,7 @@ int main() {
     if (build_plan(g, mask.data(), p, err) != LBM_OK) return 1;
     const int esz = precision == LBM_FP64 ? 8 : (precision == LBM_FP16DEV ? 2 : 4);
     if (count == 1) {
-      const FuseMap m = step_map(p, precision, collision, forces != 0, esz);
+      const FuseMap m = step_map(p, precision, collision, forces != 0, esz, moving != 0);
       std::printf("%s\n", m.nblocks == 0 ? "single" : (m.tile_rows ? "tiles" : "windows"));
       continue;
     }
@@ -259,7 +260,7 @@ int main() {
     one.add(p, fuse_map(p, esz, int64_t(count) * nx * ny), esz);
     for (int k = 0; k < count; ++k) all.add(p, fuse_map(p, esz, int64_t(count) * nx * ny), esz);
     if (all.nodes != count * one.nodes || one.nodes != double(nx) * ny) return 1;
-    std::printf("%s\n", fuse_pays(precision, collision, forces != 0, all) ? "windows" : "single");
+    std::printf("%s\n", fuse_pays(precision, collision, forces != 0, all, moving != 0, true) ? "windows" : "single");
   }
   return 0;
 }
@@ -302,6 +303,19 @@ FORMS = [
     (16, 400, 200, "fp32", "bgk", 0, "windows"),       # 19.1 : 14.3
     (8, 700, 350, "fp64", "bgk", 1, "windows"),        # 54 : 33
     (128, 96, 64, "fp64", "bgk", 0, "windows"),        # 26.4 : 22.4
+    (1, 130, 156, "fp64", "kbc", 0, "tiles"),          # 4.4 : 3.5 (two columns in the last strip)
+    (1, 490, 491, "fp32", "bgk", 0, "tiles"),          # two rounds of blocks
+    (1, 515, 234, "fp64", "kbc", 0, "single"),         # 1.33 of it tiles
+    (1, 515, 293, "fp32", "kbc", 0, "tiles"),
+    (1, 1020, 317, "fp32", "bgk", 0, "single"),        # 7.0 : 7.7 windows
+]
+# Bodies of the given side, at rest and in motion (the same with their forms).
+MOVING = [
+    (1, 850, 531, "fp32", "bgk", 1, 44, "windows", "single"),    # 10.1 : 10.0, 10.7 : 12.6
+    (1, 1700, 212, "fp32", "bgk", 1, 70, "tiles", "single"),     # 9.9 : 9.4, 9.6 : 10.7
+    (1, 600, 300, "fp16dev", "bgk", 0, 20, "tiles", "single"),   # 4.0 : 3.8, 4.0 : 4.3
+    (1, 2048, 1024, "fp32", "bgk", 1, 60, "windows", "windows"),
+    (62, 200, 80, "fp32", "bgk", 1, 26, "single", "windows"),    # 22 : 28, 42 : 31
 ]
 
 
@@ -314,12 +328,15 @@ def test_form_goes_by_the_work_that_a_shape_leaves(tmp_path):
     exe = tmp_path / "form"
     subprocess.check_call(["g++", "-std=c++17", "-O1", "-I", CSRC, "-I", os.path.join(ROOT, "include"),
                            str(src), os.path.join(CSRC, "plan.cpp"), "-o", str(exe)])
-    lines = "".join("%d %d %d %d %d %d\n" % (n, nx, ny, PRECISIONS[p], COLLISIONS[c], f)
-                    for n, nx, ny, p, c, f, _ in FORMS)
+    cases = [case[:6] + (0, 12, case[-1]) for case in FORMS]
+    for case in MOVING:
+        cases += [case[:6] + (moving, case[6], case[7 + moving]) for moving in (0, 1)]
+    lines = "".join("%d %d %d %d %d %d %d %d\n" % (n, nx, ny, PRECISIONS[p], COLLISIONS[c], f, moving, side)
+                    for n, nx, ny, p, c, f, moving, side, _ in cases)
     out = subprocess.run([str(exe)], input=lines, capture_output=True, text=True, timeout=120)
     got = out.stdout.split()
-    assert out.returncode == 0 and len(got) == len(FORMS)
-    wrong = [(case, form) for case, form in zip(FORMS, got) if case[-1] != form]
+    assert out.returncode == 0 and len(got) == len(cases)
+    wrong = [(case, form) for case, form in zip(cases, got) if case[-1] != form]
     assert not wrong, wrong
 
 
@@ -572,9 +589,8 @@ def test_window_and_tile_cases_take_their_forms(tmp_path):
     subprocess.check_call(["g++", "-std=c++17", "-O1", "-I", CSRC, "-I", os.path.join(ROOT, "include"),
                            str(src), os.path.join(CSRC, "plan.cpp"), "-o", str(exe)])
     cases = [(1, nx, ny, PRECISIONS[p], 0, f, "windows") for p, nx, ny, f in WINDOWS]
-    cases += [(1, nx, ny, PRECISIONS[p], COLLISIONS[c], f, "tiles") for p, c, nx, ny, f in TILES
-              if not (p == "fp64" and c == "kbc" and not f and 1 <= nx % 64 <= 8)]
-    out = subprocess.run([str(exe)], input="".join("%d %d %d %d %d %d\n" % c[:6] for c in cases),
+    cases += [(1, nx, ny, PRECISIONS[p], COLLISIONS[c], f, "tiles") for p, c, nx, ny, f in TILES]
+    out = subprocess.run([str(exe)], input="".join("%d %d %d %d %d %d 0 12\n" % c[:6] for c in cases),
                          capture_output=True, text=True, timeout=120)
     got = out.stdout.split()
     wrong = [(c, g) for c, g in zip(cases, got) if c[6] != g]
