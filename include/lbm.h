@@ -399,10 +399,10 @@ const char* lbm_last_error(const lbm_t* h);
  * precision and advances all of them together: each step is ONE kernel launch that
  * updates every instance (a sweep over the concatenated tile lists of all instances,
  * optionally by a persistent grid), and runs of launches can be replayed from captured
- * HIP graphs.  Batches large enough take three steps a launch instead (the schedule then
- * covers the steps left over).  Every instance computes exactly what lbm_step computes for it (same
- * kernels per tile, same force reduction order): populations and forces are bitwise
- * those of the member stepped alone with the same call lengths.
+ * HIP graphs.  Batches for which that is faster take three steps a launch instead (the
+ * schedule then covers the steps left over).  Every instance computes exactly what lbm_step
+ * computes for it (same kernels per tile, same force reduction order): populations and
+ * forces are bitwise those of the member stepped alone with the same call lengths.
  *
  * Ownership: the members stay owned by the caller and must outlive the batch; their
  * workspaces hold the states, which lbm_get_populations etc. read as usual.  While a
@@ -425,8 +425,9 @@ typedef struct lbm_batch_schedule {
                           grid_blocks-th tile of the list; 1 = workgroups take the
                           next 16 tiles from a device counter (one global atomic per
                           16 tiles, reset by a small kernel at each lbm_batch_step call
-                          that takes launches of one step, and by each for the next), over a list ordered
-                          largest instance first.  Results do not depend on it.      */
+                          that takes launches of one step, and by each of them for the
+                          next), over a list ordered largest instance first.  Results do
+                          not depend on it.                                          */
   int32_t tile_shape;  /* LBM_TILE_AUTO (0): every instance keeps its own tile shape;
                           LBM_TILE_WIDE / LBM_TILE_NARROW: every instance runs in
                           256 x 1 / 64 x 4 tiles in the batch (the member's own

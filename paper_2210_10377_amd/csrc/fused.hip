@@ -10,8 +10,10 @@
 // between waves and no LDS is used.  A third of the bytes per step remains, and vector
 // arithmetic (about 115 instructions per node and step in binary32, and a fifth more on margins)
 // comes to bound it together with HBM.  Measured at 8192 x 4096 in binary32, all forces: 396 us a
-// step by single steps, 171 - 177 us fused (196 GLUPS; 2.92 GB counted per launch of 541 us,
-// 5.4 TB/s, where three single steps move 7.25); 2048 x 1024 in binary64 52 and 29 us.
+// step by single steps, fused 173 in a run of 2000 steps (194 GLUPS), 191 in one of 12, and 222 in
+// one of 20, of which two are single steps (each run ends with a sweep over the control volume);
+// 2.92 GB counted per launch of 541 us, 5.4 TB/s, where three single steps move 7.25; 2048 x 1024
+// in binary64 52 and 29 us.
 //
 // The windows of the plain rectangles own 56 of their 64 lanes, 8 bytes of columns a lane, so
 // that every store covers whole 64-byte sectors.  That decides: windows of 60 binary32 columns

@@ -2,8 +2,9 @@
 // the per-step forces (A, B, DRTT terms, SI), the control-volume momentum sweep, and the
 // fixed-order reductions of the force partials into ring rows.
 //
-// One launch per step (two where the strips with force terms have their own).  A block of 256 threads covers a tile of 256 nodes along x in one
-// (y, z) row; each wave a 64-node strip whose class (strip table) picks its path:
+// One launch per step (two where the strips with force terms have their own).  A block of 256
+// threads covers a tile of 256 nodes along x in one (y, z) row; each wave a 64-node strip whose
+// class (strip table) picks its path:
 //   plain / box-J: 27 loads at fixed offsets (no boundary within reach), collision,
 //     27 non-temporal stores; box-J strips add the momentum of their pulled populations;
 //   general: the node word and the coordinates select, per direction, plain streaming,
@@ -15,7 +16,7 @@
 // strip's launch, while it branched on every direction of the pull and of the link terms and
 // summed over lanes through LDS; without branches (selects by bit masks, walls and wrapped
 // rows scalar), with lane sums by register swaps and rotations, and in the step's own launch
-// it takes 11.
+// it takes 12.
 // The first block of a launch reduces the previous step's slots, in a fixed order, into
 // that step's ring row.  Blocks are mapped to tiles so that runs of kXcdRun (8)
 // neighbouring tiles along x go to one XCD (their +-1-shifted pulls share cache lines in
